@@ -241,25 +241,23 @@ lb_status lb_bead_positions(lb_handle* h, double* host_out, size_t bytes);
  * steps the 64-node segments around chains above 256 beads in boxes they do
  * not cover densely are collided beside the other nodes once the chain's
  * impulses are in; batched = 2 re-collides the chain's nodes after the
- * collide instead.  Batched steps launched directly (graph_steps = 0) of
- * boxes with chains of at most 256 beads only, no dense box and at most 2^20
- * nodes in all run each step's coupling and the re-collision of its nodes
- * on one queue, the collide beside them on the other (batched = 2, and graph
- * replays, keep the re-collision behind the collide on the handle's
- * stream).  All forms compute the same bits.
+ * collide instead.  Batched steps of boxes whose chains all have at most 256
+ * beads run as one kernel each (batched = 2: separate kernels, the chain's
+ * nodes re-collided).  All forms compute the same bits.
  * graph_steps > 0 records that many LB steps (rounded up to even) in a HIP
  * graph and replays it; 0 launches kernels directly.  The graphs of both
  * buffer parities are recorded and instantiated here, before returning
- * (synchronous), so that lb_step only replays them.  Exception: batched FP32
- * steps whose chains all exceed 256 beads (and cover no box densely) are
- * always launched directly: each collide there carries the step's node
- * tables and a resident chain kernel waits for them, an order that graph
- * replay does not keep (a stream under capture takes a graph-safe form).
+ * (synchronous), so that lb_step only replays them.  Only steps that keep to
+ * one stream are recorded: the per-box form, one-kernel steps, boxes without
+ * beads, and boxes that their beads all cover densely; the other batched forms, whose steps put kernels on two
+ * streams, are always launched directly.  Batched FP32 steps whose chains all
+ * exceed 256 beads (and cover no box densely) put each step's node tables
+ * into its collide, with a resident chain kernel that waits for them (a
+ * stream under capture takes another form).
  * Such a run also needs the GPU to run kernels of its two streams at once;
  * where a tool runs one kernel at a time (hardware counter collection), the
  * wait gives up and LB_HEALTH_SYNC is set.  batched = 3 is batched = 1
- * without that layout: the node tables get a kernel of their own, and
- * graph_steps applies.
+ * without that layout: the node tables get a kernel of their own.
  * LB_EINVAL for batched outside 0..3 or graph_steps < 0, LB_ESTATE with
  * impulses pending, LB_EDEVICE if capture or instantiation fails. */
 lb_status lb_set_launch(lb_handle* h, int32_t batched, int32_t graph_steps);

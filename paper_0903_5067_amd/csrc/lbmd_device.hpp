@@ -27,6 +27,7 @@ struct BoxDev {
     int32_t therm;       // 0 none, 1 stress modes, 2 all non-conserved modes
     int32_t substeps;
     int32_t couple_T;    // lanes per bead on the one-workgroup coupling path (a function of N only)
+    int32_t adj_T;       // the same for its reverse
     int32_t chain_len;   // beads per chain (> 0; N for a single chain)
     int32_t dense;       // 1: beads cover much of the box; its collide follows the coupling and
                          // takes the node impulses itself (no fix-up pass)
@@ -62,6 +63,8 @@ struct Ctrl {
     uint32_t ovf_flag[2];   // [t & 1]: the deferral stamp of step t if it listed any such impulse
     uint32_t head_done[2];  // [t & 1]: node-table workgroups of step t's collide that are done
     uint32_t head_fix[2];   // [t & 1]: those that have done their part of step t-1's overflow fix-up
+    uint32_t step_pend[2];  // one-kernel steps, [t & 1]: the deferral stamp of step t if some box listed impulses
+                            // outside its set-aside nodes
 };
 
 // Deferral is decided per segment of DSEG consecutive nodes of a box (one

@@ -24,6 +24,9 @@
 //                 records turned into node impulses
 //   k_fixup       re-collides the nodes the beads touched, with their
 //                 impulse, and overwrites their outputs
+//   k_step        a batched step of chains of up to 256 beads in one kernel:
+//                 the first workgroups do k_couple's work and collide the
+//                 beads' nodes, which the tiles of the others skip
 //   k_collide_deferred, k_overflow
 //                 batched steps with chains of 257..1024 beads in sparse
 //                 boxes: the tiles holding the beads' node tables skip the
@@ -73,6 +76,21 @@ __device__ __forceinline__ void gather_pre(const R* __restrict__ a, const Upwind
     for (int i = 0; i < 19; ++i) {
         const uint64_t q = pop_at(i, up.src(i));
         d[i] = NT ? __builtin_nontemporal_load(a + q) : a[q];
+    }
+}
+
+// the pre-collision populations of node `up` with 32-bit offsets from the
+// box's array (valid while that array is under 4 GiB): a uniform base and one
+// 32-bit offset per load instead of 64-bit address arithmetic
+template <typename R>
+__device__ __forceinline__ void gather_pre32(const R* __restrict__ a, const Upwind& up, R d[19])
+{
+    const char* base = (const char*)a;
+#pragma unroll
+    for (int i = 0; i < 19; ++i) {
+        const uint32_t s = up.src(i);
+        const uint32_t e = ((s >> PTILE_LOG) * 19u + (uint32_t)i) * PTILE + (s & (PTILE - 1u));
+        d[i] = *(const R*)(base + (uint64_t)(e * (uint32_t)sizeof(R)));
     }
 }
 
@@ -221,48 +239,33 @@ __device__ __forceinline__ void stencil_velocities(const R* __restrict__ a, cons
     }
 }
 
-// stencil_velocities over the T lanes of one bead (T = 8 / NK, or 16 with the
-// upper eight lanes repeating the lower): lane l gathers corners l, l + T8,
-// ... (NK of them, T8 = 8 / NK), and the lanes then exchange them, so that
-// every lane ends with all eight corners, computed as stencil_velocities
-// computes them
-template <typename R, int NK>
-__device__ __forceinline__ void stencil_shared(const R* __restrict__ a, const int i0[3], int L, double rho0,
-                                               double inv_tau, int lane, int T, R u[8][3])
+// node at (ix, iy, iz), each at most one box edge outside
+__device__ __forceinline__ uint32_t node_of(int ix, int iy, int iz, int L)
 {
-    constexpr int T8 = 8 / NK;
-    R d[NK][19];
-    const int k0 = lane & (T8 - 1);
+    ix = ix >= L ? ix - L : (ix < 0 ? ix + L : ix);
+    iy = iy >= L ? iy - L : (iy < 0 ? iy + L : iy);
+    iz = iz >= L ? iz - L : (iz < 0 ? iz + L : iz);
+    return (uint32_t)ix + (uint32_t)L * ((uint32_t)iy + (uint32_t)L * (uint32_t)iz);
+}
+
+// fluid velocity of one node in MD units (u = j / rho / tau_lb) from its
+// gathered pre-collision deviations
+template <typename R>
+__device__ __forceinline__ void node_velocity(const R d[19], double rho0, double inv_tau, R u[3])
+{
+    double rho = 0.0, jx = 0.0, jy = 0.0, jz = 0.0;
 #pragma unroll
-    for (int k = 0; k < NK; ++k) {
-        const int kk = k0 + k * T8;
-        const int ix = i0[0] + (kk & 1), iy = i0[1] + ((kk >> 1) & 1), iz = i0[2] + ((kk >> 2) & 1);
-        const Upwind up((uint32_t)(ix >= L ? ix - L : ix), (uint32_t)(iy >= L ? iy - L : iy),
-                        (uint32_t)(iz >= L ? iz - L : iz), (uint32_t)L);
-        gather_pre<R, false>(a, up, d[k]);
+    for (int i = 0; i < 19; ++i) {
+        const double di = (double)d[i];
+        rho += di;
+        if (cxv(i)) jx += cxv(i) * di;
+        if (cyv(i)) jy += cyv(i) * di;
+        if (czv(i)) jz += czv(i) * di;
     }
-    R own[NK][3];
-#pragma unroll
-    for (int k = 0; k < NK; ++k) {
-        double rho = 0.0, jx = 0.0, jy = 0.0, jz = 0.0;
-#pragma unroll
-        for (int i = 0; i < 19; ++i) {
-            const double di = (double)d[k][i];
-            rho += di;
-            if (cxv(i)) jx += cxv(i) * di;
-            if (cyv(i)) jy += cyv(i) * di;
-            if (czv(i)) jz += czv(i) * di;
-        }
-        rho += rho0;
-        own[k][0] = (R)(jx / rho * inv_tau);
-        own[k][1] = (R)(jy / rho * inv_tau);
-        own[k][2] = (R)(jz / rho * inv_tau);
-    }
-    // corner k sits in slot k / T8 of lane k % T8 of the bead's lanes
-#pragma unroll
-    for (int k = 0; k < 8; ++k)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) u[k][c] = __shfl(own[k / T8][c], k % T8, T);
+    rho += rho0;
+    u[0] = (R)(jx / rho * inv_tau);
+    u[1] = (R)(jy / rho * inv_tau);
+    u[2] = (R)(jz / rho * inv_tau);
 }
 
 constexpr int MAXB = 1024;
@@ -369,232 +372,410 @@ __global__ __launch_bounds__(1024) void k_init_forces(const BoxDev* __restrict__
     }
 }
 
-// hand one stencil's accumulated impulse (MD units) to the dense field and
-// list the nodes; no result is waited on
-__device__ __forceinline__ uint32_t flush_stencil(const ChainArgs& ca, uint64_t node_off, uint64_t g,
-                                                  const uint32_t cnode[8], double acc[8][3], double tau,
-                                                  int& tcnt)
+// value of v in another lane of the same 16-lane row, by a DPP lane move of
+// both 32-bit halves (CTRL: a gfx9 DPP control; every source lane is active)
+template <int CTRL>
+__device__ __forceinline__ double dpp_from(double v)
 {
-    uint32_t hb = 0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        unsigned long long* dst = ca.imp + 3 * (node_off + cnode[k]);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            double v = acc[k][c] * tau;      // lattice momentum units
-            if (!(fabs(v) < IMP_MAX)) { hb |= H_FIXED; v = 0.0; }
-            atomicAdd(dst + c, (unsigned long long)(long long)llrint(v * IMP_SCALE));
-        }
-        if (tcnt < ca.touch_cap) ca.touched[g * ca.touch_cap + tcnt] = cnode[k];
-        else hb |= H_TABLE;
-        ++tcnt;
-    }
-    return hb;
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
+    return __hiloint2double(hi, lo);
 }
 
-// One workgroup per chain; T lanes per bead split the pair loop.  Threads
-// 0..T*Npad-1: bead b = tid / T, lane = tid % T.  All T lanes of a bead
-// compute the same bead update (their force partial sums are combined by a
-// butterfly, which gives every lane the same bits); lane 0 writes.
-// Lane l of bead b owns the partners j = l, l + T, l + 2T, ... (j != b).  It
-// keeps the ones within the list radius (cut-off plus NL_SKIN) in its own
-// list, in ascending j, built at the first substep and again whenever some
-// bead of the chain has moved more than half the skin since the last build:
-// every partner within the cut-off is then on the list, and the list holds
-// them in the order of the full scan, so the forces are the same bits.  A
-// lane whose partners within the list radius exceed its slots scans all of
-// them instead.
-constexpr int CPL_SLOTS = 32;   // list slots per lane of the one-workgroup coupling kernel
-template <typename R, int MAXT = 256>
+// value of component c's lane (c = 0, 1, 2) of the quad
+template <int C>
+__device__ __forceinline__ double quad_value(double v) { return dpp_from<C * 0x55>(v); }
+
+// Repulsive LJ on a bead at x from up to U of its partners j[u] (those with
+// ok[u]): the separations and the two divisions of all U run side by side,
+// without a branch each; the forces are added in order of u.
+template <int U>
+__device__ __forceinline__ void wca_add(const double x[3], const double* xs, const int j[U], const bool ok[U],
+                                        double Ld, double iL, double rc2, double sigsq, double eps24, double F[3])
+{
+#pragma clang fp contract(on)
+    double d[U][3], r2[U];
+    bool hit[U], any = false;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            d[u][c] = x[c] - xs[3 * j[u] + c];
+            d[u][c] -= Ld * rint(d[u][c] * iL);
+        }
+        r2[u] = d[u][0] * d[u][0] + d[u][1] * d[u][1] + d[u][2] * d[u][2];
+        hit[u] = ok[u] && r2[u] < rc2;
+        any |= hit[u];
+    }
+    if (any) {
+        double gf[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const double ir2 = 1.0 / (hit[u] ? r2[u] : 1.0);
+            const double s2 = sigsq * ir2;
+            const double s6 = s2 * s2 * s2;
+            gf[u] = eps24 * s6 * (2.0 * s6 - 1.0) * ir2;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (hit[u]) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) F[c] += gf[u] * d[u][c];
+            }
+    }
+}
+
+// The substeps of one LB step for a chain of at most BIG_CHAIN beads, by one
+// workgroup: T lanes per bead (a function of N only), bead b = thread / T.
+// What bounds it is the serial chain of a substep (drift, positions to LDS,
+// barrier, pair forces, interpolation, kick) at one or a few wavefronts per
+// SIMD, so the lanes share a bead's work:
+//   - lane l holds component c = l mod 4 of the bead (position, velocity,
+//     force, the eight stencil velocities and impulses); the fourth lane of a
+//     quad repeats the third, further quads the first;
+//   - the partners of the pair forces are split over `cls` lanes (the 16, 8,
+//     4, 2 or 1 lanes that 256 threads hold per bead): lane l sums those with
+//     j = l (mod cls), ascending, then a butterfly adds the lanes' sums.
+//     Chains above 64 beads have 4 lanes each and cls = 2 or 1: lanes repeat
+//     a class rather than split it further, which would change the sums;
+//   - lanes 0 and 1 take the bonds to b - 1 and b + 1;
+//   - the noise: lane l draws the words of substeps l, l + T, ..., handed
+//     over by a shuffle ahead of the barrier;
+//   - a new stencil's populations are gathered by corner: lane l takes corners
+//     l mod T8, + T8, ... (T8 = min(T, 8)).
+// Lanes exchange values by DPP moves within the quad (a few cycles, where a
+// shuffle through LDS takes ~60 per stage).  Positions alternate between two
+// LDS buffers, so a substep has one barrier.
+// Pair lists (chains above 16 beads): the partners of a lane's class within
+// the list radius (cut-off plus NL_SKIN) are bits of one 64-bit word (four
+// words for cls = 1), set at the first substep and again whenever a coordinate
+// of some bead has moved more than half the skin / sqrt(3); the exact cut-off
+// decides, so the list's age does not show in the bits.
+// Measured per substep beside the step's tiles: 16 beads 0.84 us, 32 1.15,
+// 64 1.5, 128 2.7, where lanes that each repeated the whole bead but its pair
+// forces took 2.1, 1.9, 2.0 and 3.1 us (alone).
+
+// the same value, unknown to the compiler: keeps the addresses of rare paths
+// from being computed ahead of the substep loop and held through it
+__device__ __forceinline__ int here(int v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+__device__ __forceinline__ double here(double uniform)
+{
+    asm volatile("" : "+s"(uniform));
+    return uniform;
+}
+
+template <int MB>   // most beads
+struct ChainLds {
+    union {
+        struct {
+            double xs[2][3 * MB];   // positions of this and the previous substep
+        };
+        uint32_t hash[MB >= 256 ? 4096 : 1024];   // after the substeps: nodes set aside for the next step
+    };
+    int moved[3];                  // per substep mod 3: a bead moved past half the skin
+    uint32_t n_ovf, n_next;        // one-kernel steps: impulses outside the set-aside nodes, next step's such nodes
+};
+// ONE: the step is one kernel (k_step): `mask` holds this step's set-aside
+// nodes, impulses on other nodes are listed in the box's touched slots,
+// sh.n_ovf of them; xe, ve return the bead's end position and velocity.
+template <typename R, int T, bool ONE, int MB>
+__device__ __forceinline__ uint32_t chain_substeps(const BoxDev& bx, const R* __restrict__ A, const ChainArgs& ca,
+                                                   uint32_t t, ChainLds<MB>& sh,
+                                                   const unsigned long long* __restrict__ mask, double xe[3],
+                                                   double ve[3])
+{
+#pragma clang fp contract(on)
+    constexpr int T8 = T < 8 ? T : 8, NC = 8 / T8;   // corners gathered per lane
+    constexpr bool LISTS = T < 16;                   // T = 16: one partner per lane at most
+    constexpr int U = T == 4 ? 2 : 1;                // partners tested side by side
+    constexpr int NW = MB > 64 && T == 4 ? 4 : 1;    // list words per lane
+    constexpr int NQ = T / 4;                        // quads per bead
+    const int N = bx.N, L = bx.L;
+    const int cls = T > 4 || MB <= 64 ? T : (N <= 64 ? 4 : (N <= 128 ? 2 : 1));
+    const int b = (int)threadIdx.x / T, lane = (int)threadIdx.x % T;
+    const bool act = b < N;
+    const int c = (lane & 3) < 3 ? lane & 3 : 2;   // this lane's component
+    const bool own = lane < 3;                     // the lanes that store the bead
+    const uint64_t g = bx.bead_off + (uint64_t)(act ? b : 0);
+    const ChainSpan sp = chain_span(bx, act ? b : 0);
+    const double Ld = (double)L, iL = bx.inv_L;
+    const double dt = bx.dt, hdt_m = 0.5 * dt / bx.mass;
+    const double eps24 = 24.0 * bx.eps;
+    const R* a = A + bx.pop_off;
+    const bool off32 = pop_elems_of((uint64_t)L * L * L) * sizeof(R) < (1ull << 32);
+    // bonded partners (the bead itself, a zero separation, where there is none)
+    const int jb0 = act && b > sp.lo ? b - 1 : (act ? b : 0), jb1 = act && b < sp.hi ? b + 1 : (act ? b : 0);
+    const int jb = lane & 1 ? jb1 : jb0;
+    if (threadIdx.x < 3) sh.moved[threadIdx.x] = 0;
+
+    double x = 0.0, v = 0.0, f = 0.0, fc = 0.0;
+    if (act) {
+        x = ca.x[3 * g + c]; v = ca.v[3 * g + c]; f = ca.f[3 * g + c];
+        if (ca.tape_x0 && own) {   // the step's starting beads, for the adjoint
+            ca.tape_x0[3 * g + c] = x;
+            ca.tape_x0[ca.tape_vo + 3 * g + c] = v;
+            ca.tape_x0[ca.tape_fo + 3 * g + c] = f;
+        }
+    }
+    int cb = -1;                  // base cell of the cached stencil, this component
+    uint32_t base = 0;            // its base node, all components
+    // component c of the stencil's node velocities (MD units), kept in the
+    // storage precision: FP32 storage carries no more digits than that
+    R cu[8];
+    double acc[8];                // impulse accumulated on them (MD units)
+    uint32_t aside = 0;           // ONE: bit k: corner k's node is set aside
+    uint32_t hbits = 0;
+    int tcnt = 0;
+    double x0 = 0.0;              // position at the last list build
+    unsigned long long nl[NW] = {};   // partners of the lane's class within the list radius
+    U4 pw{0, 0, 0, 0};            // noise words of this lane's substep
+
+    // hand the accumulated impulses over, quad by quad: fixed-point adds that
+    // nothing waits on; the bead lists the nodes
+    auto flush = [&]() __attribute__((always_inline)) {
+        const int lane = here((int)threadIdx.x % T), c = (lane & 3) < 3 ? lane & 3 : 2;
+        const uint64_t g = bx.bead_off + (uint64_t)here(b);
+        const double tau = here(bx.tau_lb);
+        const uint32_t LL = (uint32_t)L * (uint32_t)L;
+        const uint32_t bz = base / LL, rem = base - bz * LL, by = rem / (uint32_t)L, bx_ = rem - by * (uint32_t)L;
+        const int q = lane >> 2;
+#pragma unroll
+        for (int kk = 0; kk < 8 / NQ; ++kk) {
+            // quad q takes corners q, q + NQ, ...
+            const double a0 = acc[NQ * kk], a1 = acc[NQ * kk + (NQ > 1 ? 1 : 0)], a2 = acc[NQ * kk + (NQ > 2 ? 2 : 0)],
+                         a3 = acc[NQ * kk + (NQ > 2 ? 3 : 0)];
+            const double ak = q == 0 ? a0 : (q == 1 ? a1 : (q == 2 ? a2 : a3));
+            const int k = NQ * kk + q;
+            const uint32_t node = node_of((int)bx_ + (k & 1), (int)by + ((k >> 1) & 1), (int)bz + (k >> 2), L);
+            if ((lane & 3) < 3) {
+                double m = ak * tau;      // lattice momentum units
+                if (!(fabs(m) < IMP_MAX)) { hbits |= H_FIXED; m = 0.0; }
+                atomicAdd(ca.imp + 3 * (bx.node_off + node) + c, (unsigned long long)(long long)llrint(m * IMP_SCALE));
+            } else if (ONE) {
+                // at most 8 per bead and stencil, so the box's slots hold them
+                if (!((aside >> k) & 1u)) ca.touched[bx.bead_off * ca.touch_cap + atomicAdd(&sh.n_ovf, 1u)] = node;
+            } else {
+                const int slot = tcnt + k;
+                if (slot < ca.touch_cap) ca.touched[g * ca.touch_cap + slot] = node;
+                else hbits |= H_TABLE;
+            }
+        }
+        tcnt += 8;
+    };
+
+    for (int s = 0; s < bx.substeps; ++s) {
+        double* xs = sh.xs[s & 1];
+        double fr = 0.0, nz = 0.0;
+        int ii = 0;
+        if (act) {
+            v += f * hdt_m;
+            x += v * dt;
+            if (own) {
+                xs[3 * b + c] = x;
+                if (LISTS && s > 0 && fabs(x - x0) > 0.5 * NL_SKIN * 0.577) sh.moved[s % 3] = 1;
+            }
+            // ahead of the barrier: what depends on the bead alone
+            if (s % T == 0) pw = philox10(U4{(uint32_t)b, t, (1u << 16) | (uint32_t)(s + lane), 0u}, bx.seed, bx.box_id);
+            const uint32_t w0 = __shfl(pw.x, s % T, T), w1 = __shfl(pw.y, s % T, T), w2 = __shfl(pw.z, s % T, T);
+            nz = unit_noise<double>(c == 0 ? w0 : (c == 1 ? w1 : w2));
+            // stencil of the bead: nodes at integer coordinates, periodic
+            const double xt = x - Ld * floor(x * iL);
+            const double fl = floor(xt);
+            fr = xt - fl;
+            ii = (int)fl;
+            if (ii >= L) ii -= L;
+            if (ii < 0) ii += L;
+        }
+        __syncthreads();
+        // the same for every thread; flag s + 2 (mod 3) was last read a
+        // substep ago and is next set after the next barrier
+        const bool rebuild = LISTS && (s == 0 || sh.moved[s % 3] != 0);
+        if (LISTS && threadIdx.x == 0) sh.moved[(s + 2) % 3] = 0;
+        if (act) {
+            const double xb[3] = {quad_value<0>(x), quad_value<1>(x), quad_value<2>(x)};
+            // bond of lanes 0 and 1 (FENE, unwrapped separations), then both
+            // bonds' component c in each lane
+            double Ff;
+            {
+                const double d0 = xb[0] - xs[3 * jb], d1 = xb[1] - xs[3 * jb + 1], d2 = xb[2] - xs[3 * jb + 2];
+                const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
+                double den = 1.0 - r2 * bx.inv_r0sq;
+                if (!(den > 0.0)) { hbits |= H_FENE; den = 1e-12; }
+                const double gf = -bx.k_fene / den;
+                const double e0 = x - xs[3 * jb0 + c], e1 = x - xs[3 * jb1 + c];
+                Ff = quad_value<0>(gf) * e0;
+                Ff += quad_value<1>(gf) * e1;
+            }
+            // repulsive LJ over the partners of this lane's class
+            double W[3] = {0, 0, 0};
+            if (LISTS) {
+                if (rebuild) {
+                    x0 = x;
+                    // list radius, a hair above cut-off plus skin so that rounding cannot
+                    // drop a partner that comes within the cut-off
+                    const double rl = sqrt(here(bx.rc2)) + NL_SKIN + 1e-6;
+                    const double rl2 = rl * rl;
+                    // cls = T: bit m is partner lane + T m; cls = 2: (lane mod 2) + 2 m, half of the
+                    // word by each of two lanes; cls = 1: word l is partners 64 l .. 64 l + 63, by lane l
+                    const int j0 = cls == 1 ? 64 * lane : (cls == 2 ? (lane & 1) + 64 * (lane >> 1) : lane);
+                    const int nj = cls == 1 ? 64 : (cls == 2 ? 32 : (N - lane + T - 1) / T);
+                    unsigned long long found = 0ull;
+#pragma unroll 2
+                    for (int m = 0; m < nj; ++m) {
+                        const int j = j0 + cls * m < N ? j0 + cls * m : b;
+                        double d0 = xb[0] - xs[3 * j], d1 = xb[1] - xs[3 * j + 1], d2 = xb[2] - xs[3 * j + 2];
+                        d0 -= Ld * rint(d0 * iL); d1 -= Ld * rint(d1 * iL); d2 -= Ld * rint(d2 * iL);
+                        if (j != b && d0 * d0 + d1 * d1 + d2 * d2 < rl2) found |= 1ull << m;
+                    }
+                    if (cls == T) {
+                        nl[0] = found;
+                    } else if (cls == 2) {
+                        const unsigned long long lo = __shfl(found, lane & 1, T), hi = __shfl(found, (lane & 1) + 2, T);
+                        nl[0] = lo | (hi << 32);
+                    } else {
+#pragma unroll
+                        for (int w = 0; w < NW; ++w) nl[w] = __shfl(found, w, T);
+                    }
+                }
+                const int jl = cls == 1 ? 0 : lane & (cls - 1);
+                auto pairs = [&](unsigned long long m, int j0) __attribute__((always_inline)) {
+                    while (m) {
+                        int j[U];
+                        bool ok[U];
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            ok[u] = m != 0ull;
+                            j[u] = ok[u] ? j0 + cls * (__ffsll((long long)m) - 1) : b;
+                            m &= m - 1ull;
+                        }
+                        wca_add<U>(xb, xs, j, ok, Ld, iL, bx.rc2, bx.sigsq, eps24, W);
+                    }
+                };
+                pairs(nl[0], jl);
+                if (NW > 1 && cls == 1) {
+                    pairs(nl[NW > 1 ? 1 : 0], 64);
+                    pairs(nl[NW > 2 ? 2 : 0], 128);
+                    pairs(nl[NW > 3 ? 3 : 0], 192);
+                }
+            } else {
+                const int j[U] = {lane < N ? lane : b};
+                const bool ok[U] = {j[0] != b};
+                wca_add<U>(xb, xs, j, ok, Ld, iL, bx.rc2, bx.sigsq, eps24, W);
+            }
+            // the class sums: each stage adds the same two values in either
+            // order, so every lane gets the same bits
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                if (T > 4 || cls >= 2) W[d] += dpp_from<0xB1>(W[d]);                  // quad_perm [1,0,3,2]
+                if (T > 4 || cls >= 4) W[d] += dpp_from<0x4E>(W[d]);                  // quad_perm [2,3,0,1]
+                if (T >= 8) W[d] += dpp_from<0x141>(W[d]);                   // row_half_mirror
+                if (T >= 16) W[d] += dpp_from<0x140>(W[d]);                  // row_mirror
+            }
+            const double F = Ff + (c == 0 ? W[0] : (c == 1 ? W[1] : W[2]));
+            // a change in any of the quad's components
+            const int chg = ii != cb ? 1 : 0;
+            if (__builtin_amdgcn_update_dpp(0, chg, 0x00, 0xF, 0xF, false) |
+                __builtin_amdgcn_update_dpp(0, chg, 0x55, 0xF, 0xF, false) |
+                __builtin_amdgcn_update_dpp(0, chg, 0xAA, 0xF, 0xF, false)) {
+                if (s > 0) flush();
+                const int i0[3] = {__builtin_amdgcn_update_dpp(0, ii, 0x00, 0xF, 0xF, false),
+                                   __builtin_amdgcn_update_dpp(0, ii, 0x55, 0xF, 0xF, false),
+                                   __builtin_amdgcn_update_dpp(0, ii, 0xAA, 0xF, 0xF, false)};
+                base = (uint32_t)i0[0] + (uint32_t)L * ((uint32_t)i0[1] + (uint32_t)L * (uint32_t)i0[2]);
+                cb = ii;
+                const int kc = lane & (T8 - 1);
+                const double inv_tau = 1.0 / here(bx.tau_lb);
+                R u[NC][3];
+                uint32_t in = 0;
+                auto at_corner = [&](int k) __attribute__((always_inline)) {
+                    const int ix = i0[0] + (k & 1), iy = i0[1] + ((k >> 1) & 1), iz = i0[2] + (k >> 2);
+                    const uint32_t nx = ix >= L ? ix - L : ix, ny = iy >= L ? iy - L : iy, nz_ = iz >= L ? iz - L : iz;
+                    if (ONE) {
+                        const uint32_t node = nx + (uint32_t)L * (ny + (uint32_t)L * nz_);
+                        in |= (uint32_t)((mask[dseg_of(bx, node)] >> (node % DSEG)) & 1ull) << k;
+                    }
+                    return Upwind(nx, ny, nz_, (uint32_t)L);
+                };
+                // one corner's loads at a time: those of two (T = 4) would
+                // cost the loop its registers
+#pragma unroll
+                for (int kk = 0; kk < NC; ++kk) {
+                    R d[19];
+                    const Upwind up = at_corner(kc + kk * T8);
+                    if (off32) gather_pre32<R>(a, up, d);
+                    else gather_pre<R, false>(a, up, d);
+                    node_velocity<R>(d, bx.rho0, inv_tau, u[kk]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                // corner k sits in slot k / T8 of lane k mod T8
+                aside = 0;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const R u0 = __shfl(u[k / T8][0], k % T8, T), u1 = __shfl(u[k / T8][1], k % T8, T),
+                            u2 = __shfl(u[k / T8][2], k % T8, T);
+                    cu[k] = c == 0 ? u0 : (c == 1 ? u1 : u2);
+                    acc[k] = 0.0;
+                    if (ONE) aside |= __shfl(in, k % T8, T) & (1u << k);
+                }
+            }
+            const double fx = quad_value<0>(fr), fy = quad_value<1>(fr), fz = quad_value<2>(fr);
+            double wt[8], ub = 0.0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                wt[k] = ((k & 1) ? fx : 1.0 - fx) * (((k >> 1) & 1) ? fy : 1.0 - fy) * ((k >> 2) ? fz : 1.0 - fz);
+                ub += wt[k] * (double)cu[k];
+            }
+            const double fric = bx.zeta * (v - ub);
+            fc = fma(bx.bead_noise, nz, -fric);
+            if (ca.tape && own) {   // substep record for the adjoint: x1, v1, fc, base cell, fractions, node velocities
+                double* tp = ca.tape + ((uint64_t)s * ca.total_beads + bx.bead_off + (uint64_t)here(b)) * TAPE_REC;
+                tp[c] = x; tp[3 + c] = v; tp[6 + c] = fc; tp[9 + c] = (double)ii; tp[12 + c] = fr;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) tp[15 + 3 * k + c] = (double)cu[k];
+            }
+            f = F + fc;
+            v += f * hdt_m;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) acc[k] -= wt[k] * fc * dt;
+        }
+    }
+    if (act) {
+        flush();
+        if (own) {
+            const uint64_t g = bx.bead_off + (uint64_t)here(b);
+            if (!ONE && lane == 0) ca.touched_cnt[g] = tcnt < ca.touch_cap ? tcnt : ca.touch_cap;
+            ca.x[3 * g + c] = x; ca.v[3 * g + c] = v; ca.f[3 * g + c] = f; ca.fc[3 * g + c] = fc;
+            if (ca.vhist) ca.vhist[((uint64_t)(t % (uint32_t)ca.hist_len) * ca.total_beads + g) * 3 + c] = v;
+        }
+    }
+    if (ONE) {
+        xe[0] = quad_value<0>(x); xe[1] = quad_value<1>(x); xe[2] = quad_value<2>(x);
+        ve[0] = quad_value<0>(v); ve[1] = quad_value<1>(v); ve[2] = quad_value<2>(v);
+    }
+    return act ? hbits : 0u;
+}
+
+// the coupling stage of one box per workgroup: couple_T lanes per bead
+template <typename R, int MAXT>
 __global__ __launch_bounds__(MAXT) void k_couple(const BoxDev* __restrict__ boxes,
                                                  const int32_t* __restrict__ couple_list,
                                                  const R* __restrict__ A, ChainArgs ca,
                                                  Ctrl* __restrict__ ctrl, uint32_t s_off)
 {
-    __shared__ double xs[3 * BIG_CHAIN];   // chains on this path have at most BIG_CHAIN beads
-    static_assert(BIG_CHAIN <= 256, "partner indices are stored in one byte");
-    __shared__ uint8_t nl[MAXT * CPL_SLOTS + 4];   // per lane: its partners within the list radius
-    __shared__ int moved[2];                        // per substep parity: a bead moved past half the skin
+    __shared__ ChainLds<MAXT / 4> sh;
     __builtin_amdgcn_s_setprio(3);   // latency-bound chain beside the bandwidth-bound collide
-    const int bi = couple_list[blockIdx.x];
-    const BoxDev bx = boxes[bi];   // a copy: its fields stay in registers across the substeps
-    const int N = bx.N;
-    // lanes per bead depend on this chain's length alone, so a box computes
-    // the same bits in any batch
-    const int T = bx.couple_T;
-    const int b = threadIdx.x / T, lane = threadIdx.x % T;
-    const bool act = b < N;
-    const bool writer = act && lane == 0;
-    const uint64_t g = bx.bead_off + (uint64_t)(act ? b : 0);
-    const ChainSpan sp = chain_span(bx, act ? b : 0);
+    const BoxDev bx = boxes[couple_list[blockIdx.x]];   // a copy: its fields stay in registers across the substeps
     const uint32_t t = ctrl->step + s_off;
-    const int L = bx.L;
-    const double Ld = (double)L, iL = bx.inv_L;
-    const double dt = bx.dt, hdt_m = 0.5 * dt / bx.mass;
-    const double inv_tau = 1.0 / bx.tau_lb;
-    const double eps24 = 24.0 * bx.eps;
-    const R* a = A + bx.pop_off;
-    // list radius, a hair above cut-off plus skin so that rounding cannot
-    // drop a partner that comes within the cut-off
-    const double rl = sqrt(bx.rc2) + NL_SKIN + 1e-6;
-    const double rl2 = rl * rl;
-    const uint32_t nl_base = threadIdx.x * CPL_SLOTS;
-    if (threadIdx.x == 0) { moved[0] = 0; moved[1] = 0; }
-
-    double x[3] = {0, 0, 0}, v[3] = {0, 0, 0}, f[3] = {0, 0, 0}, fcl[3] = {0, 0, 0};
-    if (act) {
-#pragma unroll
-        for (int c = 0; c < 3; ++c) { x[c] = ca.x[3 * g + c]; v[c] = ca.v[3 * g + c]; f[c] = ca.f[3 * g + c]; }
-        if (ca.tape_x0 && lane == 0)   // the step's starting beads, for the adjoint
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                ca.tape_x0[3 * g + c] = x[c];
-                ca.tape_x0[ca.tape_vo + 3 * g + c] = v[c];
-                ca.tape_x0[ca.tape_fo + 3 * g + c] = f[c];
-            }
-    }
-    int cb[3] = {-1, -1, -1};     // base cell of the cached stencil
-    // node velocities of the cached stencil (MD units), kept in the storage
-    // precision: FP32 storage carries no more digits than that
-    R cu[8][3];
-    double acc[8][3];             // impulse accumulated on the cached stencil (MD units)
-    uint32_t cnode[8];
-    bool have_acc = false;
-    uint32_t hbits = 0;
-    int tcnt = 0;
-    double x0[3] = {0, 0, 0};     // position at the last list build
-    int nl_n = -1;                // entries of this lane's list (-1: the lane scans all its partners)
-
-    for (int s = 0; s < bx.substeps; ++s) {
-        if (act) {
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                v[c] += f[c] * hdt_m;
-                x[c] += v[c] * dt;
-            }
-            if (lane == 0) {
-                xs[3 * b] = x[0]; xs[3 * b + 1] = x[1]; xs[3 * b + 2] = x[2];
-                const double e0 = x[0] - x0[0], e1 = x[1] - x0[1], e2 = x[2] - x0[2];
-                if (s > 0 && e0 * e0 + e1 * e1 + e2 * e2 > 0.25 * NL_SKIN * NL_SKIN) moved[s & 1] = 1;
-            }
-        }
-        __syncthreads();
-        // the same for every thread: the flag of this parity was cleared a
-        // substep ago, and the other parity's is cleared now, after every
-        // read of it
-        const bool rebuild = s == 0 || moved[s & 1] != 0;
-        if (threadIdx.x == 0) moved[(s + 1) & 1] = 0;
-        if (act) {
-            if (rebuild) {
-                x0[0] = x[0]; x0[1] = x[1]; x0[2] = x[2];
-                int cnt = 0;
-                for (int j = lane; j < N; j += T) {
-                    double d0 = x[0] - xs[3 * j], d1 = x[1] - xs[3 * j + 1], d2 = x[2] - xs[3 * j + 2];
-                    d0 -= Ld * rint(d0 * iL); d1 -= Ld * rint(d1 * iL); d2 -= Ld * rint(d2 * iL);
-                    if (j != b && d0 * d0 + d1 * d1 + d2 * d2 < rl2) {
-                        if (cnt < CPL_SLOTS) nl[nl_base + cnt] = (uint8_t)j;
-                        ++cnt;
-                    }
-                }
-                nl_n = cnt <= CPL_SLOTS ? cnt : -1;
-            }
-            // repulsive LJ over this lane's share of the partners
-            double W[3] = {0, 0, 0};
-            if (nl_n >= 0) {
-                auto jl = [&](int k) { return (int)nl[nl_base + k]; };
-                for (int k = 0; k < nl_n; k += 4) wca_add4(x, xs, jl, k, nl_n, 1, b, Ld, iL, bx.rc2, bx.sigsq, eps24, W);
-            } else {
-                auto jof = [](int k) { return k; };
-                for (int j = lane; j < N; j += 4 * T) wca_add4(x, xs, jof, j, N, T, b, Ld, iL, bx.rc2, bx.sigsq, eps24, W);
-            }
-            for (int o = 1; o < T; o <<= 1) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) W[c] += __shfl_xor(W[c], o, T);
-            }
-            double F[3] = {0, 0, 0};
-            hbits |= fene_force(bx, b, sp, x, xs, F);
-            F[0] += W[0]; F[1] += W[1]; F[2] += W[2];
-            // stencil of the bead: nodes at integer coordinates, periodic
-            int i0[3];
-            double fr[3];
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const double xt = x[c] - Ld * floor(x[c] * iL);
-                const double fl = floor(xt);
-                fr[c] = xt - fl;
-                int ii = (int)fl;
-                if (ii >= L) ii -= L;
-                if (ii < 0) ii += L;
-                i0[c] = ii;
-            }
-            if (i0[0] != cb[0] || i0[1] != cb[1] || i0[2] != cb[2]) {
-                if (have_acc && lane == 0) hbits |= flush_stencil(ca, bx.node_off, g, cnode, acc, bx.tau_lb, tcnt);
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const int ix = i0[0] + (k & 1), iy = i0[1] + ((k >> 1) & 1), iz = i0[2] + ((k >> 2) & 1);
-                    cnode[k] = (uint32_t)(ix >= L ? ix - L : ix) +
-                               (uint32_t)L * ((uint32_t)(iy >= L ? iy - L : iy) + (uint32_t)L * (uint32_t)(iz >= L ? iz - L : iz));
-                    acc[k][0] = acc[k][1] = acc[k][2] = 0.0;
-                }
-                // the bead's lanes share the gathers (T is uniform over the workgroup)
-                if (T >= 8) stencil_shared<R, 1>(a, i0, L, bx.rho0, inv_tau, lane, T, cu);
-                else if (T == 4) stencil_shared<R, 2>(a, i0, L, bx.rho0, inv_tau, lane, T, cu);
-                else if (T == 2) stencil_shared<R, 4>(a, i0, L, bx.rho0, inv_tau, lane, T, cu);
-                else stencil_velocities<R, R, 8>(a, i0, L, bx.rho0, inv_tau, cu);
-                cb[0] = i0[0]; cb[1] = i0[1]; cb[2] = i0[2];
-                have_acc = true;
-            }
-            double wt[8], ub[3] = {0, 0, 0};
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                wt[k] = ((k & 1) ? fr[0] : 1.0 - fr[0]) * (((k >> 1) & 1) ? fr[1] : 1.0 - fr[1]) *
-                        (((k >> 2) & 1) ? fr[2] : 1.0 - fr[2]);
-                ub[0] += wt[k] * (double)cu[k][0]; ub[1] += wt[k] * (double)cu[k][1]; ub[2] += wt[k] * (double)cu[k][2];
-            }
-            const U4 w = philox10(U4{(uint32_t)b, t, (1u << 16) | (uint32_t)s, 0u}, bx.seed, bx.box_id);
-            const uint32_t ws[3] = {w.x, w.y, w.z};
-            double* tp = (ca.tape && lane == 0) ? ca.tape + ((uint64_t)s * ca.total_beads + g) * TAPE_REC : nullptr;
-            if (tp) {   // substep record for the adjoint: x1, v1, fc, base cell, fractions, node velocities
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    tp[c] = x[c]; tp[3 + c] = v[c]; tp[9 + c] = (double)i0[c]; tp[12 + c] = fr[c];
-                }
-#pragma unroll
-                for (int k = 0; k < 8; ++k)
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) tp[15 + 3 * k + c] = (double)cu[k][c];
-            }
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const double ffr = -bx.zeta * (v[c] - ub[c]);
-                const double frn = bx.bead_noise * unit_noise<double>(ws[c]);
-                fcl[c] = ffr + frn;
-                f[c] = F[c] + fcl[c];
-                v[c] += f[c] * hdt_m;
-            }
-            if (tp) { tp[6] = fcl[0]; tp[7] = fcl[1]; tp[8] = fcl[2]; }
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                acc[k][0] -= wt[k] * fcl[0] * dt;
-                acc[k][1] -= wt[k] * fcl[1] * dt;
-                acc[k][2] -= wt[k] * fcl[2] * dt;
-            }
-        }
-        __syncthreads();
-    }
-    if (writer) {
-        if (have_acc) hbits |= flush_stencil(ca, bx.node_off, g, cnode, acc, bx.tau_lb, tcnt);
-        ca.touched_cnt[g] = tcnt < ca.touch_cap ? tcnt : ca.touch_cap;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            ca.x[3 * g + c] = x[c]; ca.v[3 * g + c] = v[c]; ca.f[3 * g + c] = f[c]; ca.fc[3 * g + c] = fcl[c];
-        }
-        if (ca.vhist) {
-            double* hv = ca.vhist + ((uint64_t)(t % (uint32_t)ca.hist_len) * ca.total_beads + g) * 3;
-            hv[0] = v[0]; hv[1] = v[1]; hv[2] = v[2];
-        }
-    }
-    if (act && hbits) atomicOr(&ctrl->health, hbits);
+    uint32_t hbits;
+    double xe[3], ve[3];
+    if (bx.couple_T == 4) hbits = chain_substeps<R, 4, false>(bx, A, ca, t, sh, nullptr, xe, ve);
+    else if (bx.couple_T == 8) hbits = chain_substeps<R, 8, false>(bx, A, ca, t, sh, nullptr, xe, ve);
+    else hbits = chain_substeps<R, 16, false>(bx, A, ca, t, sh, nullptr, xe, ve);
+    if (hbits) atomicOr(&ctrl->health, hbits);
 }
 
 // ------------------------------------------------- couple, large chains
@@ -653,40 +834,12 @@ __device__ __forceinline__ int cell_of(double xc, int L, double Ld, double iL, d
     return ii;
 }
 
-__device__ __forceinline__ uint32_t node_of(int ix, int iy, int iz, int L)
-{
-    ix = ix >= L ? ix - L : (ix < 0 ? ix + L : ix);
-    iy = iy >= L ? iy - L : (iy < 0 ? iy + L : iy);
-    iz = iz >= L ? iz - L : (iz < 0 ? iz + L : iz);
-    return (uint32_t)ix + (uint32_t)L * ((uint32_t)iy + (uint32_t)L * (uint32_t)iz);
-}
-
 // nearest node of a bead position, per axis
 __device__ __forceinline__ int nearest_of(double xc, int L, double Ld, double iL)
 {
     const double xt = xc - Ld * floor(xc * iL);
     int n = (int)floor(xt + 0.5);
     return n >= L ? n - L : n;
-}
-
-// fluid velocity of one node in MD units (u = j / rho / tau_lb) from its
-// gathered pre-collision deviations
-template <typename R>
-__device__ __forceinline__ void node_velocity(const R d[19], double rho0, double inv_tau, R u[3])
-{
-    double rho = 0.0, jx = 0.0, jy = 0.0, jz = 0.0;
-#pragma unroll
-    for (int i = 0; i < 19; ++i) {
-        const double di = (double)d[i];
-        rho += di;
-        if (cxv(i)) jx += cxv(i) * di;
-        if (cyv(i)) jy += cyv(i) * di;
-        if (czv(i)) jz += czv(i) * di;
-    }
-    rho += rho0;
-    u[0] = (R)(jx / rho * inv_tau);
-    u[1] = (R)(jy / rho * inv_tau);
-    u[2] = (R)(jz / rho * inv_tau);
 }
 
 // dense boxes: the velocity of every node, once per LB step, so that their
@@ -1600,6 +1753,248 @@ __global__ __launch_bounds__(256) void k_fixup(const BoxDev* __restrict__ boxes,
         fixup_node<R>(fb, cc, ca.touched[g * ca.touch_cap + k], ca.imp, claim, A, B, ctrl, t, keep_imp);
 }
 
+// ------------------------------------------------ one kernel per step
+// Batched steps whose chains all have at most BIG_CHAIN beads.  The first
+// n_chain workgroups run one box's coupling each, the others collide the
+// tiles.  The nodes a chain will hand impulses to are set aside beforehand:
+// their bits are set in a node mask (one 64-bit word per wavefront of a
+// tile), the tiles' lanes skip them, and the chain's workgroup collides them
+// itself, with their impulses, once its substeps are done.  Both sides read
+// A and write disjoint nodes of B, so nothing waits within the kernel, and a
+// step is max(chain + its nodes, tiles) and one kernel boundary.  Bounds: the
+// chain's serial substeps for small boxes, HBM for large ones.
+//   - Set aside at the end of each step for the next: the stencil of the
+//     bead's end position, one node wider on a side the bead may reach within
+//     a step (set_aside); two masks and lists, by step parity.
+//   - A bead that leaves them all the same hands its impulse to nodes that
+//     the tiles have collided without it: those are listed, and the next
+//     step's chain workgroup re-collides them (Aprev -> A) before anything
+//     reads them; the box's tiles wait for that (a bounded wait; the chain
+//     workgroups come first in the grid and wait for nothing).
+// Every node gets the same collide call with the same impulse as in the
+// fix-up form (k_couple, k_collide, k_fixup), so the bits are the same.
+// Measured against that form, its coupling on a second queue (us per step):
+// 16^3, 16 beads, FP64 20 against 40; 64^3, 64 beads 40 against 48; 128 boxes
+// of 15^3, 32 beads 28 against 41; 256 boxes of 16^3..64^3 543 against 569 (the
+// tiles alone: 545).
+
+// the nodes (range per axis) that a bead at x with velocity v may touch in
+// the next step: its stencil, wider by one node on a side whose distance to
+// the cell's face is under twice the bead's ballistic path plus four thermal
+// ones (or half a cell)
+struct NodeRange { int lo[3], n[3]; };
+__device__ __forceinline__ NodeRange set_aside(const BoxDev& bx, const double x[3], const double v[3])
+{
+    NodeRange r;
+    const double th = 4.0 * sqrt(bx.mu / (3.0 * bx.mass));
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        double fr;
+        const int i = cell_of(x[c], bx.L, (double)bx.L, bx.inv_L, fr);
+        double m = 2.0 * fabs(v[c]) * bx.tau_lb + th;
+        m = m < 0.5 ? m : 0.5;
+        const int below = fr < m ? 1 : 0, above = fr > 1.0 - m ? 1 : 0;
+        r.lo[c] = i - below;
+        r.n[c] = 2 + below + above;
+    }
+    return r;
+}
+
+// set aside a bead's nodes, shared by the `step` threads of which this is the
+// `first`: each node once, its mask bit set and appended to `list`.  Who
+// comes first is decided by a hash table in LDS (linear probing; a returning
+// atomic on the mask takes a microsecond or more, and each thread has two or
+// three nodes), or without one (hash null), and for a node that finds no
+// slot, by the mask bit's old value.
+template <int HASH_BITS>
+__device__ __forceinline__ void set_aside_nodes(const BoxDev& bx, const double x[3], const double v[3], int first,
+                                                int step, unsigned long long* mask, uint32_t* list, uint32_t* n,
+                                                uint32_t* hash)
+{
+    const NodeRange r = set_aside(bx, x, v);
+    const int cnt = r.n[0] * r.n[1] * r.n[2];
+    for (int q = first; q < cnt; q += step) {
+        const int qyz = r.n[0] == 2 ? q >> 1 : q / 3, qx = q - qyz * r.n[0];
+        const int qz = r.n[1] == 2 ? qyz >> 1 : qyz / 3, qy = qyz - qz * r.n[1];
+        const uint32_t node = node_of(r.lo[0] + qx, r.lo[1] + qy, r.lo[2] + qz, bx.L);
+        const unsigned long long bit = 1ull << (node % DSEG);
+        int won = -1;
+        if (HASH_BITS > 0) {
+            uint32_t h = (node * 2654435761u) >> (32 - (HASH_BITS > 0 ? HASH_BITS : 1));
+            for (int k = 0; k < 32 && won < 0; ++k) {
+                const uint32_t old = atomicCAS(hash + h, 0u, node + 1u);
+                if (old == 0u) won = 1;
+                else if (old == node + 1u) won = 0;
+                h = (h + 1u) & ((1u << HASH_BITS) - 1u);
+            }
+            if (won == 1) atomicOr(mask + dseg_of(bx, node), bit);
+        }
+        if (won < 0) won = !(atomicOr(mask + dseg_of(bx, node), bit) & bit);
+        if (won) list[atomicAdd(n, 1u)] = node;
+    }
+}
+
+// one tile, its set-aside lanes left out
+template <typename R>
+__device__ __forceinline__ void step_tile(const BoxDev* __restrict__ boxes, const CollideConst<R>* __restrict__ ccs,
+                                          const uint32_t* __restrict__ tile_box, const StepArgs& sa, uint32_t tile,
+                                          uint32_t lane, const R* A, R* B, Ctrl* __restrict__ ctrl, uint32_t t)
+{
+    const uint32_t p = t & 1u;
+    const uint32_t w = __builtin_amdgcn_readfirstlane(lane / DSEG);   // wavefront-uniform: scalar loads
+    const unsigned long long aside = sa.mask[p][DSEG_PER_TILE * tile + w];
+    const int bi = (int)tile_box[tile];
+    if (ctrl->step_pend[p ^ 1u] == defer_stamp(t - 1u) && sa.rec[bi].pend[p ^ 1u] == defer_stamp(t - 1u)) {
+        uint32_t it = 0;
+        while (__hip_atomic_load(&sa.rec[bi].fixed[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != defer_stamp(t)) {
+            if (++it > SPIN_LIMIT) { atomicOr(&ctrl->health, H_SYNC); break; }
+            __builtin_amdgcn_s_sleep(8);
+        }
+        __atomic_thread_fence(__ATOMIC_ACQUIRE);
+    }
+    if ((aside >> (lane % DSEG)) & 1ull) return;
+    collide_tile<R>(boxes, ccs, tile_box, bi, tile, A, B, ctrl, t, nullptr, lane);
+}
+
+// BT threads per workgroup, at least W waves per SIMD.  A chain's workgroup
+// needs couple_T lanes per bead; further threads clear the old mask and take
+// the first of its nodes while the bead's lanes set the next step's nodes
+// aside.
+template <typename R, int BT, int W>
+__global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(W))) void k_step(
+    const BoxDev* __restrict__ boxes, const CollideConst<R>* __restrict__ ccs, const uint32_t* __restrict__ tile_box,
+    const int32_t* __restrict__ list, uint32_t n_chain, uint32_t n_tiles, R* A, R* B, const R* Aprev, ChainArgs ca,
+    unsigned long long* imp_prev, StepArgs sa, uint32_t* __restrict__ claim, Ctrl* __restrict__ ctrl, uint32_t s_off,
+    int keep_imp)   // Aprev and B may be one buffer: the fix-up reads it, the tiles write it
+{
+    const uint32_t t = ctrl->step + s_off, p = t & 1u;
+    if (blockIdx.x >= n_chain) {
+        const uint32_t sub = BT == 256 ? 0u : __builtin_amdgcn_readfirstlane(threadIdx.x / 256u);
+        const uint32_t lane = BT == 256 ? threadIdx.x : threadIdx.x % 256u;
+        const uint32_t tile = (blockIdx.x - n_chain) * (BT / 256) + sub;
+        if (BT == 256 || tile < n_tiles) step_tile<R>(boxes, ccs, tile_box, sa, tile, lane, A, B, ctrl, t);
+        return;
+    }
+    __shared__ ChainLds<BT == 1024 ? 256 : 64> sh;
+    __builtin_amdgcn_s_setprio(3);   // latency-bound chain beside the bandwidth-bound tiles
+    const int bi = list[blockIdx.x];
+    const BoxDev bx = boxes[bi];   // a copy: its fields stay in registers across the substeps
+    StepRec& rec = sa.rec[bi];
+    const uint32_t n_def = rec.n[p], n_old = rec.n[p ^ 1u];
+    const uint32_t from_top = (uint32_t)BT - 1u - threadIdx.x;   // threads without a bead come first
+    const uint64_t l0 = (uint64_t)NODES_PER_BEAD * bx.bead_off;
+    if (rec.pend[p ^ 1u] == defer_stamp(t - 1u)) {
+        const FixBox fb = fix_box(bx);
+        const uint32_t n_ovf = rec.n_ovf;
+        for (uint32_t e = threadIdx.x; e < n_ovf; e += BT)
+            fixup_node<R>(fb, ccs[bi], ca.touched[bx.bead_off * ca.touch_cap + e], imp_prev, claim, Aprev, A, ctrl,
+                          t - 1u, keep_imp);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            __threadfence();
+            __hip_atomic_store(&rec.fixed[p], defer_stamp(t), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    // the other parity's mask held the previous step's nodes and takes the next step's
+    for (uint32_t i = from_top; i < n_old; i += BT)
+        atomicExch(&sa.mask[p ^ 1u][dseg_of(bx, sa.list[p ^ 1u][l0 + i])], 0ull);
+    if (threadIdx.x == 0) { sh.n_ovf = 0u; sh.n_next = 0u; }
+    uint32_t hbits;
+    double xe[3], ve[3];
+    const int T = bx.couple_T;
+    if (T == 4) hbits = chain_substeps<R, 4, true>(bx, A, ca, t, sh, sa.mask[p], xe, ve);
+    else if (T == 8) hbits = chain_substeps<R, 8, true>(bx, A, ca, t, sh, sa.mask[p], xe, ve);
+    else hbits = chain_substeps<R, 16, true>(bx, A, ca, t, sh, sa.mask[p], xe, ve);
+    constexpr int HASH = 16 * (BT == 1024 ? 256 : 64);
+    __syncthreads();   // every impulse of the box is in the field, the positions in LDS are done with
+    for (int i = (int)threadIdx.x; i < HASH; i += BT) sh.hash[i] = 0u;
+    __syncthreads();
+    if ((int)threadIdx.x / T < bx.N)
+        set_aside_nodes<HASH == 1024 ? 10 : 12>(bx, xe, ve, (int)threadIdx.x % T, T, sa.mask[p ^ 1u],
+                                                sa.list[p ^ 1u] + l0, &sh.n_next, sh.hash);
+    const CollideConst<R> cc = ccs[bi];
+    for (uint32_t i = from_top; i < n_def; i += BT) {
+        const uint32_t r = sa.list[p][l0 + i];
+        R d[19];
+        gather_pre<R, false>(A + bx.pop_off, upwind_of(r, bx.L, bx.inv_L), d);
+        unsigned long long* q = ca.imp + 3 * (bx.node_off + r);
+        unsigned long long qc[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) qc[c] = __hip_atomic_load(q + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!keep_imp && (qc[0] | qc[1] | qc[2])) { q[0] = 0ull; q[1] = 0ull; q[2] = 0ull; }
+        const R fx = (R)((double)(long long)qc[0] * IMP_INV_SCALE), fy = (R)((double)(long long)qc[1] * IMP_INV_SCALE),
+                fz = (R)((double)(long long)qc[2] * IMP_INV_SCALE);
+        R o[19];
+        hbits |= collide<R>(d, o, fx, fy, fz, cc, r, t, bx.seed, bx.box_id);
+        R* b = B + bx.pop_off;
+#pragma unroll
+        for (int k = 0; k < 19; ++k) b[pop_at(k, r)] = o[k];
+    }
+    __syncthreads();   // the next step's nodes are counted
+    if (threadIdx.x == 0) {
+        rec.n[p ^ 1u] = sh.n_next;
+        rec.n_ovf = sh.n_ovf;
+        rec.pend[p] = sh.n_ovf ? defer_stamp(t) : 0u;
+        if (sh.n_ovf) ctrl->step_pend[p] = defer_stamp(t);   // every writer stores the same
+        rec.t = t;
+    }
+    if (hbits) atomicOr(&ctrl->health, hbits);
+}
+
+// start of a run of one-kernel steps: every chain's nodes for step s_off
+// (both masks are clear between runs)
+__global__ __launch_bounds__(256) void k_step_begin(const BoxDev* __restrict__ boxes, const int32_t* __restrict__ list,
+                                                    ChainArgs ca, StepArgs sa, const Ctrl* __restrict__ ctrl,
+                                                    uint32_t s_off)
+{
+    __shared__ uint32_t n;
+    const int bi = list[blockIdx.x];
+    const BoxDev& bx = boxes[bi];
+    const uint32_t p = (ctrl->step + s_off) & 1u;
+    if (threadIdx.x == 0) n = 0u;
+    __syncthreads();
+    for (int e = (int)threadIdx.x; e < 4 * bx.N; e += 256) {
+        const uint64_t g = bx.bead_off + (uint64_t)(e / 4);
+        const double x[3] = {ca.x[3 * g], ca.x[3 * g + 1], ca.x[3 * g + 2]};
+        const double v[3] = {ca.v[3 * g], ca.v[3 * g + 1], ca.v[3 * g + 2]};
+        set_aside_nodes<0>(bx, x, v, e % 4, 4, sa.mask[p], sa.list[p] + NODES_PER_BEAD * bx.bead_off, &n, nullptr);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        StepRec& rec = sa.rec[bi];
+        rec.n[p] = n;
+        rec.n[p ^ 1u] = 0u;
+        rec.pend[0] = rec.pend[1] = 0u;
+        rec.fixed[0] = rec.fixed[1] = 0u;
+        rec.n_ovf = 0u;
+    }
+}
+
+// end of a run of one-kernel steps: the last step's impulses outside its
+// set-aside nodes, both node masks cleared, and the step counter advanced (no workgroup reads it here: the
+// step number comes from the box's record)
+template <typename R>
+__global__ __launch_bounds__(256) void k_step_end(const BoxDev* __restrict__ boxes,
+                                                  const CollideConst<R>* __restrict__ ccs,
+                                                  const int32_t* __restrict__ list, ChainArgs ca, StepArgs sa,
+                                                  uint32_t* __restrict__ claim, const R* __restrict__ A,
+                                                  R* __restrict__ B, Ctrl* __restrict__ ctrl, uint32_t advance,
+                                                  int keep_imp)
+{
+    const int bi = list[blockIdx.x];
+    const BoxDev& bx = boxes[bi];
+    const StepRec& rec = sa.rec[bi];
+    const uint32_t t = rec.t, p = t & 1u;
+    if (rec.pend[p] == defer_stamp(t))
+        for (uint32_t e = threadIdx.x; e < rec.n_ovf; e += 256)
+            fixup_node<R>(fix_box(bx), ccs[bi], ca.touched[bx.bead_off * ca.touch_cap + e], ca.imp, claim, A, B, ctrl,
+                          t, keep_imp);
+    for (int q = 0; q < 2; ++q)
+        for (uint32_t i = threadIdx.x; i < rec.n[q]; i += 256)
+            sa.mask[q][dseg_of(bx, sa.list[q][NODES_PER_BEAD * bx.bead_off + i])] = 0ull;
+    if (blockIdx.x == 0 && threadIdx.x == 0) ctrl->step += advance;
+}
+
 // End of a step that deferred tiles (one workgroup): fix the listed nodes
 // outside the deferred tiles, then reset both list counts for the next step
 // (the per-tile stamps need no clearing).  Runs after the plain collide, the
@@ -1750,16 +2145,6 @@ __global__ void k_advance(Ctrl* ctrl, uint32_t n)
 // order), so a state gives the same bits on every call and in any batch.
 constexpr int NSTAT = NSTAT_REC;
 
-// value of v in another lane of the same 16-lane row, by a DPP lane move of
-// both 32-bit halves (CTRL: a gfx9 DPP control; every source lane is active)
-template <int CTRL>
-__device__ __forceinline__ double dpp_from(double v)
-{
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
-    return __hiloint2double(hi, lo);
-}
-
 __device__ __forceinline__ double lane_value(double v, int lane)
 {
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
@@ -1818,21 +2203,6 @@ __device__ __forceinline__ double uniform_value(double v)
 {
     return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
                             __builtin_amdgcn_readfirstlane(__double2loint(v)));
-}
-
-// the pre-collision populations of node `up` with 32-bit offsets from the
-// box's array (valid while that array is under 4 GiB): a uniform base and one
-// 32-bit offset per load instead of 64-bit address arithmetic
-template <typename R>
-__device__ __forceinline__ void gather_pre32(const R* __restrict__ a, const Upwind& up, R d[19])
-{
-    const char* base = (const char*)a;
-#pragma unroll
-    for (int i = 0; i < 19; ++i) {
-        const uint32_t s = up.src(i);
-        const uint32_t e = ((s >> PTILE_LOG) * 19u + (uint32_t)i) * PTILE + (s & (PTILE - 1u));
-        d[i] = *(const R*)(base + (uint64_t)(e * (uint32_t)sizeof(R)));
-    }
 }
 
 template <typename R, bool O32>
@@ -2077,9 +2447,61 @@ hipError_t launch_couple(const LaunchCtx& c, const void* A, const int32_t* list,
                          uint32_t s_off)
 {
     if (n_list == 0) return hipSuccess;
-    if (block > 256) return hipErrorInvalidValue;   // larger chains take the one-workgroup-per-chain kernel
-    hipLaunchKernelGGL((k_couple<R, 256>), dim3(n_list), dim3(block), 0, c.stream, c.boxes, list, (const R*)A,
-                       chain_args(c), c.ctrl, s_off);
+    if (block > 1024) return hipErrorInvalidValue;   // larger chains take the one-workgroup-per-chain kernel
+    if (block > 256)
+        hipLaunchKernelGGL((k_couple<R, 1024>), dim3(n_list), dim3(block), 0, c.stream, c.boxes, list, (const R*)A,
+                           chain_args(c), c.ctrl, s_off);
+    else
+        hipLaunchKernelGGL((k_couple<R, 256>), dim3(n_list), dim3(block), 0, c.stream, c.boxes, list, (const R*)A,
+                           chain_args(c), c.ctrl, s_off);
+    return hipGetLastError();
+}
+
+static StepArgs step_args(const LaunchCtx& c) { return StepArgs{{c.nmask[0], c.nmask[1]}, {c.nlist[0], c.nlist[1]}, c.step_rec}; }
+
+constexpr int STEP_FEW_TILES_PER_CU = 16;
+
+template <typename R, int BT, int W>
+static void launch_step_v(const LaunchCtx& c, const int32_t* list, int n_list, void* A, void* B, const void* Aprev,
+                          unsigned long long* imp_prev, uint32_t n_tiles, uint32_t s_off)
+{
+    constexpr uint32_t M = BT / 256;
+    hipLaunchKernelGGL((k_step<R, BT, W>), dim3((uint32_t)n_list + (n_tiles + M - 1) / M), dim3(BT), 0, c.stream,
+                       c.boxes, (const CollideConst<R>*)c.ccs, c.tile_box, list, (uint32_t)n_list, n_tiles, (R*)A,
+                       (R*)B, (const R*)Aprev, chain_args(c), imp_prev, step_args(c), c.claim, c.ctrl, s_off,
+                       c.keep_imp);
+}
+
+template <typename R>
+hipError_t launch_step(const LaunchCtx& c, const int32_t* list, int n_list, int block, void* A, void* B,
+                       const void* Aprev, unsigned long long* imp_prev, uint32_t n_tiles, uint32_t s_off)
+{
+    if (n_list <= 0 || n_tiles == 0 || block > 1024 || !c.step_rec) return hipErrorInvalidValue;
+    // few tiles: the chain sets the time, and threads beyond the beads' lanes
+    // shorten its end; many: the tiles do, in 256-thread workgroups where the
+    // chains fit them
+    const bool few = n_tiles <= (uint32_t)(STEP_FEW_TILES_PER_CU * c.n_cu);
+    if (block > 256) launch_step_v<R, 1024, 4>(c, list, n_list, A, B, Aprev, imp_prev, n_tiles, s_off);
+    else if (few) launch_step_v<R, 512, 4>(c, list, n_list, A, B, Aprev, imp_prev, n_tiles, s_off);
+    else launch_step_v<R, 256, 4>(c, list, n_list, A, B, Aprev, imp_prev, n_tiles, s_off);
+    return hipGetLastError();
+}
+
+hipError_t launch_step_begin(const LaunchCtx& c, const int32_t* list, int n_list, uint32_t s_off)
+{
+    if (n_list <= 0 || !c.step_rec) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_step_begin, dim3(n_list), dim3(256), 0, c.stream, c.boxes, list, chain_args(c), step_args(c),
+                       c.ctrl, s_off);
+    return hipGetLastError();
+}
+
+template <typename R>
+hipError_t launch_step_end(const LaunchCtx& c, const int32_t* list, int n_list, const void* A, void* B,
+                           uint32_t advance)
+{
+    if (n_list <= 0 || !c.step_rec) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_step_end<R>, dim3(n_list), dim3(256), 0, c.stream, c.boxes, (const CollideConst<R>*)c.ccs,
+                       list, chain_args(c), step_args(c), c.claim, (const R*)A, (R*)B, c.ctrl, advance, c.keep_imp);
     return hipGetLastError();
 }
 
@@ -2436,7 +2858,7 @@ __global__ __launch_bounds__(256) void k_adj_couple(const BoxDev* __restrict__ b
     const int bi = couple_list[blockIdx.x];
     const BoxDev bx = boxes[bi];   // a copy: its fields stay in registers across the substeps
     const int N = bx.N, S = bx.substeps, L = bx.L;
-    const int T = bx.couple_T;
+    const int T = bx.adj_T;
     const int b = (int)threadIdx.x / T, lane = (int)threadIdx.x % T;
     const bool act = b < N;
     const bool writer = act && lane == 0;
@@ -2712,6 +3134,12 @@ template hipError_t launch_collide_forced<double>(const LaunchCtx&, const void*,
                                                   uint32_t);
 template hipError_t launch_couple<float>(const LaunchCtx&, const void*, const int32_t*, int, int, uint32_t);
 template hipError_t launch_couple<double>(const LaunchCtx&, const void*, const int32_t*, int, int, uint32_t);
+template hipError_t launch_step<float>(const LaunchCtx&, const int32_t*, int, int, void*, void*, const void*,
+                                       unsigned long long*, uint32_t, uint32_t);
+template hipError_t launch_step<double>(const LaunchCtx&, const int32_t*, int, int, void*, void*, const void*,
+                                        unsigned long long*, uint32_t, uint32_t);
+template hipError_t launch_step_end<float>(const LaunchCtx&, const int32_t*, int, const void*, void*, uint32_t);
+template hipError_t launch_step_end<double>(const LaunchCtx&, const int32_t*, int, const void*, void*, uint32_t);
 template hipError_t launch_couple_big<float>(const LaunchCtx&, const void*, const int32_t*, int, int, uint32_t,
                                             hipEvent_t, const void*, int, uint32_t, int, int);
 template hipError_t launch_couple_big<double>(const LaunchCtx&, const void*, const int32_t*, int, int, uint32_t,

@@ -9,6 +9,22 @@
 
 namespace lbd {
 
+// One-kernel steps (k_step): per box, the nodes set aside for its chain's
+// workgroup (count by step parity), and the impulses outside them.
+struct alignas(128) StepRec {
+    uint32_t n[2];       // set-aside nodes of the steps of either parity
+    uint32_t pend[2];    // by parity: the step's deferral stamp if it listed impulses outside them
+    uint32_t fixed[2];   // by parity: stamp of the step whose start re-collided the previous step's
+    uint32_t n_ovf;      // impulses the last step listed
+    uint32_t t;          // the last step
+};
+struct StepArgs {
+    unsigned long long* mask[2];   // by step parity: one bit per node, a word per DSEG nodes
+    uint32_t* list[2];             // by step parity: the set-aside nodes, NODES_PER_BEAD slots per bead
+    StepRec* rec;
+};
+constexpr int NODES_PER_BEAD = 27;   // a bead's stencil, at most one node wider on one side per axis
+
 // Device pointers and sizes every launcher needs; filled by the runtime.
 struct LaunchCtx {
     hipStream_t stream;
@@ -57,6 +73,9 @@ struct LaunchCtx {
     uint32_t* ovf;                 // (bead, local node) pairs, Ctrl::ovf_cnt of them
     uint32_t ovf_cap;
     uint32_t* ovm;                 // per global node: stamp of the last step that listed it in ovf
+    unsigned long long* nmask[2];  // one-kernel steps (StepArgs)
+    uint32_t* nlist[2];
+    StepRec* step_rec;             // null: no such steps
 };
 
 template <typename R>
@@ -79,6 +98,18 @@ hipError_t launch_collide_forced(const LaunchCtx& c, const void* A, void* B, int
 template <typename R>
 hipError_t launch_couple(const LaunchCtx& c, const void* A, const int32_t* list, int n_list, int block,
                          uint32_t s_off);
+// one whole step of boxes whose chains (those in `list`) have at most
+// BIG_CHAIN beads, from A into B; Aprev, imp_prev: the previous step's input
+// and impulse field (unused by the first step after launch_step_begin).
+// block: threads of the widest chain workgroup.  A run of steps starts with
+// launch_step_begin and ends with launch_step_end on the last step's buffers.
+template <typename R>
+hipError_t launch_step(const LaunchCtx& c, const int32_t* list, int n_list, int block, void* A, void* B,
+                       const void* Aprev, unsigned long long* imp_prev, uint32_t n_tiles, uint32_t s_off);
+hipError_t launch_step_begin(const LaunchCtx& c, const int32_t* list, int n_list, uint32_t s_off);
+template <typename R>
+hipError_t launch_step_end(const LaunchCtx& c, const int32_t* list, int n_list, const void* A, void* B,
+                           uint32_t advance);
 // chains of BIG_CHAIN+1..1024 beads (at most max_n): one 1024-thread workgroup
 // per box in `list`, with its node-table and impulse-spreading launches.
 // after_table (may be null) is recorded on c.stream between the node-table

@@ -79,15 +79,16 @@ struct Layout {
            sc_touched = 0, sc_tcnt = 0, sc_beadbox = 0, sc_nlcnt = 0, sc_nlidx = 0, sc_nlx0 = 0,
            sc_part = 0, sc_mid = 0, sc_stat = 0, sc_chain = 0, sc_vhist = 0, sc_nlreb = 0, sc_biglist = 0, sc_alllist = 0,
            sc_nearu = 0, sc_nearc = 0, sc_subrec = 0, sc_field = 0, sc_binstart = 0, sc_items = 0, sc_slotof = 0,
-           sc_defer = 0, sc_dclaim = 0, sc_dlist = 0, sc_ovf = 0, sc_ovm = 0, scratch_bytes = 0;
+           sc_defer = 0, sc_dclaim = 0, sc_dlist = 0, sc_ovf = 0, sc_ovm = 0, sc_nmask[2] = {0, 0}, sc_nlist[2] = {0, 0},
+           sc_steprec = 0, scratch_bytes = 0;
     uint64_t beads_big_sparse = 0;                    // beads of the chains above BIG_CHAIN in the other boxes
     uint32_t defer_cap = 0, ovf_cap = 0;              // deferred-tile list and overflow list entries
     int max_N = 0;         // largest chain taking the one-workgroup path
     std::vector<int32_t> big_list;                    // boxes whose chain takes the 1024-thread kernel
     int big_max_n = 0, big_max_sub = 0;              // largest chain and most substeps among them
     std::vector<int32_t> small_list;                  // boxes on the one-workgroup path
-    std::vector<int> couple_T;   // per box: lanes per bead on the one-workgroup path
-    int couple_block = 64;
+    std::vector<int> couple_T, adj_T;   // per box: lanes per bead on the one-workgroup path and its reverse
+    int couple_block = 64, adj_block = 64;
     int touch_cap = 8;
 };
 
@@ -182,19 +183,24 @@ Layout make_layout(const lb_box_desc* b, int32_t n, int32_t prec, int32_t hist)
     Lo.total_tiles = tiles;
     Lo.total_beads = beads;
     Lo.total_nodes = nodes;
-    // lanes per bead in the coupling workgroup: split the pair loop while the
-    // chain is small (a function of the box's own N, so that a box computes
-    // the same bits alone and in any batch), one lane per bead otherwise
-    int widest = 0;
+    // lanes per bead of the one-workgroup coupling kernels (functions of the
+    // box's own N, so that a box computes the same bits alone and in any
+    // batch): forward 16 to 16 beads, 8 to 32, 4 above (256 threads to 64
+    // beads, 1024 at 256); reverse as many as 256 threads hold
+    int widest = 0, adj_widest = 0;
     for (int i = 0; i < n; ++i) {
         const int N = b[i].n_beads;
-        int T = 1;
-        if (N > 0 && N <= BIG_CHAIN)
-            while (T < 16 && 2 * T * N <= 256) T *= 2;
+        const bool on = N > 0 && N <= BIG_CHAIN;
+        const int T = N <= 16 ? 16 : (N <= 32 ? 8 : 4);
+        int Ta = 1;
+        if (on)
+            while (Ta < 16 && 2 * Ta * N <= 256) Ta *= 2;
         Lo.couple_T.push_back(T);
-        if (N > 0 && N <= BIG_CHAIN) widest = std::max(widest, T * N);
+        Lo.adj_T.push_back(Ta);
+        if (on) { widest = std::max(widest, T * N); adj_widest = std::max(adj_widest, Ta * N); }
     }
     if (widest > 0) Lo.couple_block = (int)round_up((uint64_t)widest, 64);
+    if (adj_widest > 0) Lo.adj_block = (int)round_up((uint64_t)adj_widest, 64);
     size_t o = 0;
     Lo.st_popA = o; o = align256(o + pop * Lo.esz);
     Lo.st_popB = o; o = align256(o + pop * Lo.esz);
@@ -250,6 +256,13 @@ Layout make_layout(const lb_box_desc* b, int32_t n, int32_t prec, int32_t hist)
         Lo.sc_ovf = o; o = align256(o + std::max<uint32_t>(Lo.ovf_cap, 1) * 2 * sizeof(uint32_t));
         Lo.sc_ovm = o; o = align256(o + (Lo.beads_big_sparse ? nodes : 1) * sizeof(uint32_t));
     }
+    if (Lo.big_list.empty() && beads) {   // one-kernel steps: node masks and lists by step parity
+        for (int q = 0; q < 2; ++q) {
+            Lo.sc_nmask[q] = o; o = align256(o + DSEG_PER_TILE * tiles * sizeof(unsigned long long));
+            Lo.sc_nlist[q] = o; o = align256(o + NODES_PER_BEAD * beads * sizeof(uint32_t));
+        }
+        Lo.sc_steprec = o; o = align256(o + n * sizeof(StepRec));
+    }
     Lo.scratch_bytes = o;
     return Lo;
 }
@@ -290,7 +303,6 @@ struct lb_handle {
     // collide kernel of the same step (both only read the current state)
     hipStream_t stream2 = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_table = nullptr, ev_head = nullptr, ev_def = nullptr;
-    hipEvent_t ev_coll = nullptr;     // chain-bound runs: this step's collide is done
     LaunchCtx ctx{};
     LaunchCtx ctx2{};
     int32_t* couple_list = nullptr;   // device: boxes on the one-workgroup path (chains <= 256 beads)
@@ -365,34 +377,42 @@ lb_status enqueue_step(lb_handle* h, int from, uint32_t s_off, bool couple)
     const int nc = (int)h->couple_host.size();
     const bool any_beads = h->lo.total_beads > 0;
     if (h->batched) {
-        const bool fork = couple && any_beads;
+        // nothing to run beside the coupling when every box is dense: its
+        // kernels then stay on the handle's stream
+        const bool work = couple && any_beads, fork = work && h->lo.tiles_sparse > 0;
         const int nbig = (int)h->lo.big_list.size();
         // chains above BIG_CHAIN beads in sparse boxes: the tiles around
         // them are collided beside the plain collide once their impulses are
         // in, instead of re-collided after it (same bits either way)
-        const bool defer = fork && h->overlap && h->lo.beads_big_sparse > 0 && !c.keep_imp && !c.tape;
+        const bool defer = work && h->overlap && h->lo.beads_big_sparse > 0 && !c.keep_imp && !c.tape;
         LaunchCtx c1 = c;
         c1.defer_on = defer ? 1 : 0;
         if (fork) {
             HIPCHK(h, hipEventRecord(h->ev_fork, h->stream));
             HIPCHK(h, hipStreamWaitEvent(h->stream2, h->ev_fork, 0));
-            LaunchCtx c2 = h->ctx2;
+        }
+        if (work) {
+            LaunchCtx c2 = fork ? h->ctx2 : h->ctx;
             c2.defer_on = c1.defer_on;
             // a chain above 256 beads needs a whole CU (1024 threads, the full
             // register file): the collide waits for its short node-table
             // kernel, so the chain kernel queued right behind it is dispatched
             // onto an idle GPU instead of behind the collide's workgroups
             if (nbig)
-                HIPCHK(h, f64 ? launch_couple_big<double>(c2, A, h->big_list, nbig, h->lo.big_max_n, s_off, h->ev_table)
-                              : launch_couple_big<float>(c2, A, h->big_list, nbig, h->lo.big_max_n, s_off, h->ev_table));
+                HIPCHK(h, f64 ? launch_couple_big<double>(c2, A, h->big_list, nbig, h->lo.big_max_n, s_off,
+                                                          fork ? h->ev_table : nullptr)
+                              : launch_couple_big<float>(c2, A, h->big_list, nbig, h->lo.big_max_n, s_off,
+                                                         fork ? h->ev_table : nullptr));
             if (nc)
                 HIPCHK(h, f64 ? launch_couple<double>(c2, A, h->couple_list, nc, h->lo.couple_block, s_off)
                               : launch_couple<float>(c2, A, h->couple_list, nc, h->lo.couple_block, s_off));
             if (defer)
                 HIPCHK(h, f64 ? launch_collide_deferred<double>(c2, A, B, s_off)
                               : launch_collide_deferred<float>(c2, A, B, s_off));
-            HIPCHK(h, hipEventRecord(h->ev_join, h->stream2));
-            if (nbig) HIPCHK(h, hipStreamWaitEvent(h->stream, h->ev_table, 0));
+            if (fork) {
+                HIPCHK(h, hipEventRecord(h->ev_join, h->stream2));
+                if (nbig) HIPCHK(h, hipStreamWaitEvent(h->stream, h->ev_table, 0));
+            }
         }
         const uint32_t ts = (uint32_t)h->lo.tiles_sparse, td = (uint32_t)(h->lo.total_tiles - h->lo.tiles_sparse);
         HIPCHK(h, f64 ? launch_collide<double>(c1, A, B, -1, 0, ts, s_off)
@@ -517,6 +537,61 @@ lb_status enqueue_headed_run(lb_handle* h, int from, uint32_t n)
     return LB_OK;
 }
 
+// Batched coupled steps whose chains all have at most BIG_CHAIN beads run as
+// one kernel each (k_step).  Chains above 64 beads make its workgroups 512 or
+// 1024 threads wide, which costs the collide of a large box (16-19 % of it at
+// 256^3) more than the fix-up and the boundaries it saves (~20 us): such
+// batches take it up to ONE_KERNEL_NODES nodes.
+constexpr uint64_t ONE_KERNEL_NODES = 4ull << 20;
+bool one_kernel_steps(const lb_handle* h)
+{
+    const Layout& lo = h->lo;
+    return h->batched && h->overlap && !h->couple_host.empty() && lo.big_list.empty() &&
+           (lo.couple_block <= 256 || lo.total_nodes <= ONE_KERNEL_NODES);
+}
+
+// one such step with launch context c (k = 0 follows launch_step_begin and
+// has no previous step)
+lb_status enqueue_one(lb_handle* h, const LaunchCtx& c, void* A, void* B, const void* Aprev,
+                      unsigned long long* imp_prev, uint32_t s_off)
+{
+    const int nc = (int)h->couple_host.size();
+    const uint32_t nt = (uint32_t)h->lo.total_tiles;
+    HIPCHK(h, h->prec == LB_FP64
+                  ? launch_step<double>(c, h->couple_list, nc, h->lo.couple_block, A, B, Aprev, imp_prev, nt, s_off)
+                  : launch_step<float>(c, h->couple_list, nc, h->lo.couple_block, A, B, Aprev, imp_prev, nt, s_off));
+    return LB_OK;
+}
+
+lb_status enqueue_one_end(lb_handle* h, const LaunchCtx& c, const void* A, void* B, uint32_t advance)
+{
+    const int nc = (int)h->couple_host.size();
+    HIPCHK(h, h->prec == LB_FP64 ? launch_step_end<double>(c, h->couple_list, nc, A, B, advance)
+                                 : launch_step_end<float>(c, h->couple_list, nc, A, B, advance));
+    return LB_OK;
+}
+
+// a run of n one-kernel steps from buffer `from`, all on the handle's stream,
+// the step counter advanced by n
+lb_status enqueue_one_run(lb_handle* h, int from, uint32_t n)
+{
+    HIPCHK(h, launch_step_begin(h->ctx, h->couple_list, (int)h->couple_host.size(), 0));
+    for (uint32_t k = 0; k < n; ++k) {
+        const int p = from ^ (int)(k & 1);
+        const lb_status s = enqueue_one(h, h->ctx, h->pop(p), h->pop(1 - p), h->pop(1 - p), h->ctx.imp, k);
+        if (s != LB_OK) return s;
+    }
+    const int pl = from ^ (int)((n - 1) & 1);
+    return enqueue_one_end(h, h->ctx, h->pop(pl), h->pop(1 - pl), n);
+}
+
+// Layouts that put a step's kernels on both streams are launched directly,
+// never from a graph: only steps that keep to one stream are recorded.
+bool linear_steps(const lb_handle* h)
+{
+    return !h->batched || one_kernel_steps(h) || h->lo.total_beads == 0 || h->lo.tiles_sparse == 0;
+}
+
 // FP32 runs whose chains are all large (every box with beads holds a chain
 // above BIG_CHAIN beads, none of them dense) take the collide that carries
 // its own node tables from the second step on.  (In FP64 the node-table code
@@ -529,59 +604,6 @@ lb_status enqueue_headed_run(lb_handle* h, int from, uint32_t n)
 // tools that run one kernel at a time, such as hardware counter collection:
 // there the waiting chain kernel can hold the GPU while the collide it waits
 // for has not started.
-// Batched coupled steps whose boxes hold chains of at most BIG_CHAIN beads
-// and no dense box, with so few nodes that the collide (~30 us per million
-// nodes in FP32) is shorter than the coupling kernel (a few us per MD
-// substep): the chain's queue sets the step time.
-constexpr uint64_t CHAIN_BOUND_NODES = 1ull << 20;
-bool chain_bound_steps(const lb_handle* h)
-{
-    const Layout& lo = h->lo;
-    return h->batched && h->overlap && !h->couple_host.empty() && lo.big_list.empty() && lo.field_nodes == 0 &&
-           !h->ctx.keep_imp && !h->ctx.tape && lo.total_nodes <= CHAIN_BOUND_NODES;
-}
-
-// A run of n chain-bound steps from buffer `from` (step offsets 0..n-1),
-// launched directly.  The second stream holds the chain work of one step
-// after another: step k's coupling, then, once step k's collide is done, its
-// fix-up.  The handle's stream holds the collides; step k's collide waits
-// for step k-1's fix-up.  So the coupling kernels follow each other's
-// fix-ups on one queue, and the collide beside each of them waits off that
-// path (in the per-step form a coupling kernel waits for the previous
-// fix-up on the other queue, and the fix-up for the coupling kernel).  A
-// replayed graph maps its kernels onto queues of its own choosing, where
-// the per-step form was measured faster, so a stream under capture takes
-// that form.  Every node gets the same collide call with the same impulse
-// as in enqueue_step, so the bits are the same.
-lb_status enqueue_chain_run(lb_handle* h, int from, uint32_t n)
-{
-    const bool f64 = h->prec == LB_FP64;
-    const LaunchCtx& c1 = h->ctx;
-    const LaunchCtx& c2 = h->ctx2;
-    const int nc = (int)h->couple_host.size();
-    const uint32_t ts = (uint32_t)h->lo.tiles_sparse;
-    HIPCHK(h, hipEventRecord(h->ev_fork, h->stream));
-    HIPCHK(h, hipStreamWaitEvent(h->stream2, h->ev_fork, 0));
-    for (uint32_t k = 0; k < n; ++k) {
-        const int p = from ^ (int)(k & 1);
-        const void* A = h->pop(p);
-        void* B = h->pop(1 - p);
-        // step k-1's fix-up wrote into A and read B
-        if (k > 0) HIPCHK(h, hipStreamWaitEvent(h->stream, h->ev_join, 0));
-        HIPCHK(h, f64 ? launch_collide<double>(c1, A, B, -1, 0, ts, k) : launch_collide<float>(c1, A, B, -1, 0, ts, k));
-        HIPCHK(h, hipEventRecord(h->ev_coll, h->stream));
-        HIPCHK(h, f64 ? launch_couple<double>(c2, A, h->couple_list, nc, h->lo.couple_block, k)
-                      : launch_couple<float>(c2, A, h->couple_list, nc, h->lo.couple_block, k));
-        HIPCHK(h, hipStreamWaitEvent(h->stream2, h->ev_coll, 0));
-        if (h->lo.beads_sparse)
-            HIPCHK(h, f64 ? launch_fixup<double>(c2, A, B, 0, h->lo.total_beads, k)
-                          : launch_fixup<float>(c2, A, B, 0, h->lo.total_beads, k));
-        HIPCHK(h, hipEventRecord(h->ev_join, h->stream2));
-    }
-    HIPCHK(h, hipStreamWaitEvent(h->stream, h->ev_join, 0));
-    return LB_OK;
-}
-
 bool fused_steps(const lb_handle* h)
 {
     // the collide's node-table workgroups wait for each other, so they must
@@ -662,12 +684,10 @@ lb_status enqueue_fused_run(lb_handle* h, int from, uint32_t n, uint32_t advance
 lb_status enqueue_steps(lb_handle* h, int from, uint32_t n)
 {
     if (n == 0) return LB_OK;
+    if (one_kernel_steps(h)) return enqueue_one_run(h, from, n);
     if (fused_steps(h) && !capturing(h->stream)) return enqueue_fused_run(h, from, n, n);
     if (headed_steps(h)) {
         const lb_status s = enqueue_headed_run(h, from, n);
-        if (s != LB_OK) return s;
-    } else if (chain_bound_steps(h) && !capturing(h->stream)) {
-        const lb_status s = enqueue_chain_run(h, from, n);
         if (s != LB_OK) return s;
     } else {
         for (uint32_t k = 0; k < n; ++k) {
@@ -709,7 +729,7 @@ lb_status build_graph(lb_handle* h, int parity)
 lb_status prepare_graphs(lb_handle* h)
 {
     drop_graphs(h);
-    if (h->graph_steps <= 0 || fused_steps(h)) return LB_OK;
+    if (h->graph_steps <= 0 || !linear_steps(h)) return LB_OK;
     for (int p = 0; p < 2; ++p) {
         lb_status s = build_graph(h, p);
         if (s != LB_OK) return s;
@@ -786,6 +806,7 @@ lb_status lb_init(const lb_box_desc* boxes, int32_t n_boxes, int32_t precision, 
         b.tile_begin = lo.tile_begin[i]; b.n_tiles = lo.n_tiles[i];
         b.therm = d.thermalize; b.substeps = d.md_substeps;
         b.couple_T = lo.couple_T[i];
+        b.adj_T = lo.adj_T[i];
         b.chain_len = d.chain_len > 0 ? d.chain_len : std::max(d.n_beads, 1);
         b.dense = lo.dense[i];
         b.stat_off = lo.stat_off[i];
@@ -891,6 +912,14 @@ lb_status lb_init(const lb_box_desc* boxes, int32_t n_boxes, int32_t precision, 
     c.ovf = (uint32_t*)sc(lo.sc_ovf);
     c.ovf_cap = lo.ovf_cap;
     c.ovm = (uint32_t*)sc(lo.sc_ovm);
+    c.step_rec = nullptr;
+    if (lo.sc_steprec) {
+        for (int q = 0; q < 2; ++q) {
+            c.nmask[q] = (unsigned long long*)sc(lo.sc_nmask[q]);
+            c.nlist[q] = (uint32_t*)sc(lo.sc_nlist[q]);
+        }
+        c.step_rec = (StepRec*)sc(lo.sc_steprec);
+    }
     c.vhist = hist_steps > 0 ? (double*)sc(lo.sc_vhist) : nullptr;
     c.hist_len = hist_steps > 0 ? hist_steps : 1;
     c.total_beads = nb;
@@ -902,7 +931,6 @@ lb_status lb_init(const lb_box_desc* boxes, int32_t n_boxes, int32_t precision, 
     if (e == hipSuccess) e = hipEventCreateWithFlags(&h->ev_table, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&h->ev_head, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&h->ev_def, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&h->ev_coll, hipEventDisableTiming);
     if (e != hipSuccess) {
         std::string msg = std::string("second stream: ") + hipGetErrorString(e);
         lb_free(h);
@@ -972,7 +1000,7 @@ lb_status lb_step(lb_handle* h, int64_t n_steps)
         h->pending = false;
         left -= 1;
     }
-    if (h->graph_steps > 0 && !fused_steps(h)) {
+    if (h->graph_steps > 0 && linear_steps(h)) {
         while (left >= h->graph_steps) {
             if (!h->gexec[h->cur]) {
                 lb_status s = build_graph(h, h->cur);
@@ -1370,17 +1398,14 @@ lb_status ck_restore(lb_handle* h, char* ws, const WinLayout& w, int j, uint64_t
     return LB_OK;
 }
 
-// One LB step of a window from populations A into B, its launches serialised
-// on the main stream: step number = device step counter + s_off (the caller
-// advances the counter once after a run of steps).  imp: where the node
-// impulses go (null: the library's field, consumed by the fix-up; else a
-// zeroed tape slot that keeps them); tape: substep tape (null: none), with
+// the launch context of a window's steps: imp, where the node impulses go
+// (null: the library's field, consumed by the step; else zeroed tape slots
+// that keep them, this step's at imp); tape: substep tape (null: none), with
 // tape_beads the step's starting x, v, f in the state's layout; vh, hist_len:
-// ring of bead velocities after each step (null: the handle's own).
-lb_status window_step(lb_handle* h, const void* A, void* B, unsigned long long* imp, double* tape,
-                      double* tape_beads, double* vh, int hist_len, uint32_t s_off)
+// ring of bead velocities after each step (null: the handle's own)
+LaunchCtx window_ctx(const lb_handle* h, unsigned long long* imp, double* tape, double* tape_beads, double* vh,
+                     int hist_len)
 {
-    const bool f64 = h->prec == LB_FP64;
     LaunchCtx c = h->ctx;
     c.tape = tape;
     c.tape_x0 = tape ? tape_beads : nullptr;
@@ -1388,16 +1413,40 @@ lb_status window_step(lb_handle* h, const void* A, void* B, unsigned long long* 
     c.tape_fo = (h->lo.st_f - h->lo.st_x) / sizeof(double);
     if (imp) { c.imp = imp; c.keep_imp = 1; }
     if (vh) { c.vhist = vh; c.hist_len = hist_len; }
+    return c;
+}
+
+// the first step of a run of window steps: the nodes set aside for its chains
+lb_status window_begin(lb_handle* h, uint32_t s_off)
+{
     const int nc = (int)h->couple_host.size();
-    if (nc)
-        HIPCHK(h, f64 ? launch_couple<double>(c, A, h->couple_list, nc, h->lo.couple_block, s_off)
-                      : launch_couple<float>(c, A, h->couple_list, nc, h->lo.couple_block, s_off));
-    HIPCHK(h, f64 ? launch_collide<double>(c, A, B, -1, 0, (uint32_t)h->lo.total_tiles, s_off)
-                  : launch_collide<float>(c, A, B, -1, 0, (uint32_t)h->lo.total_tiles, s_off));
-    if (h->lo.total_beads)
-        HIPCHK(h, f64 ? launch_fixup<double>(c, A, B, 0, h->lo.total_beads, s_off)
-                      : launch_fixup<float>(c, A, B, 0, h->lo.total_beads, s_off));
+    if (nc) HIPCHK(h, launch_step_begin(h->ctx, h->couple_list, nc, s_off));
+    return LB_OK;
+}
+
+// One LB step of a window from populations A into B on the main stream, one
+// kernel: step number = device step counter + s_off (the caller advances the
+// counter once after a run of steps).  Aprev, imp_prev: as in launch_step.
+lb_status window_step(lb_handle* h, const LaunchCtx& c, void* A, void* B, const void* Aprev,
+                      unsigned long long* imp_prev, uint32_t s_off)
+{
+    if (!h->couple_host.empty()) {
+        const lb_status s = enqueue_one(h, c, A, B, Aprev, imp_prev, s_off);
+        if (s != LB_OK) return s;
+    } else {
+        HIPCHK(h, h->prec == LB_FP64 ? launch_collide<double>(c, A, B, -1, 0, (uint32_t)h->lo.total_tiles, s_off)
+                                     : launch_collide<float>(c, A, B, -1, 0, (uint32_t)h->lo.total_tiles, s_off));
+    }
     h->step += 1;
+    return LB_OK;
+}
+
+// the end of a run of window steps, after its last one (c, A, B), the device
+// counter advanced
+lb_status window_end(lb_handle* h, const LaunchCtx& c, const void* A, void* B, uint32_t advance)
+{
+    if (!h->couple_host.empty()) return enqueue_one_end(h, c, A, B, advance);
+    if (advance) HIPCHK(h, launch_advance(h->ctx, advance));
     return LB_OK;
 }
 
@@ -1457,18 +1506,22 @@ lb_status lb_window_forward(lb_handle* h, void* d_ws, size_t bytes, int32_t T, i
     h->win_step0 = h->step;
     // the coupling kernel writes the bead velocities after step s into slot
     // s mod T of the window's ring: slot (step0 + t) mod T holds step t
+    const LaunchCtx c = window_ctx(h, nullptr, nullptr, nullptr, (double*)(ws + w.vh), T);
     int t_adv = 0;   // steps the device counter has been advanced by
     for (int t = 0; t < T; ++t) {
+        lb_status s = LB_OK;
         if (t % k == 0) {
-            lb_status s = ck_save(h, ws, w, t / k);
-            if (s != LB_OK) return s;
+            s = ck_save(h, ws, w, t / k);
+            if (s == LB_OK) s = window_begin(h, 0);
         }
-        lb_status s = window_step(h, h->pop(h->cur), h->pop(1 - h->cur), nullptr, nullptr, nullptr,
-                                  (double*)(ws + w.vh), T, (uint32_t)(t - t_adv));
+        void* A = h->pop(h->cur);
+        void* B = h->pop(1 - h->cur);
+        if (s == LB_OK) s = window_step(h, c, A, B, B, c.imp, (uint32_t)(t - t_adv));
         if (s != LB_OK) return s;
         h->cur ^= 1;
         if ((t + 1) % k == 0 || t + 1 == T) {   // the device counter catches up before a checkpoint
-            HIPCHK(h, launch_advance(h->ctx, (uint32_t)(t + 1 - t_adv)));
+            s = window_end(h, c, A, B, (uint32_t)(t + 1 - t_adv));
+            if (s != LB_OK) return s;
             t_adv = t + 1;
         }
     }
@@ -1567,13 +1620,17 @@ lb_status lb_window_backward(lb_handle* h, void* d_ws, size_t bytes, const doubl
         // its own zeroed impulse slot
         HIPCHK(h, hipMemcpyAsync(tpop, ws + w.ck_pop + seg * popb, popb, hipMemcpyDeviceToDevice, h->stream));
         HIPCHK(h, hipMemsetAsync(timp, 0, (size_t)(t1 - t0) * 3 * nodes * 8, h->stream));
+        st = window_begin(h, (uint32_t)t0);
+        if (st != LB_OK) return st;
         for (int t = t0; t < t1; ++t) {
             const int j = t - t0;
             // the coupling kernel records the step's starting beads in slot j
-            st = window_step(h, tpop + j * popb, tpop + (j + 1) * popb,
-                             (unsigned long long*)(timp + (size_t)j * 3 * nodes * 8),
-                             (double*)(tsub + (size_t)j * smax * nbx * TAPE_REC * sizeof(double)),
-                             (double*)(tbeads + (size_t)j * w.bspan), nullptr, 0, (uint32_t)t);
+            unsigned long long* imp = (unsigned long long*)(timp + (size_t)j * 3 * nodes * 8);
+            const LaunchCtx c = window_ctx(h, imp, (double*)(tsub + (size_t)j * smax * nbx * TAPE_REC * sizeof(double)),
+                                           (double*)(tbeads + (size_t)j * w.bspan), nullptr, 0);
+            st = window_step(h, c, tpop + j * popb, tpop + (j + 1) * popb, j ? tpop + (j - 1) * popb : nullptr,
+                             j ? imp - 3 * nodes : nullptr, (uint32_t)t);
+            if (st == LB_OK && t + 1 == t1) st = window_end(h, c, tpop + j * popb, tpop + (j + 1) * popb, 0);
             if (st != LB_OK) return st;
         }
         HIPCHK(h, hipEventRecord(replayed[tb], h->stream));
@@ -1603,8 +1660,8 @@ lb_status lb_window_backward(lb_handle* h, void* d_ws, size_t bytes, const doubl
             a.gz = (double*)(ws + w.gz);
             a.nodes = nodes;
             const int nc = (int)h->couple_host.size();
-            HIPCHK(h, f64 ? launch_adj_couple<double>(rc, h->couple_list, nc, lo.couple_block, P, a, stepv)
-                          : launch_adj_couple<float>(rc, h->couple_list, nc, lo.couple_block, P, a, stepv));
+            HIPCHK(h, f64 ? launch_adj_couple<double>(rc, h->couple_list, nc, lo.adj_block, P, a, stepv)
+                          : launch_adj_couple<float>(rc, h->couple_list, nc, lo.adj_block, P, a, stepv));
             std::swap(lam_next, lam_cur);
         }
         HIPCHK(h, hipEventRecord(reversed[tb], rs));
@@ -1730,7 +1787,6 @@ void lb_free(lb_handle* h)
     if (h->ev_table) (void)hipEventDestroy(h->ev_table);
     if (h->ev_head) (void)hipEventDestroy(h->ev_head);
     if (h->ev_def) (void)hipEventDestroy(h->ev_def);
-    if (h->ev_coll) (void)hipEventDestroy(h->ev_coll);
     if (h->stream2) (void)hipStreamDestroy(h->stream2);
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
     delete h;

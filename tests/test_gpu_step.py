@@ -1,0 +1,110 @@
+"""Batched steps in one kernel (chains of at most 256 beads): the chain's
+workgroup collides the nodes set aside for it, the tiles all others.  Bits
+equal those of the form that re-collides the chain's nodes after the collide
+(launch mode 2); a single box also matches the FP64 oracle."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from lbtest import chain, gpu_system, initial_pops, max_rel_pop_err, oracle_state, params, say
+
+pytestmark = pytest.mark.gpu
+
+FP64, FP32 = 0, 1
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_0903_5067_amd as lbm
+    lbm.lib()
+
+
+def _run(boxes, xs, prec, overlap, graph, calls):
+    s = gpu_system(boxes, prec, xs=xs)
+    s.set_launch(batched=True, graph_steps=graph, overlap=overlap)
+    for n in calls:
+        s.step(n)
+    assert all(o["health"] == 0 for o in s.observables())
+    out = s.export_state()["boxes"]
+    s.close()
+    return out
+
+
+def _equal(a, b):
+    for i, (p, q) in enumerate(zip(a, b)):
+        for k in ("n", "x", "v", "f", "fc"):
+            assert np.array_equal(p[k], q[k]), (i, k)
+
+
+# one bead; both sides of 16, 32 and 64 beads (lanes per bead, threads per
+# workgroup), 128 / 129 and the longest chain; a box that one stencil wraps
+@pytest.mark.parametrize("prec", [FP64, FP32])
+@pytest.mark.parametrize("L,N", [(2, 1), (4, 16), (7, 17), (16, 32), (16, 33), (24, 64), (24, 65), (32, 128),
+                                 (32, 129), (32, 256)])
+def test_one_kernel_step_matches_fixup_form_and_oracle(orc, L, N, prec):
+    say("one-kernel step", L, N, prec)
+    p = params(L=L, N=N, kT=1e-2, omega_s=1.2, omega_b=0.8, omega_g=1.4, seed=21, box_id=3)
+    x = chain(p)
+    got = _run([p], [x], prec, True, 0, (5, 3))
+    _equal(got, _run([p], [x], prec, False, 0, (8,)))
+    o = oracle_state(orc, p, initial_pops(orc, p), x)
+    o.run(8)
+    if prec == FP64:
+        assert np.max(np.abs(got[0]["n"] - o.n)) < 1e-12
+        assert np.max(np.abs(got[0]["x"] - o.x)) < 1e-10
+    else:
+        assert max_rel_pop_err(got[0]["n"], o.n, orc) < 1e-5
+
+
+def _left_set_aside(p, x0, v0, x1):
+    """Beads whose end position's stencil reaches past the nodes that may be
+    set aside from (x0, v0): the start's stencil, one node wider on a side
+    closer than twice the ballistic path plus four thermal ones."""
+    m = np.minimum(2 * np.abs(v0) * p["tau_lb"] + 4 * np.sqrt(p["kT"] / p["mass"]) * p["tau_lb"], 0.5)
+    i, fr = np.floor(x0), x0 - np.floor(x0)
+    lo, hi = i - (fr < m), i + 1 + (fr > 1 - m)
+    return (np.floor(x1) < lo).any(1) | (np.floor(x1) + 1 > hi).any(1)
+
+
+@pytest.mark.parametrize("prec,graph", [(FP64, 0), (FP32, 0), (FP64, 4), (FP32, 4)])
+def test_beads_that_leave_their_set_aside_nodes(prec, graph):
+    """A chain at rest, shrunk by 7 %, flies apart within its
+    first steps: its impulses land on nodes the tiles have collided, which
+    the next step's start (or the run's end) re-collides.  A quiet box and one
+    without a chain in the batch; runs of 1, 4 and 7 steps."""
+    say("left set-aside nodes", prec, graph)
+    boxes = [params(L=16, N=16, kT=0.0, therm=0, seed=5, box_id=0),
+             params(L=12, N=0, kT=1e-2, seed=5, box_id=1),
+             params(L=24, N=60, kT=1e-2, seed=5, box_id=2)]
+    xs = [chain(b) for b in boxes]
+    xs[0] = xs[0][0] + 0.93 * (xs[0] - xs[0][0])
+    ref = gpu_system(boxes, prec, xs=xs)
+    ref.set_launch(batched=True, overlap=False)
+    left = 0
+    for _ in range(4):
+        a = ref.export_state()["boxes"][0]
+        ref.step(1)
+        left += int(_left_set_aside(boxes[0], a["x"], a["v"], ref.export_state()["boxes"][0]["x"]).sum())
+    ref.close()
+    assert left > 0
+    want = _run(boxes, xs, prec, False, 0, (12,))
+    _equal(_run(boxes, xs, prec, True, graph, (1, 4, 7)), want)
+
+
+@pytest.mark.parametrize("prec", [FP64, FP32])
+def test_many_tiles_and_wide_workgroups(prec):
+    """The launch shapes by batch: more tiles than the small-batch shape takes
+    (256-thread workgroups), and a long chain in a batch of short ones."""
+    say("step launch shapes", prec)
+    many = [params(L=104, N=48, kT=1e-2, seed=8, box_id=0), params(L=10, N=10, kT=1e-2, seed=8, box_id=1)]
+    mixed = [params(L=20, N=200, kT=1e-2, seed=8, box_id=0), params(L=10, N=10, kT=1e-2, seed=8, box_id=1),
+             params(L=9, N=24, kT=1e-2, seed=8, box_id=2)]
+    for boxes in (many, mixed):
+        xs = [chain(b) for b in boxes]
+        got = _run(boxes, xs, prec, True, 2, (5,))
+        _equal(got, _run(boxes, xs, prec, False, 0, (5,)))
+        _equal(got[1:2], _run(boxes[1:2], xs[1:2], prec, True, 0, (5,)))   # a box alone
