@@ -38,7 +38,8 @@
 //                 once per step for the beads' tables, and a collide after
 //                 the coupling that takes the node impulses itself
 //   k_stats*      FP64 conserved sums, mode variances, negative-population
-//                 count; k_chain_obs: centre of mass, R_g^2, R_e^2 (Sec. III.A)
+//                 count; k_obs: these per box, and the chain's centre of mass,
+//                 R_g^2, R_e^2 (Sec. III.A)
 #include "lbmd_device.hpp"
 #include "lbmd_kernels.hpp"
 
@@ -2192,9 +2193,41 @@ __device__ __forceinline__ double block_sum256(double acc[NV], double (*lds)[NV]
     return r;
 }
 
-// grid (records of the largest box, boxes): block (c, box) sums tiles
-// c*STAT_TPB .. c*STAT_TPB + STAT_TPB - 1 of the box, one node per thread and
-// tile, into record stat_off + c
+// Sums of v[0..23] over the 64 lanes of a wavefront (all active), written to
+// dst[0..23] by the first 16: at each stage a lane keeps half of its values
+// and hands the other half to its partner (mirrored row, mirrored half-row,
+// mirrored quad, neighbour: the partner differs in the bit that says which
+// half is kept and agrees in those before), so 24 values cost ~170
+// instructions where a full butterfly of each costs ~550; then the four rows.
+__device__ __forceinline__ void wave_sums24(const double v[24], double* dst)
+{
+    const int lane = (int)(threadIdx.x & 63u);
+    const bool b3 = lane & 8, b2 = lane & 4, b1 = lane & 2, b0 = lane & 1;
+    double a[12], c[6], d[3];
+#pragma unroll
+    for (int i = 0; i < 12; ++i) a[i] = (b3 ? v[i + 12] : v[i]) + dpp_from<0x140>(b3 ? v[i] : v[i + 12]);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) c[i] = (b2 ? a[i + 6] : a[i]) + dpp_from<0x141>(b2 ? a[i] : a[i + 6]);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) d[i] = (b1 ? c[i + 3] : c[i]) + dpp_from<0x1B>(b1 ? c[i] : c[i + 3]);
+    double r0 = (b0 ? d[2] : d[0]) + dpp_from<0xB1>(b0 ? d[0] : d[2]);
+    double r1 = d[1] + dpp_from<0xB1>(d[1]);
+#pragma unroll
+    for (int o = 16; o < 64; o <<= 1) { r0 += __shfl_xor(r0, o, 64); r1 += __shfl_xor(r1, o, 64); }
+    if (lane < 16) {
+        const int i = (b3 ? 12 : 0) + (b2 ? 6 : 0) + (b1 ? 3 : 0);
+        dst[i + (b0 ? 2 : 0)] = r0;
+        if (!b0) dst[i + 1] = r1;
+    }
+}
+
+// grid (records of the largest box, boxes): block (c, box) sums the
+// stat_tpb(n_tiles) tiles from c * stat_tpb on, one node per thread and four
+// tiles, into record stat_off + c.  Bound by HBM on large boxes (one read of
+// each population); on small ones by how many wavefronts share the nodes (a
+// 64^3 box's 64 blocks of 256 threads took 27 us).  The whole call, with one
+// copy to the host instead of four: 64^3 106 -> 39 us, 128 boxes of 15^3 178
+// -> 61, 256^3 304 -> 295 (1.275 GB).
 __device__ __forceinline__ float uniform_value(float v)
 {
     return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
@@ -2205,13 +2238,14 @@ __device__ __forceinline__ double uniform_value(double v)
                             __builtin_amdgcn_readfirstlane(__double2loint(v)));
 }
 
+constexpr int STAT_BLOCK = 1024;
 template <typename R, bool O32>
-__global__ __launch_bounds__(256) void k_stats(const BoxDev* __restrict__ boxes, const R* __restrict__ A,
-                                               double* __restrict__ part)
+__global__ __launch_bounds__(STAT_BLOCK) void k_stats(const BoxDev* __restrict__ boxes, const R* __restrict__ A,
+                                                      double* __restrict__ part)
 {
-    __shared__ double red[4][NSTAT];
+    __shared__ double red[STAT_BLOCK / 64][NSTAT];
     const BoxDev& bx = boxes[blockIdx.y];
-    const uint32_t c = blockIdx.x;
+    const uint32_t c = blockIdx.x, tpb = stat_tpb(bx.n_tiles);
     if (c >= stat_recs_of(bx.n_tiles)) return;
     const uint32_t V = (uint32_t)bx.L * bx.L * bx.L;
     const R* a = A + bx.pop_off;
@@ -2232,8 +2266,8 @@ __global__ __launch_bounds__(256) void k_stats(const BoxDev* __restrict__ boxes,
 #pragma unroll
     for (int k = 0; k < NSTAT; ++k) acc[k] = 0.0;
     uint32_t neg = 0;
-    for (int k = 0; k < STAT_TPB; ++k) {
-        const uint32_t r = (c * STAT_TPB + k) * 256u + threadIdx.x;
+    for (uint32_t k = threadIdx.x; k < 256u * tpb; k += STAT_BLOCK) {
+        const uint32_t r = c * tpb * 256u + k;
         if (r >= V) break;
         const Upwind up = upwind_of(r, bx.L, bx.inv_L);
         R dr[19];
@@ -2251,51 +2285,76 @@ __global__ __launch_bounds__(256) void k_stats(const BoxDev* __restrict__ boxes,
         for (int q = 0; q < 19; ++q) acc[5 + q] += m[q] * m[q];
     }
     acc[4] = (double)neg;   // what adding 1.0 per negative population gives, exactly
-    const double s = block_sum256<NSTAT>(acc, red);
-    if (threadIdx.x < NSTAT) part[(uint64_t)(bx.stat_off + c) * NSTAT + threadIdx.x] = s;
+    wave_sums24(acc, red[threadIdx.x / 64]);
+    __syncthreads();
+    if (threadIdx.x < NSTAT) {
+        double s = 0.0;
+        for (int w = 0; w < STAT_BLOCK / 64; ++w) s += red[w][threadIdx.x];
+        part[(uint64_t)(bx.stat_off + c) * NSTAT + threadIdx.x] = s;
+    }
 }
 
-// grid (STAT_CHUNKS, boxes): block (c, box) sums the block records of chunk
-// c of the box (a fixed split of its records into STAT_CHUNKS ranges)
+// sum of records rec[0..n-1], by a block of 256 threads: ten ranges of every
+// tenth record, then the ranges in order; the result in threads 0..NSTAT-1
+__device__ __forceinline__ double sum_records(const double* __restrict__ rec, uint32_t n, double (*red)[NSTAT])
+{
+    const uint32_t g = threadIdx.x / NSTAT, k = threadIdx.x % NSTAT;
+    if (g < 10) {
+        double s = 0.0;
+#pragma unroll 8
+        for (uint32_t i = g; i < n; i += 10) s += rec[(uint64_t)i * NSTAT + k];
+        red[g][k] = s;
+    }
+    __syncthreads();
+    double s = 0.0;
+    if (threadIdx.x < NSTAT)
+        for (int w = 0; w < 10; ++w) s += red[w][threadIdx.x];
+    return s;
+}
+
+// boxes of more than STAT_DIRECT records: grid (STAT_CHUNKS, boxes), block
+// (c, box) sums range c of the box's records
 __global__ __launch_bounds__(256) void k_stats_mid(const BoxDev* __restrict__ boxes,
                                                    const double* __restrict__ part, double* __restrict__ mid)
 {
-    __shared__ double red[4][NSTAT];
+    __shared__ double red[10][NSTAT];
     const BoxDev& bx = boxes[blockIdx.y];
     const uint32_t nrec = stat_recs_of(bx.n_tiles);
+    if (nrec <= STAT_DIRECT) return;
     const uint32_t per = (nrec + STAT_CHUNKS - 1) / STAT_CHUNKS;
-    const uint32_t t0 = blockIdx.x * per, t1 = min(nrec, t0 + per);
-    double acc[NSTAT];
-#pragma unroll
-    for (int k = 0; k < NSTAT; ++k) acc[k] = 0.0;
-    for (uint32_t tt = t0 + threadIdx.x; tt < t1; tt += 256) {
-        const double* rec = part + (uint64_t)(bx.stat_off + tt) * NSTAT;
-#pragma unroll
-        for (int k = 0; k < NSTAT; ++k) acc[k] += rec[k];
-    }
-    const double s = block_sum256<NSTAT>(acc, red);
+    const uint32_t t0 = min(nrec, blockIdx.x * per), t1 = min(nrec, t0 + per);
+    const double s = sum_records(part + (uint64_t)(bx.stat_off + t0) * NSTAT, t1 - t0, red);
     if (threadIdx.x < NSTAT) mid[((uint64_t)blockIdx.y * STAT_CHUNKS + blockIdx.x) * NSTAT + threadIdx.x] = s;
 }
 
-// one wavefront per box: the box's STAT_CHUNKS chunk sums, in chunk order
-__global__ __launch_bounds__(64) void k_stats_final(const double* __restrict__ mid, double* __restrict__ out)
-{
-    const int k = threadIdx.x;
-    if (k >= NSTAT) return;
-    const double* m = mid + (uint64_t)blockIdx.x * STAT_CHUNKS * NSTAT;
-    double s = 0.0;
-    for (int c = 0; c < STAT_CHUNKS; ++c) s += m[c * NSTAT + k];
-    out[(uint64_t)blockIdx.x * NSTAT + k] = s;
-}
-
-// one block per box: chain sums.  Record: [0..2] sum x, [3..5] sum m v,
+// one block per box: the box's record of OBS_REC doubles, [0..23] the fluid
+// sums, then the chain sums, [35] the neighbour-list builds; block 0 also
+// writes the health bits and the step behind the last record, so that one
+// copy brings everything to the host.  Chain sums: [0..2] sum x, [3..5] sum m v,
 // [6..8] sum fc, [9] sum over the chains of R_e^2, then after the second pass
 // [10] sum over beads of |x - com of the bead's chain|^2.
-constexpr int NCHAIN = 11;
+constexpr int NCHAIN = NCHAIN_REC;
 
-__global__ __launch_bounds__(256) void k_chain_obs(const BoxDev* __restrict__ boxes, ChainArgs ca,
-                                                   double* __restrict__ out)
+__global__ __launch_bounds__(256) void k_obs(const BoxDev* __restrict__ boxes, ChainArgs ca,
+                                             const double* __restrict__ part, const double* __restrict__ mid,
+                                             const Ctrl* __restrict__ ctrl, double* __restrict__ out)
 {
+    __shared__ double red10[10][NSTAT];
+    {
+        const BoxDev& bx = boxes[blockIdx.x];
+        const uint32_t nrec = stat_recs_of(bx.n_tiles);
+        const double s = nrec <= STAT_DIRECT
+                             ? sum_records(part + (uint64_t)bx.stat_off * NSTAT, nrec, red10)
+                             : sum_records(mid + (uint64_t)blockIdx.x * STAT_CHUNKS * NSTAT, STAT_CHUNKS, red10);
+        if (threadIdx.x < NSTAT) out[(uint64_t)blockIdx.x * OBS_REC + threadIdx.x] = s;
+        if (threadIdx.x == 0) {
+            out[(uint64_t)blockIdx.x * OBS_REC + NSTAT + NCHAIN] = (double)ca.nl_rebuilds[blockIdx.x];
+            if (blockIdx.x == 0) {
+                out[(uint64_t)gridDim.x * OBS_REC] = (double)ctrl->health;
+                out[(uint64_t)gridDim.x * OBS_REC + 1] = (double)ctrl->step;
+            }
+        }
+    }
     __shared__ double red[4][9];
     __shared__ double red1[4][1];
     __shared__ double sums[9];
@@ -2337,7 +2396,7 @@ __global__ __launch_bounds__(256) void k_chain_obs(const BoxDev* __restrict__ bo
     double s1[1] = {s};
     const double sg = block_sum256<1>(s1, red1);
     if (threadIdx.x == 0) {
-        double* o = out + (uint64_t)blockIdx.x * NCHAIN;
+        double* o = out + (uint64_t)blockIdx.x * OBS_REC + NSTAT;
         for (int k = 0; k < 9; ++k) o[k] = sums[k];
         o[10] = sg;
         double e2 = 0.0;
@@ -2591,8 +2650,8 @@ hipError_t launch_advance(const LaunchCtx& c, uint32_t n)
 }
 
 template <typename R>
-hipError_t launch_stats(const LaunchCtx& c, const void* A, uint32_t max_recs, double* part, double* mid,
-                        double* out)
+hipError_t launch_observables(const LaunchCtx& c, const void* A, uint32_t max_recs, double* part, double* mid,
+                              double* out)
 {
     // every box's population array under 4 GiB: 32-bit offsets
     bool o32 = true;
@@ -2600,19 +2659,15 @@ hipError_t launch_stats(const LaunchCtx& c, const void* A, uint32_t max_recs, do
         o32 = o32 && pop_elems_of((uint64_t)c.boxes_host[b].L * c.boxes_host[b].L * c.boxes_host[b].L) * sizeof(R) <
                          ((uint64_t)1 << 32);
     if (o32)
-        hipLaunchKernelGGL((k_stats<R, true>), dim3(max_recs, c.n_boxes), dim3(256), 0, c.stream, c.boxes, (const R*)A,
-                           part);
-    else
-        hipLaunchKernelGGL((k_stats<R, false>), dim3(max_recs, c.n_boxes), dim3(256), 0, c.stream, c.boxes,
+        hipLaunchKernelGGL((k_stats<R, true>), dim3(max_recs, c.n_boxes), dim3(STAT_BLOCK), 0, c.stream, c.boxes,
                            (const R*)A, part);
-    hipLaunchKernelGGL(k_stats_mid, dim3(STAT_CHUNKS, c.n_boxes), dim3(256), 0, c.stream, c.boxes, part, mid);
-    hipLaunchKernelGGL(k_stats_final, dim3(c.n_boxes), dim3(64), 0, c.stream, mid, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_chain_obs(const LaunchCtx& c, double* out)
-{
-    hipLaunchKernelGGL(k_chain_obs, dim3(c.n_boxes), dim3(256), 0, c.stream, c.boxes, chain_args(c), out);
+    else
+        hipLaunchKernelGGL((k_stats<R, false>), dim3(max_recs, c.n_boxes), dim3(STAT_BLOCK), 0, c.stream, c.boxes,
+                           (const R*)A, part);
+    if (max_recs > STAT_DIRECT)
+        hipLaunchKernelGGL(k_stats_mid, dim3(STAT_CHUNKS, c.n_boxes), dim3(256), 0, c.stream, c.boxes, part, mid);
+    hipLaunchKernelGGL(k_obs, dim3(c.n_boxes), dim3(256), 0, c.stream, c.boxes, chain_args(c), (const double*)part,
+                       (const double*)mid, (const Ctrl*)c.ctrl, out);
     return hipGetLastError();
 }
 
@@ -3148,7 +3203,7 @@ template hipError_t launch_collide_headed<float>(const LaunchCtx&, const void*, 
                                                  const int32_t*, int, int, const void*, int);
 template hipError_t launch_collide_headed<double>(const LaunchCtx&, const void*, void*, uint32_t, uint32_t,
                                                   const int32_t*, int, int, const void*, int);
-template hipError_t launch_stats<float>(const LaunchCtx&, const void*, uint32_t, double*, double*, double*);
-template hipError_t launch_stats<double>(const LaunchCtx&, const void*, uint32_t, double*, double*, double*);
+template hipError_t launch_observables<float>(const LaunchCtx&, const void*, uint32_t, double*, double*, double*);
+template hipError_t launch_observables<double>(const LaunchCtx&, const void*, uint32_t, double*, double*, double*);
 
 }  // namespace lbd

@@ -145,12 +145,12 @@ inline uint32_t head_blocks(int n_list, int max_n)
 hipError_t launch_advance(const LaunchCtx& c, uint32_t n);
 hipError_t launch_init_forces(const LaunchCtx& c, const int32_t* list, int n_list, int block);
 // observables of the state A: per-block records in part [sum of stat_recs_of(n_tiles)][NSTAT_REC]
-// (box b's from BoxDev::stat_off), per-chunk sums in mid [n_boxes][STAT_CHUNKS][NSTAT_REC], per-box
-// sums in out [n_boxes][NSTAT_REC]; max_recs: the most records of any box
+// (box b's from BoxDev::stat_off), sums of ranges of them in mid [n_boxes][STAT_CHUNKS][NSTAT_REC]
+// (boxes of more than STAT_DIRECT records), per-box records in out [n_boxes][OBS_REC], then the health
+// bits and the step; max_recs: the most records of any box
 template <typename R>
-hipError_t launch_stats(const LaunchCtx& c, const void* A, uint32_t max_recs, double* part, double* mid,
-                        double* out);
-hipError_t launch_chain_obs(const LaunchCtx& c, double* out);
+hipError_t launch_observables(const LaunchCtx& c, const void* A, uint32_t max_recs, double* part, double* mid,
+                              double* out);
 
 // device pointers of one reverse step of the adjoint window
 struct AdjArgsHost {
@@ -171,10 +171,22 @@ hipError_t launch_adj_couple(const LaunchCtx& c, const int32_t* list, int n_list
 constexpr int N_COLLIDE_VARIANTS = 13;
 constexpr int DEFAULT_COLLIDE_VARIANT = 3;   // one block per tile, at most 7 waves per SIMD
 constexpr int NSTAT_REC = 24;
-constexpr int STAT_TPB = 16;      // collide tiles per block of the observables pass (16 nodes per thread)
-constexpr int STAT_CHUNKS = 64;   // per box, the block records are summed in this many fixed ranges first
-__host__ __device__ inline uint32_t stat_recs_of(uint32_t n_tiles) { return (n_tiles + STAT_TPB - 1) / STAT_TPB; }
+constexpr uint32_t STAT_CHUNKS = 64;    // ranges of a box's block records that are summed first,
+constexpr uint32_t STAT_DIRECT = 256;   // where it has more than these
+// Collide tiles per block of the observables pass, a function of the box
+// alone: few for a small box, so that its blocks fill the GPU, as far as its
+// records and their ranges fit 64 + n_tiles / 16 of them (what
+// lb_observables_static counts per box).
+__host__ __device__ inline uint32_t stat_tpb(uint32_t n_tiles)
+{
+    return n_tiles <= 320 ? 4u : (n_tiles <= 960 ? 8u : (n_tiles <= 2880 ? 12u : 16u));
+}
+__host__ __device__ inline uint32_t stat_recs_of(uint32_t n_tiles)
+{
+    return (n_tiles + stat_tpb(n_tiles) - 1) / stat_tpb(n_tiles);
+}
 constexpr int NCHAIN_REC = 11;
+constexpr int OBS_REC = NSTAT_REC + NCHAIN_REC + 1;
 constexpr int NL_SLOTS = 32;
 constexpr int TAPE_REC = 40;     // doubles per bead and substep in the adjoint tape
 

@@ -29,7 +29,11 @@ using namespace lbd;
 // name stands for a host-side symbol, not a device address: kernels receive
 // the address hipGetSymbolAddress gives for the current device (static_scratch).
 constexpr size_t STATIC_SCRATCH_BYTES = LB_STATIC_SCRATCH_BYTES;
-static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];
+// (boxes accepted by LB_STATIC_SCRATCH_BYTES need at most this much: their
+// block records fit into what that counts for records and ranges, and the
+// ranges of the large ones come on top)
+constexpr size_t STATIC_SCRATCH_ALLOC = 2 * STATIC_SCRATCH_BYTES + ((size_t)256 << 10);
+static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_ALLOC];
 
 namespace {
 
@@ -77,7 +81,7 @@ struct Layout {
     size_t st_popA = 0, st_popB = 0, st_x = 0, st_v = 0, st_f = 0, st_fc = 0, state_bytes = 0;
     size_t sc_ctrl = 0, sc_boxes = 0, sc_ccs = 0, sc_tilebox = 0, sc_couple = 0, sc_imp = 0, sc_claim = 0,
            sc_touched = 0, sc_tcnt = 0, sc_beadbox = 0, sc_nlcnt = 0, sc_nlidx = 0, sc_nlx0 = 0,
-           sc_part = 0, sc_mid = 0, sc_stat = 0, sc_chain = 0, sc_vhist = 0, sc_nlreb = 0, sc_biglist = 0, sc_alllist = 0,
+           sc_part = 0, sc_mid = 0, sc_obs = 0, sc_vhist = 0, sc_nlreb = 0, sc_biglist = 0, sc_alllist = 0,
            sc_nearu = 0, sc_nearc = 0, sc_subrec = 0, sc_field = 0, sc_binstart = 0, sc_items = 0, sc_slotof = 0,
            sc_defer = 0, sc_dclaim = 0, sc_dlist = 0, sc_ovf = 0, sc_ovm = 0, sc_nmask[2] = {0, 0}, sc_nlist[2] = {0, 0},
            sc_steprec = 0, scratch_bytes = 0;
@@ -229,8 +233,7 @@ Layout make_layout(const lb_box_desc* b, int32_t n, int32_t prec, int32_t hist)
     Lo.sc_nlx0 = o; o = align256(o + std::max<uint64_t>(beads, 1) * 3 * sizeof(double));
     Lo.sc_part = o; o = align256(o + (size_t)Lo.stat_recs * NSTAT_REC * sizeof(double));
     Lo.sc_mid = o; o = align256(o + (size_t)n * STAT_CHUNKS * NSTAT_REC * sizeof(double));
-    Lo.sc_stat = o; o = align256(o + n * NSTAT_REC * sizeof(double));
-    Lo.sc_chain = o; o = align256(o + n * NCHAIN_REC * sizeof(double));
+    Lo.sc_obs = o; o = align256(o + ((size_t)n * OBS_REC + 2) * sizeof(double));
     Lo.sc_vhist = o; o = align256(o + (size_t)hist * std::max<uint64_t>(beads, 1) * 3 * sizeof(double));
     Lo.sc_nlreb = o; o = align256(o + n * sizeof(uint32_t));
     Lo.sc_biglist = o; o = align256(o + n * sizeof(int32_t));
@@ -1024,11 +1027,10 @@ lb_status lb_step(lb_handle* h, int64_t n_steps)
 
 namespace {
 
-// one box's lb_obs from its stats record s [NSTAT_REC] and chain record c
-// [NCHAIN_REC]
-void fill_obs(const lb_handle* h, int i, const double* s, const double* c, uint32_t rebuilds, const Ctrl& ctrl,
-              lb_obs& o)
+// one box's lb_obs from its record s [OBS_REC]
+void fill_obs(const lb_handle* h, int i, const double* s, uint32_t health, uint64_t step, lb_obs& o)
 {
+    const double* c = s + NSTAT_REC;
     const lb_box_desc& d = h->desc[i];
     std::memset(&o, 0, sizeof o);
     o.mass = (double)h->lo.V[i] * d.rho0 + s[0];
@@ -1046,9 +1048,9 @@ void fill_obs(const lb_handle* h, int i, const double* s, const double* c, uint3
     o.re2 = c[9] / chains;
     o.neg_count = s[4];
     for (int k = 0; k < 19; ++k) o.mode_sq[k] = s[5 + k];
-    o.health = ctrl.health;
-    o.nlist_builds = rebuilds;
-    o.step = ctrl.step;
+    o.health = health;
+    o.nlist_builds = (uint32_t)s[NSTAT_REC + NCHAIN_REC];
+    o.step = step;
 }
 
 }  // namespace
@@ -1060,26 +1062,19 @@ lb_status lb_observables(lb_handle* h, lb_obs* out)
     if (!h || !out) return fail(h, LB_EINVAL, "null argument");
     const Layout& lo = h->lo;
     double* part = (double*)(h->scratch + lo.sc_part);
-    double* stat = (double*)(h->scratch + lo.sc_stat);
-    double* chain = (double*)(h->scratch + lo.sc_chain);
-    const void* A = h->pop(h->cur);
     double* mid = (double*)(h->scratch + lo.sc_mid);
-    if (h->prec == LB_FP64)
-        HIPCHK(h, launch_stats<double>(h->ctx, A, lo.stat_max_recs, part, mid, stat));
-    else
-        HIPCHK(h, launch_stats<float>(h->ctx, A, lo.stat_max_recs, part, mid, stat));
-    HIPCHK(h, launch_chain_obs(h->ctx, chain));
-    std::vector<double> st(h->n_boxes * NSTAT_REC), ch(h->n_boxes * NCHAIN_REC);
-    std::vector<uint32_t> reb(h->n_boxes);
-    Ctrl ctrl;
-    HIPCHK(h, hipMemcpyAsync(reb.data(), h->scratch + lo.sc_nlreb, reb.size() * sizeof(uint32_t), hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(h, hipMemcpyAsync(st.data(), stat, st.size() * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(h, hipMemcpyAsync(ch.data(), chain, ch.size() * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(h, hipMemcpyAsync(&ctrl, h->scratch + lo.sc_ctrl, sizeof ctrl, hipMemcpyDeviceToHost, h->stream));
+    double* obs = (double*)(h->scratch + lo.sc_obs);
+    const void* A = h->pop(h->cur);
+    HIPCHK(h, h->prec == LB_FP64 ? launch_observables<double>(h->ctx, A, lo.stat_max_recs, part, mid, obs)
+                                 : launch_observables<float>(h->ctx, A, lo.stat_max_recs, part, mid, obs));
+    std::vector<double> rec((size_t)h->n_boxes * OBS_REC + 2);
+    HIPCHK(h, hipMemcpyAsync(rec.data(), obs, rec.size() * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     HIPCHK(h, hipStreamSynchronize(h->stream));
+    const double* tail = &rec[(size_t)h->n_boxes * OBS_REC];
+    const uint32_t health = (uint32_t)tail[0];
     for (int i = 0; i < h->n_boxes; ++i)
-        fill_obs(h, i, &st[i * NSTAT_REC], &ch[i * NCHAIN_REC], reb[i], ctrl, out[i]);
-    if (ctrl.health) return fail(h, LB_ENUMERIC, "device health flags set: " + std::to_string(ctrl.health));
+        fill_obs(h, i, &rec[(size_t)i * OBS_REC], health, (uint64_t)tail[1], out[i]);
+    if (health) return fail(h, LB_ENUMERIC, "device health flags set: " + std::to_string(health));
     return LB_OK;
 }
 
@@ -1088,47 +1083,47 @@ lb_status lb_observables_static(lb_handle* h, lb_obs* out)
     if (!h || !out) return fail(h, LB_EINVAL, "null argument");
     if (!h->static_scr) return fail(h, LB_EDEVICE, "no device address for the static partial-sum array");
     const Layout& lo = h->lo;
-    // partials in the static array: block records, chunk sums, box sums, chain records
-    const size_t part_b = align256((size_t)lo.stat_recs * NSTAT_REC * sizeof(double));
-    const size_t mid_b = align256((size_t)h->n_boxes * STAT_CHUNKS * NSTAT_REC * sizeof(double));
-    const size_t stat_b = align256((size_t)h->n_boxes * NSTAT_REC * sizeof(double));
-    const size_t chain_b = align256((size_t)h->n_boxes * NCHAIN_REC * sizeof(double));
-    if (part_b + mid_b + stat_b + chain_b > STATIC_SCRATCH_BYTES)
-        return fail(h, LB_ENOMEM, "boxes need " + std::to_string(part_b + mid_b + stat_b + chain_b) +
-                                      " bytes of partial sums; the static array holds " +
+    // what the boxes need of the static array: 64 records and one per 4096
+    // nodes, box sums and chain sums; the partials below fit into that
+    size_t recs = 0;
+    for (int i = 0; i < h->n_boxes; ++i) recs += (lo.n_tiles[i] + 15) / 16;
+    const size_t need = align256(recs * NSTAT_REC * sizeof(double)) +
+                        align256((size_t)h->n_boxes * STAT_CHUNKS * NSTAT_REC * sizeof(double)) +
+                        align256((size_t)h->n_boxes * NSTAT_REC * sizeof(double)) +
+                        align256((size_t)h->n_boxes * NCHAIN_REC * sizeof(double));
+    if (need > STATIC_SCRATCH_BYTES)
+        return fail(h, LB_ENOMEM, "boxes need " + std::to_string(need) + " bytes of partial sums; the static array holds " +
                                       std::to_string(STATIC_SCRATCH_BYTES));
+    // in the static array: block records, range sums (boxes that have them), box records
+    const size_t part_b = align256((size_t)lo.stat_recs * NSTAT_REC * sizeof(double));
+    const size_t mid_b = lo.stat_max_recs > STAT_DIRECT
+                             ? align256((size_t)h->n_boxes * STAT_CHUNKS * NSTAT_REC * sizeof(double)) : 0;
+    const size_t obs_b = align256(((size_t)h->n_boxes * OBS_REC + 2) * sizeof(double));
+    if (part_b + mid_b + obs_b > STATIC_SCRATCH_ALLOC)
+        return fail(h, LB_ENOMEM, "partial sums beyond the static array");
     char* base = (char*)h->static_scr;
     double* part = (double*)base;
     double* mid = (double*)(base + part_b);
-    double* stat = (double*)(base + part_b + mid_b);
-    double* chain = (double*)(base + part_b + mid_b + stat_b);
+    double* obs = (double*)(base + part_b + mid_b);
     const void* A = h->pop(h->cur);
     // every partial the kernels read is written earlier in the same call, so
     // no value carries over from a previous call
-    if (h->prec == LB_FP64)
-        HIPCHK(h, launch_stats<double>(h->ctx, A, lo.stat_max_recs, part, mid, stat));
-    else
-        HIPCHK(h, launch_stats<float>(h->ctx, A, lo.stat_max_recs, part, mid, stat));
-    HIPCHK(h, launch_chain_obs(h->ctx, chain));
-    Ctrl ctrl;
-    HIPCHK(h, hipMemcpyAsync(&ctrl, h->scratch + lo.sc_ctrl, sizeof ctrl, hipMemcpyDeviceToHost, h->stream));
-    // results to the host in chunks of boxes, through fixed buffers
+    HIPCHK(h, h->prec == LB_FP64 ? launch_observables<double>(h->ctx, A, lo.stat_max_recs, part, mid, obs)
+                                 : launch_observables<float>(h->ctx, A, lo.stat_max_recs, part, mid, obs));
+    double tail[2];
+    HIPCHK(h, hipMemcpyAsync(tail, obs + (size_t)h->n_boxes * OBS_REC, sizeof tail, hipMemcpyDeviceToHost, h->stream));
+    // results to the host in chunks of boxes, through a fixed buffer
     constexpr int CH = 32;
-    double st[CH * NSTAT_REC], ch[CH * NCHAIN_REC];
-    uint32_t reb[CH];
+    double rec[CH * OBS_REC];
     for (int b0 = 0; b0 < h->n_boxes; b0 += CH) {
         const int nb = std::min(CH, h->n_boxes - b0);
-        HIPCHK(h, hipMemcpyAsync(st, stat + (size_t)b0 * NSTAT_REC, (size_t)nb * NSTAT_REC * sizeof(double),
+        HIPCHK(h, hipMemcpyAsync(rec, obs + (size_t)b0 * OBS_REC, (size_t)nb * OBS_REC * sizeof(double),
                                  hipMemcpyDeviceToHost, h->stream));
-        HIPCHK(h, hipMemcpyAsync(ch, chain + (size_t)b0 * NCHAIN_REC, (size_t)nb * NCHAIN_REC * sizeof(double),
-                                 hipMemcpyDeviceToHost, h->stream));
-        HIPCHK(h, hipMemcpyAsync(reb, h->scratch + lo.sc_nlreb + (size_t)b0 * sizeof(uint32_t),
-                                 (size_t)nb * sizeof(uint32_t), hipMemcpyDeviceToHost, h->stream));
         HIPCHK(h, hipStreamSynchronize(h->stream));
         for (int i = 0; i < nb; ++i)
-            fill_obs(h, b0 + i, &st[i * NSTAT_REC], &ch[i * NCHAIN_REC], reb[i], ctrl, out[b0 + i]);
+            fill_obs(h, b0 + i, &rec[i * OBS_REC], (uint32_t)tail[0], (uint64_t)tail[1], out[b0 + i]);
     }
-    if (ctrl.health) return fail(h, LB_ENUMERIC, "device health flags set: " + std::to_string(ctrl.health));
+    if (tail[0] != 0.0) return fail(h, LB_ENUMERIC, "device health flags set: " + std::to_string((uint32_t)tail[0]));
     return LB_OK;
 }
 
