@@ -215,6 +215,11 @@ size_t lb_state_host_bytes(const lb_handle* h);
 lb_status lb_export_state(lb_handle* h, void* host_buf, size_t bytes);
 lb_status lb_import_state(lb_handle* h, const void* host_buf, size_t bytes);
 
+/* lb_import_state from arrays that lie apart: the step count, and per box n
+ * [19][L^3], x, v, f and fc [N][3] (host, FP64; the last four may be null in a
+ * box without beads), n_arrays = 5 per box.  Status as lb_import_state. */
+lb_status lb_import_arrays(lb_handle* h, uint64_t step, const double* const* arrays, int32_t n_arrays);
+
 /* Node impulses pending after lb_couple (the momentum the coupling of
  * Sec. II.B takes from the sites around each bead), scattered into dense host
  * arrays [3][L^3] (lattice units) per box in order; zero where no bead acted.

@@ -85,6 +85,7 @@ def lib() -> ctypes.CDLL:
         L.lb_state_host_bytes.restype = sz
         L.lb_export_state.argtypes = [vp, vp, sz]
         L.lb_import_state.argtypes = [vp, vp, sz]
+        L.lb_import_arrays.argtypes = [vp, ctypes.c_uint64, ctypes.POINTER(vp), i32]
         L.lb_pending_impulse.argtypes = [vp, ctypes.POINTER(ctypes.c_double), sz]
         L.lb_velocity_history.argtypes = [vp, i64, ctypes.POINTER(ctypes.c_double), sz]
         L.lb_bead_positions.argtypes = [vp, ctypes.POINTER(ctypes.c_double), sz]
@@ -105,7 +106,7 @@ def lib() -> ctypes.CDLL:
         L.lb_last_error.argtypes = [vp]
         L.lb_last_error.restype = ctypes.c_char_p
         for name in ("lb_query_sizes", "lb_init", "lb_couple", "lb_step", "lb_observables", "lb_observables_static",
-                     "lb_export_state", "lb_import_state", "lb_pending_impulse",
+                     "lb_export_state", "lb_import_state", "lb_import_arrays", "lb_pending_impulse",
                      "lb_velocity_history", "lb_bead_positions", "lb_set_launch", "lb_collide_only", "lb_window_forward",
                      "lb_window_backward", "lb_window_rewind", "lb_set_rates", "lb_autotune",
                      "lb_set_collide_variant"):
@@ -228,13 +229,28 @@ class LBSystem:
 
     def export_state(self) -> dict:
         nbytes = lib().lb_state_host_bytes(self.h)
-        buf = np.zeros(nbytes // 8, dtype=np.float64)
+        buf = np.empty(nbytes // 8, dtype=np.float64)
         _check(lib().lb_export_state(self.h, buf.ctypes.data_as(ctypes.c_void_p), nbytes), self.h)
         return self._split(buf)
 
     def import_state(self, state: dict):
-        buf = self._join(state)
-        _check(lib().lb_import_state(self.h, buf.ctypes.data_as(ctypes.c_void_p), buf.nbytes), self.h)
+        arrs, fits = [], len(state["boxes"]) == len(self.boxes)
+        for b, s in zip(self.boxes, state["boxes"]):
+            for k in ("n", "x", "v", "f", "fc"):
+                a = np.ascontiguousarray(s[k], dtype=np.float64)
+                fits = fits and a.size == (19 * int(b["L"]) ** 3 if k == "n" else 3 * int(b["N"]))
+                arrs.append(a)
+        if not fits:    # arrays of other sizes are taken, or refused, as one buffer
+            buf = self._join(state["step"], arrs)
+            _check(lib().lb_import_state(self.h, buf.ctypes.data_as(ctypes.c_void_p), buf.nbytes), self.h)
+            return
+        ptrs = (ctypes.c_void_p * len(arrs))(*[a.ctypes.data for a in arrs])
+        _check(lib().lb_import_arrays(self.h, int(state["step"]), ptrs, len(arrs)), self.h)
+
+    @staticmethod
+    def _join(step, arrs) -> np.ndarray:
+        head = np.array([step], dtype=np.uint64).view(np.float64)
+        return np.ascontiguousarray(np.concatenate([head] + [a.reshape(-1) for a in arrs]))
 
     def _split(self, buf: np.ndarray) -> dict:
         step = int(buf[:1].view(np.uint64)[0])
@@ -243,22 +259,14 @@ class LBSystem:
         for b in self.boxes:
             L, N = int(b["L"]), int(b["N"])
             V = L ** 3
-            n = buf[o:o + 19 * V].reshape(19, L, L, L).copy()
+            n = buf[o:o + 19 * V].reshape(19, L, L, L)
             o += 19 * V
             arrs = []
             for _ in range(4):
-                arrs.append(buf[o:o + 3 * N].reshape(N, 3).copy())
+                arrs.append(buf[o:o + 3 * N].reshape(N, 3))
                 o += 3 * N
             boxes.append({"n": n, "x": arrs[0], "v": arrs[1], "f": arrs[2], "fc": arrs[3]})
         return {"step": step, "boxes": boxes}
-
-    def _join(self, state: dict) -> np.ndarray:
-        parts = [np.array([state["step"]], dtype=np.uint64).view(np.float64)]
-        for b, s in zip(self.boxes, state["boxes"]):
-            parts.append(np.ascontiguousarray(s["n"], dtype=np.float64).reshape(-1))
-            for k in ("x", "v", "f", "fc"):
-                parts.append(np.ascontiguousarray(s[k], dtype=np.float64).reshape(-1))
-        return np.ascontiguousarray(np.concatenate(parts))
 
     def pending_impulse(self) -> list[np.ndarray]:
         total = sum(3 * int(b["L"]) ** 3 for b in self.boxes)

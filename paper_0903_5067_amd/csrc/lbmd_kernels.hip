@@ -2411,6 +2411,49 @@ __global__ __launch_bounds__(256) void k_obs(const BoxDev* __restrict__ boxes, C
     }
 }
 
+// ---------------------------------------------------------- checkpoints
+// Planes q0 .. q0 + nq - 1 of a box between the pull layout and the canonical
+// one, FP64 full populations n_q(r), node r fastest: n_q(r) = w_q rho0 +
+// p_q(r - c_q).  Bound by the copy over PCIe that follows or precedes; the
+// host loops that did this took 33 ms for a 64^3 box, out and back.
+template <typename R>
+__global__ __launch_bounds__(256) void k_export(const BoxDev* __restrict__ boxes, int bi, const R* __restrict__ A,
+                                                double* __restrict__ n, int q0, int nq)
+{
+#pragma clang fp contract(off)   // w_q rho0 rounded first: an import takes the same value off again
+    const BoxDev& bx = boxes[bi];
+    const uint32_t V = (uint32_t)bx.L * bx.L * bx.L, r = blockIdx.x * 256u + threadIdx.x;
+    if (r >= V) return;
+    const Upwind up = upwind_of(r, bx.L, bx.inv_L);
+    const R* a = A + bx.pop_off;
+#pragma unroll
+    for (int q = 0; q < 19; ++q)
+        if (q >= q0 && q < q0 + nq) n[(uint64_t)(q - q0) * V + r] = wv(q) * bx.rho0 + (double)a[pop_at(q, up.src(q))];
+}
+template <typename R>
+__global__ __launch_bounds__(256) void k_import(const BoxDev* __restrict__ boxes, int bi, const double* __restrict__ n,
+                                                R* __restrict__ A, int q0, int nq)
+{
+#pragma clang fp contract(off)
+    const BoxDev& bx = boxes[bi];
+    const uint32_t V = (uint32_t)bx.L * bx.L * bx.L, r = blockIdx.x * 256u + threadIdx.x;
+    if (r >= V) return;
+    const Upwind up = upwind_of(r, bx.L, bx.inv_L);
+    R* a = A + bx.pop_off;
+#pragma unroll
+    for (int q = 0; q < 19; ++q)
+        if (q >= q0 && q < q0 + nq) a[pop_at(q, up.src(q))] = (R)(n[(uint64_t)(q - q0) * V + r] - wv(q) * bx.rho0);
+}
+// zeros behind each box's last node (the buffer served as staging space)
+template <typename R>
+__global__ __launch_bounds__(256) void k_clear_tails(const BoxDev* __restrict__ boxes, R* __restrict__ A)
+{
+    const BoxDev& bx = boxes[blockIdx.x];
+    const uint32_t V = (uint32_t)bx.L * bx.L * bx.L, end = (V + PTILE - 1) / PTILE * PTILE;
+    for (uint32_t e = threadIdx.x; e < 19u * (end - V); e += 256)
+        A[bx.pop_off + pop_at((int)(e / (end - V)), V + e % (end - V))] = (R)0;
+}
+
 // --------------------------------------------------------------- launchers
 static ChainArgs chain_args(const LaunchCtx& c)
 {
@@ -2635,6 +2678,33 @@ hipError_t launch_collide_headed(const LaunchCtx& c, const void* A, void* B, uin
         launch_collide_headed_w<R, 5>(c, A, B, n_tiles, s_off, list, n_list, max_n, Aprev, single_box);
     return hipGetLastError();
 }
+
+template <typename R>
+hipError_t launch_export(const LaunchCtx& c, int box, const void* A, double* n, int q0, int nq)
+{
+    const uint32_t tiles = c.boxes_host[box].n_tiles;
+    hipLaunchKernelGGL(k_export<R>, dim3(tiles), dim3(256), 0, c.stream, c.boxes, box, (const R*)A, n, q0, nq);
+    return hipGetLastError();
+}
+template <typename R>
+hipError_t launch_import(const LaunchCtx& c, int box, const double* n, void* A, int q0, int nq)
+{
+    const uint32_t tiles = c.boxes_host[box].n_tiles;
+    hipLaunchKernelGGL(k_import<R>, dim3(tiles), dim3(256), 0, c.stream, c.boxes, box, n, (R*)A, q0, nq);
+    return hipGetLastError();
+}
+template <typename R>
+hipError_t launch_clear_tails(const LaunchCtx& c, void* A)
+{
+    hipLaunchKernelGGL(k_clear_tails<R>, dim3(c.n_boxes), dim3(256), 0, c.stream, c.boxes, (R*)A);
+    return hipGetLastError();
+}
+template hipError_t launch_export<float>(const LaunchCtx&, int, const void*, double*, int, int);
+template hipError_t launch_export<double>(const LaunchCtx&, int, const void*, double*, int, int);
+template hipError_t launch_import<float>(const LaunchCtx&, int, const double*, void*, int, int);
+template hipError_t launch_import<double>(const LaunchCtx&, int, const double*, void*, int, int);
+template hipError_t launch_clear_tails<float>(const LaunchCtx&, void*);
+template hipError_t launch_clear_tails<double>(const LaunchCtx&, void*);
 
 hipError_t launch_init_forces(const LaunchCtx& c, const int32_t* list, int n_list, int block)
 {

@@ -144,6 +144,15 @@ inline uint32_t head_blocks(int n_list, int max_n)
 }
 hipError_t launch_advance(const LaunchCtx& c, uint32_t n);
 hipError_t launch_init_forces(const LaunchCtx& c, const int32_t* list, int n_list, int block);
+// planes q0 .. q0 + nq - 1 of one box as canonical FP64 populations in n
+// [nq][L^3], from or into the stored populations A; zeros behind every box's
+// last node in a buffer that held other data
+template <typename R>
+hipError_t launch_export(const LaunchCtx& c, int box, const void* A, double* n, int q0, int nq);
+template <typename R>
+hipError_t launch_import(const LaunchCtx& c, int box, const double* n, void* A, int q0, int nq);
+template <typename R>
+hipError_t launch_clear_tails(const LaunchCtx& c, void* A);
 // observables of the state A: per-block records in part [sum of stat_recs_of(n_tiles)][NSTAT_REC]
 // (box b's from BoxDev::stat_off), sums of ranges of them in mid [n_boxes][STAT_CHUNKS][NSTAT_REC]
 // (boxes of more than STAT_DIRECT records), per-box records in out [n_boxes][OBS_REC], then the health

@@ -1135,90 +1135,54 @@ size_t lb_state_host_bytes(const lb_handle* h)
     return n;
 }
 
-lb_status lb_export_state(lb_handle* h, void* host_buf, size_t bytes)
+}  // extern "C"
+
+namespace {
+
+// The canonical populations are staged in the population buffer that the next
+// step writes (its contents are dead between calls), as many planes at a time
+// as it holds.
+size_t staged_planes(const lb_handle* h, int box)
 {
-    if (!h || !host_buf) return fail(h, LB_EINVAL, "null argument");
-    if (bytes < lb_state_host_bytes(h)) return fail(h, LB_ENOMEM, "host buffer too small");
-    const Layout& lo = h->lo;
-    HIPCHK(h, hipStreamSynchronize(h->stream));
-    Ctrl ctrl;
-    HIPCHK(h, hipMemcpy(&ctrl, h->scratch + lo.sc_ctrl, sizeof ctrl, hipMemcpyDeviceToHost));
-    char* o = (char*)host_buf;
-    uint64_t stepv = ctrl.step;
-    std::memcpy(o, &stepv, sizeof stepv);
-    o += sizeof stepv;
-    const char* P = (const char*)h->pop(h->cur);
-    for (int i = 0; i < h->n_boxes; ++i) {
-        const uint64_t V = lo.V[i];
-        double* n = (double*)o;
-        std::vector<char> raw(pop_elems_of(V) * lo.esz);
-        const int L = h->desc[i].L;
-        HIPCHK(h, hipMemcpy(raw.data(), P + lo.pop_off[i] * lo.esz, raw.size(), hipMemcpyDeviceToHost));
-        for (int q = 0; q < 19; ++q) {
-            const double base = wv(q) * h->desc[i].rho0;
-            // stored p_q(s) is the population that arrives at s + c_q
-            for (int z = 0; z < L; ++z)
-                for (int y = 0; y < L; ++y)
-                    for (int x = 0; x < L; ++x) {
-                        const uint64_t s = x + (uint64_t)L * (y + (uint64_t)L * z);
-                        const int xd = (x + cxv(q) + L) % L, yd = (y + cyv(q) + L) % L, zd = (z + czv(q) + L) % L;
-                        const uint64_t dd = xd + (uint64_t)L * (yd + (uint64_t)L * zd);
-                        const uint64_t a = pop_at(q, (uint32_t)s);
-                        const double dv = lo.esz == 8 ? ((const double*)raw.data())[a] : (double)((const float*)raw.data())[a];
-                        n[q * V + dd] = base + dv;
-                    }
-        }
-        o += 19 * V * sizeof(double);
-        const size_t nbb = (size_t)h->desc[i].n_beads * 3 * sizeof(double);
-        const size_t goff = lo.bead_off[i] * 3 * sizeof(double);
-        for (size_t arr : {lo.st_x, lo.st_v, lo.st_f, lo.st_fc}) {
-            if (nbb) HIPCHK(h, hipMemcpy(o, h->state + arr + goff, nbb, hipMemcpyDeviceToHost));
-            o += nbb;
-        }
-    }
-    if (ctrl.health) return fail(h, LB_ENUMERIC, "device health flags set: " + std::to_string(ctrl.health));
+    const size_t room = h->lo.pop_elems * h->lo.esz / sizeof(double);
+    return std::min<size_t>(19, room / h->lo.V[box]);
+}
+
+lb_status clear_staging(lb_handle* h)
+{
+    void* B = h->pop(1 - h->cur);
+    HIPCHK(h, h->prec == LB_FP64 ? launch_clear_tails<double>(h->ctx, B) : launch_clear_tails<float>(h->ctx, B));
     return LB_OK;
 }
 
-lb_status lb_import_state(lb_handle* h, const void* host_buf, size_t bytes)
+// part(box, k): host array k of a box (0: n, then x, v, f, fc)
+template <typename P>
+lb_status import_parts(lb_handle* h, uint64_t stepv, P part)
 {
-    if (!h || !host_buf) return fail(h, LB_EINVAL, "null argument");
-    if (bytes < lb_state_host_bytes(h)) return fail(h, LB_ENOMEM, "host buffer too small");
-    if (h->pending) return fail(h, LB_ESTATE, "impulses pending from lb_couple");
     const Layout& lo = h->lo;
-    HIPCHK(h, hipStreamSynchronize(h->stream));
-    const char* o = (const char*)host_buf;
-    uint64_t stepv;
-    std::memcpy(&stepv, o, sizeof stepv);
-    o += sizeof stepv;
-    char* P = (char*)h->pop(h->cur);
+    const bool f64 = h->prec == LB_FP64;
+    double* stage = (double*)h->pop(1 - h->cur);
+    void* A = h->pop(h->cur);
     for (int i = 0; i < h->n_boxes; ++i) {
         const uint64_t V = lo.V[i];
-        const double* n = (const double*)o;
-        std::vector<char> raw(pop_elems_of(V) * lo.esz, 0);
-        const int L = h->desc[i].L;
-        for (int q = 0; q < 19; ++q) {
-            const double base = wv(q) * h->desc[i].rho0;
-            for (int z = 0; z < L; ++z)
-                for (int y = 0; y < L; ++y)
-                    for (int x = 0; x < L; ++x) {
-                        const uint64_t s = x + (uint64_t)L * (y + (uint64_t)L * z);
-                        const int xd = (x + cxv(q) + L) % L, yd = (y + cyv(q) + L) % L, zd = (z + czv(q) + L) % L;
-                        const double dv = n[q * V + xd + (uint64_t)L * (yd + (uint64_t)L * zd)] - base;
-                        const uint64_t a = pop_at(q, (uint32_t)s);
-                        if (lo.esz == 8) ((double*)raw.data())[a] = dv;
-                        else ((float*)raw.data())[a] = (float)dv;
-                    }
+        const double* n = part(i, 0);
+        const int per = (int)staged_planes(h, i);
+        for (int q = 0; q < 19; q += per) {
+            const int nq = std::min(per, 19 - q);
+            HIPCHK(h, hipMemcpyAsync(stage, n + (uint64_t)q * V, (size_t)nq * V * sizeof(double), hipMemcpyHostToDevice,
+                                     h->stream));
+            HIPCHK(h, f64 ? launch_import<double>(h->ctx, i, stage, A, q, nq)
+                          : launch_import<float>(h->ctx, i, stage, A, q, nq));
         }
-        HIPCHK(h, hipMemcpy(P + lo.pop_off[i] * lo.esz, raw.data(), raw.size(), hipMemcpyHostToDevice));
-        o += 19 * V * sizeof(double);
         const size_t nbb = (size_t)h->desc[i].n_beads * 3 * sizeof(double);
         const size_t goff = lo.bead_off[i] * 3 * sizeof(double);
-        for (size_t arr : {lo.st_x, lo.st_v, lo.st_f, lo.st_fc}) {
-            if (nbb) HIPCHK(h, hipMemcpy(h->state + arr + goff, o, nbb, hipMemcpyHostToDevice));
-            o += nbb;
-        }
+        const size_t arrs[4] = {lo.st_x, lo.st_v, lo.st_f, lo.st_fc};
+        for (int k = 0; k < 4 && nbb; ++k)
+            HIPCHK(h, hipMemcpyAsync(h->state + arrs[k] + goff, part(i, 1 + k), nbb, hipMemcpyHostToDevice, h->stream));
     }
+    lb_status st = clear_staging(h);
+    if (st != LB_OK) return st;
+    HIPCHK(h, hipStreamSynchronize(h->stream));
     Ctrl ctrl;
     HIPCHK(h, hipMemcpy(&ctrl, h->scratch + lo.sc_ctrl, sizeof ctrl, hipMemcpyDeviceToHost));
     ctrl.step = (uint32_t)stepv;
@@ -1230,6 +1194,79 @@ lb_status lb_import_state(lb_handle* h, const void* host_buf, size_t bytes)
     HIPCHK(h, clear_step_stamps(h));
     h->step = stepv;
     return LB_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+lb_status lb_export_state(lb_handle* h, void* host_buf, size_t bytes)
+{
+    if (!h || !host_buf) return fail(h, LB_EINVAL, "null argument");
+    if (bytes < lb_state_host_bytes(h)) return fail(h, LB_ENOMEM, "host buffer too small");
+    const Layout& lo = h->lo;
+    const bool f64 = h->prec == LB_FP64;
+    HIPCHK(h, hipStreamSynchronize(h->stream));
+    Ctrl ctrl;
+    HIPCHK(h, hipMemcpy(&ctrl, h->scratch + lo.sc_ctrl, sizeof ctrl, hipMemcpyDeviceToHost));
+    char* o = (char*)host_buf;
+    uint64_t stepv = ctrl.step;
+    std::memcpy(o, &stepv, sizeof stepv);
+    o += sizeof stepv;
+    const void* A = h->pop(h->cur);
+    double* stage = (double*)h->pop(1 - h->cur);
+    for (int i = 0; i < h->n_boxes; ++i) {
+        const uint64_t V = lo.V[i];
+        const int per = (int)staged_planes(h, i);
+        for (int q = 0; q < 19; q += per) {
+            const int nq = std::min(per, 19 - q);
+            HIPCHK(h, f64 ? launch_export<double>(h->ctx, i, A, stage, q, nq)
+                          : launch_export<float>(h->ctx, i, A, stage, q, nq));
+            HIPCHK(h, hipMemcpyAsync(o, stage, (size_t)nq * V * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+            o += (size_t)nq * V * sizeof(double);
+        }
+        const size_t nbb = (size_t)h->desc[i].n_beads * 3 * sizeof(double);
+        const size_t goff = lo.bead_off[i] * 3 * sizeof(double);
+        for (size_t arr : {lo.st_x, lo.st_v, lo.st_f, lo.st_fc}) {
+            if (nbb) HIPCHK(h, hipMemcpyAsync(o, h->state + arr + goff, nbb, hipMemcpyDeviceToHost, h->stream));
+            o += nbb;
+        }
+    }
+    const lb_status st = clear_staging(h);
+    if (st != LB_OK) return st;
+    HIPCHK(h, hipStreamSynchronize(h->stream));
+    if (ctrl.health) return fail(h, LB_ENUMERIC, "device health flags set: " + std::to_string(ctrl.health));
+    return LB_OK;
+}
+
+lb_status lb_import_state(lb_handle* h, const void* host_buf, size_t bytes)
+{
+    if (!h || !host_buf) return fail(h, LB_EINVAL, "null argument");
+    if (bytes < lb_state_host_bytes(h)) return fail(h, LB_ENOMEM, "host buffer too small");
+    if (h->pending) return fail(h, LB_ESTATE, "impulses pending from lb_couple");
+    HIPCHK(h, hipStreamSynchronize(h->stream));
+    uint64_t stepv;
+    std::memcpy(&stepv, host_buf, sizeof stepv);
+    std::vector<const double*> at(h->n_boxes);
+    const double* o = (const double*)((const char*)host_buf + sizeof stepv);
+    for (int i = 0; i < h->n_boxes; ++i) {
+        at[i] = o;
+        o += 19 * h->lo.V[i] + 12 * (uint64_t)h->desc[i].n_beads;
+    }
+    return import_parts(h, stepv, [&](int i, int k) {
+        return k == 0 ? at[i] : at[i] + 19 * h->lo.V[i] + (uint64_t)(k - 1) * 3 * h->desc[i].n_beads;
+    });
+}
+
+lb_status lb_import_arrays(lb_handle* h, uint64_t step, const double* const* arrays, int32_t n_arrays)
+{
+    if (!h || !arrays) return fail(h, LB_EINVAL, "null argument");
+    if (n_arrays != 5 * h->n_boxes) return fail(h, LB_EINVAL, "five arrays per box expected");
+    for (int k = 0; k < n_arrays; ++k)
+        if (!arrays[k] && (k % 5 == 0 || h->desc[k / 5].n_beads > 0)) return fail(h, LB_EINVAL, "null array");
+    if (h->pending) return fail(h, LB_ESTATE, "impulses pending from lb_couple");
+    HIPCHK(h, hipStreamSynchronize(h->stream));
+    return import_parts(h, step, [&](int i, int k) { return arrays[5 * i + k]; });
 }
 
 lb_status lb_pending_impulse(lb_handle* h, double* host_dense, size_t bytes)

@@ -108,3 +108,33 @@ def test_many_tiles_and_wide_workgroups(prec):
         got = _run(boxes, xs, prec, True, 2, (5,))
         _equal(got, _run(boxes, xs, prec, False, 0, (5,)))
         _equal(got[1:2], _run(boxes[1:2], xs[1:2], prec, True, 0, (5,)))   # a box alone
+
+
+@pytest.mark.parametrize("prec", [FP64, FP32])
+def test_checkpoint_of_uneven_boxes(prec):
+    """Export and import through the staging buffer: boxes whose planes fit it
+    in one piece, in several, and with a ragged last tile; the exported
+    populations are the stored ones (rho0 not 1: w_i rho0 rounds), an import
+    of them exports the same, a state given as one oversized list of arrays is
+    refused, and a run goes on from an import as from the export."""
+    import paper_0903_5067_amd as lbm
+    say("checkpoint of uneven boxes", prec)
+    boxes = [params(L=11, N=9, kT=1e-2, rho0=0.864, seed=4, box_id=0), params(L=2, N=0, kT=1e-2, seed=4, box_id=1),
+             params(L=20, N=30, kT=1e-2, rho0=0.9, seed=4, box_id=2)]
+    s = gpu_system(boxes, prec, xs=[chain(b) for b in boxes])
+    s.step(5)
+    a = s.export_state()
+    obs = s.observables()
+    for b, o, p in zip(a["boxes"], obs, boxes):
+        assert abs(b["n"].sum() - o["mass"]) < 1e-9 * o["mass"]
+    s.import_state(a)
+    c = s.export_state()
+    s.step(3)
+    d = s.export_state()
+    s.import_state(a)
+    s.step(3)
+    _equal(a["boxes"], c["boxes"])
+    _equal(d["boxes"], s.export_state()["boxes"])
+    with pytest.raises(lbm.LBError):
+        s.import_state({"step": a["step"], "boxes": a["boxes"][:2]})
+    s.close()
