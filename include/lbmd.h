@@ -252,13 +252,15 @@ lb_status lb_bead_positions(lb_handle* h, double* host_out, size_t bytes);
  * graph_steps > 0 records that many LB steps (rounded up to even) in a HIP
  * graph and replays it; 0 launches kernels directly.  The graphs of both
  * buffer parities are recorded and instantiated here, before returning
- * (synchronous), so that lb_step only replays them.  Only steps that keep to
- * one stream are recorded: the per-box form, one-kernel steps, boxes without
- * beads, and boxes that their beads all cover densely; the other batched forms, whose steps put kernels on two
- * streams, are always launched directly.  Batched FP32 steps whose chains all
- * exceed 256 beads (and cover no box densely) put each step's node tables
- * into its collide, with a resident chain kernel that waits for them (a
- * stream under capture takes another form).
+ * (synchronous), so that lb_step only replays them.  Recorded are steps that
+ * keep to one stream (the per-box form, one-kernel steps, boxes without beads,
+ * boxes that their beads all cover densely) and batched steps with chains
+ * above 256 beads and no dense box; the other batched forms, whose steps put
+ * kernels on two streams, are always launched directly, and so are batched
+ * FP32 steps whose chains all exceed 256 beads (and cover no box densely):
+ * each collide there carries the step's node tables and a resident chain
+ * kernel waits for them, an order that graph replay does not keep (a stream
+ * under capture takes a graph-safe form).
  * Such a run also needs the GPU to run kernels of its two streams at once;
  * where a tool runs one kernel at a time (hardware counter collection), the
  * wait gives up and LB_HEALTH_SYNC is set.  batched = 3 is batched = 1

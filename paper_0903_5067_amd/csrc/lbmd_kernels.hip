@@ -813,6 +813,7 @@ constexpr int NEAR = 27;    // nodes in the table of one bead
 // (under 2.5e-4 for L <= 1625) cannot drop a partner, and the few extra
 // partners are skipped by the force loop's exact cut-off test.
 constexpr int NBK = 4096;
+constexpr int SORT_REGS = 16;   // lists up to this long are sorted in registers
 constexpr double NL_FP32_MARGIN = 1e-3;
 __device__ __forceinline__ int list_cells(int L, double rl)
 {
@@ -922,7 +923,7 @@ __device__ __forceinline__ void fixup_node_claim_first(const BoxDev& bx, const C
 template <typename R>
 __device__ __forceinline__ void near_work(const BoxDev* __restrict__ boxes, const int32_t* __restrict__ list,
                                           R* A, const ChainArgs& ca, R* __restrict__ near_u,
-                                          int4* __restrict__ near_c, const R* __restrict__ field, Ctrl* ctrl,
+                                          int4* __restrict__ near_c, Ctrl* ctrl,
                                           uint32_t t, const CollideConst<R>* __restrict__ ccs,
                                           const int32_t* __restrict__ bead_box, uint32_t* __restrict__ claim,
                                           const R* __restrict__ Aprev, int one_box, const BoxDev& one, int li,
@@ -943,7 +944,7 @@ __device__ __forceinline__ void near_work(const BoxDev* __restrict__ boxes, cons
     const int bi = one_box >= 0 ? one_box : list[li];
     const BoxDev bx = one_box >= 0 ? one : boxes[bi];   // a copy: its fields stay in registers
     const int N = bx.N, L = bx.L;
-    if (item >= N * NEAR) return;
+    if (item >= N * NEAR || bx.dense) return;   // the beads of a dense box read the node field
     const int b = item / NEAR, q = item - b * NEAR;
     const uint64_t g = bx.bead_off + (uint64_t)b;
     const double Ld = (double)L, iL = bx.inv_L;
@@ -953,11 +954,6 @@ __device__ __forceinline__ void near_work(const BoxDev* __restrict__ boxes, cons
     const int ix = n0 - 1 + q % 3, iy = n1 - 1 + (q / 3) % 3, iz = n2 - 1 + q / 9;
     const uint32_t node = node_of(ix, iy, iz, L);
     R* o = near_u + (g * NEAR + (uint64_t)q) * 3;
-    if (bx.dense) {
-        const R* fu = field + 3 * (bx.field_off + node);
-        o[0] = fu[0]; o[1] = fu[1]; o[2] = fu[2];
-        return;
-    }
     const uint32_t nz = node / ((uint32_t)L * (uint32_t)L), rem = node - nz * (uint32_t)L * (uint32_t)L;
     const uint32_t ny = rem / (uint32_t)L, nx = rem - ny * (uint32_t)L;
     const Upwind up(nx, ny, nz, (uint32_t)L);
@@ -1006,7 +1002,7 @@ template <typename R>
 __global__ __launch_bounds__(256) void k_near_nodes(const BoxDev* __restrict__ boxes,
                                                     const int32_t* __restrict__ list, R* A,
                                                     ChainArgs ca, R* __restrict__ near_u, int4* __restrict__ near_c,
-                                                    const R* __restrict__ field, Ctrl* __restrict__ ctrl,
+                                                    Ctrl* __restrict__ ctrl,
                                                     uint32_t s_off, const CollideConst<R>* __restrict__ ccs,
                                                     const int32_t* __restrict__ bead_box,
                                                     uint32_t* __restrict__ claim, const R* __restrict__ Aprev,
@@ -1019,7 +1015,7 @@ __global__ __launch_bounds__(256) void k_near_nodes(const BoxDev* __restrict__ b
     }
     const uint32_t nth = gridDim.x * gridDim.y * blockDim.x;
     const uint32_t e0 = (blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x;
-    near_work<R>(boxes, list, A, ca, near_u, near_c, field, ctrl, t, ccs, bead_box, claim, Aprev, one_box, one,
+    near_work<R>(boxes, list, A, ca, near_u, near_c, ctrl, t, ccs, bead_box, claim, Aprev, one_box, one,
                  (int)blockIdx.y, (int)(blockIdx.x * blockDim.x + threadIdx.x), e0, nth, true);
 }
 
@@ -1131,26 +1127,37 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, W))) voi
 }
 
 // one substep of one bead, as k_spread reads it
-constexpr int REC = 8;   // doubles: fraction x3, coupling force x3, base node, unused
+constexpr int REC = 8;   // doubles: fraction x3, coupling force x3, base cell (packed), unused
+// a base cell as one number: its coordinates, 11 bits each (L <= 1625)
+__device__ __forceinline__ double pack_cell(int x, int y, int z)
+{
+    return __longlong_as_double((long long)((unsigned long long)x | (unsigned long long)y << 11 | (unsigned long long)z << 22));
+}
+struct Cell { int x, y, z; };
+__device__ __forceinline__ Cell cell_of_packed(unsigned long long c)
+{
+    return Cell{(int)(c & 2047u), (int)((c >> 11) & 2047u), (int)(c >> 22)};
+}
 
-template <typename R>
-__global__ __launch_bounds__(WG_MAXB) void k_chain_wg(const BoxDev* __restrict__ boxes,
+// NT: threads, and the most beads; chains up to 512 beads take 512 threads,
+// which leaves each twice the registers (none spilled) at the same waves per bead.
+template <typename R, int NT>
+__global__ __launch_bounds__(NT) void k_chain_wg(const BoxDev* __restrict__ boxes,
                                                       const int32_t* __restrict__ list,
                                                       const R* __restrict__ A, ChainArgs ca,
                                                       const R* __restrict__ near_u,
-                                                      const int4* __restrict__ near_c,
+                                                      const int4* __restrict__ near_c, const R* __restrict__ field,
                                                       double* __restrict__ rec, Ctrl* __restrict__ ctrl,
                                                       uint32_t s_off, const int32_t* __restrict__ ca_bead_box,
                                                       int clear_ovf, uint32_t wait_head, int stamp_next)
 {
-    __shared__ double xs[3 * WG_MAXB];           // current positions
-    __shared__ double x0s[3 * WG_MAXB];          // positions at the last list build
-    __shared__ uint16_t nls[NL_SLOTS * WG_MAXB];  // neighbour k of bead b at [k * WG_MAXB + b]
+    __shared__ double xs[3 * NT];           // current positions
+    __shared__ double x0s[3 * NT];          // positions at the last list build
+    __shared__ uint16_t nls[NL_SLOTS * NT];  // neighbour k of bead b at [k * NT + b]
     __shared__ uint32_t bk_cnt[NBK];             // list build: beads per cell bucket,
-    __shared__ uint32_t bk_wsum[WG_MAXB / 64];   //   per-wave totals of the scan,
+    __shared__ uint32_t bk_wsum[NT / 64];   //   per-wave totals of the scan,
     __shared__ uint16_t bk_start[NBK + 1];       //   first slot of each bucket,
-    __shared__ uint16_t bk_bead[WG_MAXB];        //   beads ordered by bucket,
-    __shared__ float bk_pos[3 * WG_MAXB];        //   and their positions wrapped into the box
+    __shared__ float4 bk_pos[NT];           //   beads ordered by bucket: position wrapped into the box, index
     __builtin_amdgcn_s_setprio(3);   // latency-bound chain beside the bandwidth-bound collide
     const int bi = list[blockIdx.x];
     const BoxDev& bx = boxes[bi];
@@ -1168,6 +1175,30 @@ __global__ __launch_bounds__(WG_MAXB) void k_chain_wg(const BoxDev* __restrict__
     const double rl2 = rl * rl;
     const int nl_cap = ca.nl_cap < NL_SLOTS ? ca.nl_cap : NL_SLOTS;
 
+    double x[3] = {0, 0, 0}, v[3] = {0, 0, 0}, f[3] = {0, 0, 0};
+    int nl_n = -2;
+    int4 nc = make_int4(0, 0, 0, 0);
+    // the beads and their lists, ahead of the wait: the previous chain kernel
+    // left them
+    if (act) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            x[c] = ca.x[3 * g + c]; v[c] = ca.v[3 * g + c]; f[c] = ca.f[3 * g + c];
+            x0s[3 * b + c] = ca.nl_x0[3 * g + c];
+        }
+        nl_n = ca.nl_cnt[g];
+        // the list, eight entries per load
+        const uint4* row = (const uint4*)(ca.nl_idx + g * NL_SLOTS);
+#pragma unroll
+        for (int q = 0; q < NL_SLOTS / 8; ++q)
+            if (nl_n > 8 * q) {
+                const uint4 e = row[q];
+                const uint32_t w[4] = {e.x, e.y, e.z, e.w};
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    nls[(8 * q + k) * NT + b] = (uint16_t)(w[k / 2] >> (16 * (k & 1)));
+            }
+    }
     if (wait_head) {
         // the node tables come from the first workgroups of this step's
         // collide, which starts once the previous collide is done
@@ -1182,7 +1213,7 @@ __global__ __launch_bounds__(WG_MAXB) void k_chain_wg(const BoxDev* __restrict__
         // up by the node-table work, which left them in the field: clear
         // them before this step's spread, then reset both list counts
         const uint32_t n_ovf = min(ctrl->ovf_cnt, ca.ovf_cap);
-        for (uint32_t e = (uint32_t)b; e < n_ovf; e += WG_MAXB) {
+        for (uint32_t e = (uint32_t)b; e < n_ovf; e += NT) {
             const uint64_t gg = ca.ovf[2 * (uint64_t)e];
             const uint32_t r = ca.ovf[2 * (uint64_t)e + 1];
             unsigned long long* q = ca.imp + 3 * (boxes[ca_bead_box[gg]].node_off + r);
@@ -1192,24 +1223,15 @@ __global__ __launch_bounds__(WG_MAXB) void k_chain_wg(const BoxDev* __restrict__
         if (b == 0) { ctrl->ovf_cnt = 0u; ctrl->defer_cnt = 0u; }
     }
 
-    double x[3] = {0, 0, 0}, v[3] = {0, 0, 0}, f[3] = {0, 0, 0};
-    int nl_n = -2;
-    int4 nc = make_int4(0, 0, 0, 0);
-    if (act) {
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            x[c] = ca.x[3 * g + c]; v[c] = ca.v[3 * g + c]; f[c] = ca.f[3 * g + c];
-            x0s[3 * b + c] = ca.nl_x0[3 * g + c];
-        }
-        nc = near_c[g];
-        nl_n = ca.nl_cnt[g];
-        for (int k = 0; k < (nl_n > 0 ? nl_n : 0); ++k) nls[k * WG_MAXB + b] = ca.nl_idx[g * ca.nl_cap + k];
-    }
+    if (act && !bx.dense) nc = near_c[g];
     int rebuilds = 0;
     int cb0 = -1, cb1 = -1, cb2 = -1;   // base cell of the cached stencil
     R cu[8][3];                          // its node velocities (MD units), storage precision
     uint32_t hbits = 0;
     int tcnt = 0;
+    // the fix-up's node list: not for dense boxes and deferred tiles, whose
+    // nodes no fix-up visits
+    const bool list_touched = !bx.dense && !ca.defer;
 
     for (int s = 0; s < bx.substeps; ++s) {
         if (act) {
@@ -1231,6 +1253,7 @@ __global__ __launch_bounds__(WG_MAXB) void k_chain_wg(const BoxDev* __restrict__
         if (rebuild) {
             ++rebuilds;
             int cnt = 0;
+            bool stored = false;
             // scan over every bead (boxes under three list radii across):
             // partner j joins the list when its minimum-image distance is
             // below the list radius
@@ -1238,7 +1261,7 @@ __global__ __launch_bounds__(WG_MAXB) void k_chain_wg(const BoxDev* __restrict__
                 double d0 = x[0] - xs[3 * j], d1 = x[1] - xs[3 * j + 1], d2 = x[2] - xs[3 * j + 2];
                 d0 -= Ld * rint(d0 * iL); d1 -= Ld * rint(d1 * iL); d2 -= Ld * rint(d2 * iL);
                 if (d0 * d0 + d1 * d1 + d2 * d2 < rl2) {
-                    if (cnt < nl_cap) nls[cnt * WG_MAXB + b] = (uint16_t)j;
+                    if (cnt < nl_cap) nls[cnt * NT + b] = (uint16_t)j;
                     ++cnt;
                 }
             };
@@ -1261,16 +1284,16 @@ __global__ __launch_bounds__(WG_MAXB) void k_chain_wg(const BoxDev* __restrict__
                     }
                     hb = bucket_of(cc[0], cc[1], cc[2]);
                 }
-                for (int i = b; i < NBK; i += WG_MAXB) bk_cnt[i] = 0u;
+                for (int i = b; i < NBK; i += NT) bk_cnt[i] = 0u;
                 __syncthreads();
                 if (act) slot = (int)atomicAdd(&bk_cnt[hb], 1u);
                 __syncthreads();
-                // exclusive prefix sum of the bucket counts, four per thread: a
+                // exclusive prefix sum of the bucket counts, NBK / NT per thread: a
                 // scan per wave, then the totals of the waves before
-                static_assert(NBK == 4 * WG_MAXB, "four buckets per thread");
-                uint32_t vb[4], vs = 0;
+                constexpr int BPT = NBK / NT;
+                uint32_t vb[BPT], vs = 0;
 #pragma unroll
-                for (int u = 0; u < 4; ++u) { vb[u] = bk_cnt[4 * b + u]; vs += vb[u]; }
+                for (int u = 0; u < BPT; ++u) { vb[u] = bk_cnt[BPT * b + u]; vs += vb[u]; }
                 uint32_t inc = vs;
                 for (int o = 1; o < 64; o <<= 1) {
                     const uint32_t t = __shfl_up(inc, o, 64);
@@ -1283,65 +1306,107 @@ __global__ __launch_bounds__(WG_MAXB) void k_chain_wg(const BoxDev* __restrict__
                     for (int w = 0; w < (b >> 6); ++w) base += bk_wsum[w];
                     uint32_t ex = base + inc - vs;
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) { bk_start[4 * b + u] = (uint16_t)ex; ex += vb[u]; }
-                    if (b == WG_MAXB - 1) bk_start[NBK] = (uint16_t)ex;
+                    for (int u = 0; u < BPT; ++u) { bk_start[BPT * b + u] = (uint16_t)ex; ex += vb[u]; }
+                    if (b == NT - 1) bk_start[NBK] = (uint16_t)ex;
                 }
                 __syncthreads();
                 if (act) {
                     const int sl = bk_start[hb] + slot;
-                    bk_bead[sl] = (uint16_t)b;
-                    bk_pos[3 * sl] = pb[0]; bk_pos[3 * sl + 1] = pb[1]; bk_pos[3 * sl + 2] = pb[2];
+                    bk_pos[sl] = make_float4(pb[0], pb[1], pb[2], __int_as_float(b));
                 }
                 __syncthreads();
                 if (act) {
                     const float Lf = (float)Ld;
                     const float rlf2 = (float)((rl + NL_FP32_MARGIN) * (rl + NL_FP32_MARGIN));
+                    // candidates in bucket slots k0..k1-1, seen with this
+                    // bead at (ox, oy, oz); two per pass (a row of three cells
+                    // holds about two beads), one load each
+                    auto visit = [&](int k0, int k1, float ox, float oy, float oz) __attribute__((always_inline)) {
+#pragma unroll 1
+                        for (int k = k0; k < k1; k += 2) {
+                            int jj[2];
+                            float r2[2];
+#pragma unroll
+                            for (int u = 0; u < 2; ++u) {
+                                const bool ok = k + u < k1;
+                                const float4 e = bk_pos[ok ? k + u : k];
+                                jj[u] = ok ? __float_as_int(e.w) : b;
+                                const float d0 = e.x - ox, d1 = e.y - oy, d2 = e.z - oz;
+                                r2[u] = jj[u] == b ? rlf2 : d0 * d0 + d1 * d1 + d2 * d2;
+                            }
+#pragma unroll
+                            for (int u = 0; u < 2; ++u)
+                                if (r2[u] < rlf2) {
+                                    if (cnt < nl_cap) nls[cnt * NT + b] = (uint16_t)jj[u];
+                                    ++cnt;
+                                }
+                        }
+                    };
+                    // a row of cells along x lies in consecutive buckets (cells
+                    // lo..hi; where it passes a multiple of 16, from there on in
+                    // the row's first buckets), but for its image across the
+                    // box edge: one or two visits per row instead of three
+                    const int lo = cc[0] > 0 ? cc[0] - 1 : 0, hi = cc[0] + 1 < nc ? cc[0] + 1 : nc - 1;
+                    const int cut = (hi & 15) < (lo & 15) ? hi & ~15 : hi + 1;   // first cell of the second part
+#pragma unroll 1
                     for (int dz = -1; dz <= 1; ++dz) {
                         const int rz = cc[2] + dz, qz = wrap_cell(rz, nc);
                         // the neighbour cell's image next to this bead
                         const float oz = pb[2] + (rz < 0 ? Lf : (rz >= nc ? -Lf : 0.f));
+#pragma unroll 1
                         for (int dy = -1; dy <= 1; ++dy) {
                             const int ry = cc[1] + dy, qy = wrap_cell(ry, nc);
                             const float oy = pb[1] + (ry < 0 ? Lf : (ry >= nc ? -Lf : 0.f));
-#pragma unroll 1
-                            for (int dx = -1; dx <= 1; ++dx) {
-                                const int rx = cc[0] + dx;
-                                const float ox = pb[0] + (rx < 0 ? Lf : (rx >= nc ? -Lf : 0.f));
-                                const int q = bucket_of(wrap_cell(rx, nc), qy, qz);
-                                const int k1 = bk_start[q + 1];
-                                // four candidates per pass: their loads overlap
-                                for (int k = bk_start[q]; k < k1; k += 4) {
-                                    int jj[4];
-                                    float r2[4];
-#pragma unroll
-                                    for (int u = 0; u < 4; ++u) {
-                                        const bool ok = k + u < k1;
-                                        const int sl = ok ? k + u : k;
-                                        jj[u] = ok ? (int)bk_bead[sl] : b;
-                                        const float d0 = bk_pos[3 * sl] - ox, d1 = bk_pos[3 * sl + 1] - oy,
-                                                    d2 = bk_pos[3 * sl + 2] - oz;
-                                        r2[u] = jj[u] == b ? rlf2 : d0 * d0 + d1 * d1 + d2 * d2;
-                                    }
-#pragma unroll
-                                    for (int u = 0; u < 4; ++u)
-                                        if (r2[u] < rlf2) {
-                                            if (cnt < nl_cap) nls[cnt * WG_MAXB + b] = (uint16_t)jj[u];
-                                            ++cnt;
-                                        }
-                                }
+                            const int row = bucket_of(0, qy, qz);
+                            visit(bk_start[row + (lo & 15)], bk_start[row + ((cut - 1) & 15) + 1], pb[0], oy, oz);
+                            if (cut <= hi) visit(bk_start[row], bk_start[row + (hi & 15) + 1], pb[0], oy, oz);
+                            if (cc[0] == 0) {
+                                const int q = row + ((nc - 1) & 15);
+                                visit(bk_start[q], bk_start[q + 1], pb[0] + Lf, oy, oz);
+                            } else if (cc[0] == nc - 1) {
+                                visit(bk_start[row], bk_start[row + 1], pb[0] - Lf, oy, oz);
                             }
                         }
                     }
-                    // ascending partner order, as a scan over all beads gives
-                    if (cnt <= nl_cap)
+                    // ascending partner order, as a scan over all beads gives,
+                    // and the list stored for the next step
+                    if (cnt <= SORT_REGS) {   // an odd-even merge network in registers
+                        uint32_t key[SORT_REGS];
+#pragma unroll
+                        for (int i = 0; i < SORT_REGS; ++i) key[i] = i < cnt ? (uint32_t)nls[i * NT + b] : 0xffffu;
+#pragma unroll
+                        for (int p = 1; p < SORT_REGS; p *= 2)
+#pragma unroll
+                            for (int k = p; k >= 1; k /= 2)
+#pragma unroll
+                                for (int j = k % p; j + k < SORT_REGS; j += 2 * k)
+#pragma unroll
+                                    for (int i = 0; i < k; ++i)
+                                        if (i + j + k < SORT_REGS && (i + j) / (2 * p) == (i + j + k) / (2 * p)) {
+                                            const uint32_t x1 = key[i + j], x2 = key[i + j + k];
+                                            key[i + j] = min(x1, x2);
+                                            key[i + j + k] = max(x1, x2);
+                                        }
+#pragma unroll
+                        for (int i = 0; i < SORT_REGS; ++i)
+                            if (i < cnt) nls[i * NT + b] = (uint16_t)key[i];
+                        uint4* row = (uint4*)(ca.nl_idx + g * NL_SLOTS);
+#pragma unroll
+                        for (int q = 0; q < SORT_REGS / 8; ++q)
+                            if (cnt > 8 * q)
+                                row[q] = make_uint4(key[8 * q] | key[8 * q + 1] << 16, key[8 * q + 2] | key[8 * q + 3] << 16,
+                                                    key[8 * q + 4] | key[8 * q + 5] << 16,
+                                                    key[8 * q + 6] | key[8 * q + 7] << 16);
+                        stored = true;
+                    } else if (cnt <= nl_cap)
                         for (int i = 1; i < cnt; ++i) {
-                            const uint16_t key = nls[i * WG_MAXB + b];
+                            const uint16_t key = nls[i * NT + b];
                             int k = i - 1;
-                            while (k >= 0 && nls[k * WG_MAXB + b] > key) {
-                                nls[(k + 1) * WG_MAXB + b] = nls[k * WG_MAXB + b];
+                            while (k >= 0 && nls[k * NT + b] > key) {
+                                nls[(k + 1) * NT + b] = nls[k * NT + b];
                                 --k;
                             }
-                            nls[(k + 1) * WG_MAXB + b] = key;
+                            nls[(k + 1) * NT + b] = key;
                         }
                 }
             } else if (act) {   // boxes under three list radii across: every bead
@@ -1350,7 +1415,8 @@ __global__ __launch_bounds__(WG_MAXB) void k_chain_wg(const BoxDev* __restrict__
             }
             if (act) {
                 const int kept = cnt < nl_cap ? cnt : nl_cap;
-                for (int k = 0; k < kept; ++k) ca.nl_idx[g * ca.nl_cap + k] = nls[k * WG_MAXB + b];
+                if (!stored)
+                    for (int k = 0; k < kept; ++k) ca.nl_idx[g * ca.nl_cap + k] = nls[k * NT + b];
                 nl_n = cnt > nl_cap ? -1 : cnt;   // -1: overflow, the full loop is used
                 ca.nl_cnt[g] = nl_n;
 #pragma unroll
@@ -1365,7 +1431,7 @@ __global__ __launch_bounds__(WG_MAXB) void k_chain_wg(const BoxDev* __restrict__
             if (i0 != cb0 || i1 != cb1 || i2 != cb2) {
                 cb0 = i0; cb1 = i1; cb2 = i2;
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
+                for (int k = 0; k < (list_touched ? 8 : 0); ++k) {
                     const uint32_t node = node_of(cb0 + (k & 1), cb1 + ((k >> 1) & 1), cb2 + ((k >> 2) & 1), L);
                     if (tcnt < ca.touch_cap) ca.touched[g * ca.touch_cap + tcnt] = node;
                     else hbits |= H_TABLE;
@@ -1378,7 +1444,14 @@ __global__ __launch_bounds__(WG_MAXB) void k_chain_wg(const BoxDev* __restrict__
                 d0 = d0 < 0 ? d0 + L : (d0 >= L ? d0 - L : d0);
                 d1 = d1 < 0 ? d1 + L : (d1 >= L ? d1 - L : d1);
                 d2 = d2 < 0 ? d2 + L : (d2 >= L ? d2 - L : d2);
-                if (d0 <= 1 && d1 <= 1 && d2 <= 1) {
+                if (bx.dense) {   // every node's velocity
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        const R* fu = field + 3 * (bx.field_off + node_of(cb0 + (k & 1), cb1 + ((k >> 1) & 1),
+                                                                          cb2 + ((k >> 2) & 1), L));
+                        cu[k][0] = fu[0]; cu[k][1] = fu[1]; cu[k][2] = fu[2];
+                    }
+                } else if (d0 <= 1 && d1 <= 1 && d2 <= 1) {
                     const R* tb = near_u + g * NEAR * 3;
 #pragma unroll
                     for (int k = 0; k < 8; ++k) {
@@ -1392,7 +1465,7 @@ __global__ __launch_bounds__(WG_MAXB) void k_chain_wg(const BoxDev* __restrict__
             }
             double F[3] = {0, 0, 0};
             if (nl_n >= 0) {
-                auto jof = [&](int k) { return (int)nls[k * WG_MAXB + b]; };
+                auto jof = [&](int k) { return (int)nls[k * NT + b]; };
                 for (int k = 0; k < nl_n; k += 4) wca_add4(x, xs, jof, k, nl_n, 1, b, Ld, iL, bx.rc2, bx.sigsq, eps24, F);
             } else {
                 auto jof = [](int k) { return k; };
@@ -1422,7 +1495,7 @@ __global__ __launch_bounds__(WG_MAXB) void k_chain_wg(const BoxDev* __restrict__
             double* r = rec + ((uint64_t)s * ca.total_beads + g) * REC;
             r[0] = fr[0]; r[1] = fr[1]; r[2] = fr[2];
             r[3] = fcl[0]; r[4] = fcl[1]; r[5] = fcl[2];
-            r[6] = (double)node_of(cb0, cb1, cb2, L);
+            r[6] = pack_cell(cb0, cb1, cb2);
             if (s + 1 == bx.substeps) {
 #pragma unroll
                 for (int c = 0; c < 3; ++c) ca.fc[3 * g + c] = fcl[c];
@@ -1430,7 +1503,7 @@ __global__ __launch_bounds__(WG_MAXB) void k_chain_wg(const BoxDev* __restrict__
         }
     }
     if (act) {
-        ca.touched_cnt[g] = tcnt < ca.touch_cap ? tcnt : ca.touch_cap;
+        if (list_touched) ca.touched_cnt[g] = tcnt < ca.touch_cap ? tcnt : ca.touch_cap;
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             ca.x[3 * g + c] = x[c]; ca.v[3 * g + c] = v[c]; ca.f[3 * g + c] = f[c];
@@ -1470,16 +1543,53 @@ __device__ __forceinline__ uint32_t list_overflow(const ChainArgs& ca, const Box
     return 0u;
 }
 
+// The deferred tiles of a step as a list, built after the coupling on the
+// chain's stream: thread (bead, table node) of a sparse box claims the node's
+// tile for this step; each wave appends its new tiles with one atomic.
+__device__ __forceinline__ void list_deferred(const BoxDev& bx, const ChainArgs& ca, const int4* __restrict__ near_c,
+                                              Ctrl* __restrict__ ctrl, uint32_t s_off, int tid)
+{
+    const uint32_t stamp = defer_stamp(ctrl->step + s_off);
+    bool win = false;
+    uint32_t seg = 0;
+    if (tid < bx.N * NEAR) {
+        const int b = tid / NEAR, q = tid - b * NEAR;
+        const int4 nc = near_c[bx.bead_off + (uint64_t)b];
+        const uint32_t node = node_of(nc.x - 1 + q % 3, nc.y - 1 + (q / 3) % 3, nc.z - 1 + q / 9, bx.L);
+        seg = dseg_of(bx, node);
+        win = ca.dclaim[seg] != stamp && atomicExch(&ca.dclaim[seg], stamp) != stamp;
+    }
+    const unsigned long long m = __ballot(win);
+    if (m == 0ull) return;
+    const int lane = (int)(threadIdx.x & 63u);
+    const int lead = __ffsll((long long)m) - 1;
+    uint32_t base = 0;
+    if (lane == lead) base = atomicAdd(&ctrl->defer_cnt, (uint32_t)__popcll(m));
+    base = __shfl(base, lead);
+    if (win) {
+        const uint32_t k = base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+        if (k < ca.defer_cap) ca.defer_list[k] = seg;
+        else atomicOr(&ctrl->health, H_TABLE);
+    }
+}
+
 // node impulses from the substep records: thread (bead, corner k) accumulates
 // -w_k (F_fric + F_rand) dt over the substeps that share a stencil, in MD
 // units and in substep order, and hands each stencil's sum over when the
 // stencil changes and after the last substep (lattice units, fixed point)
+// The workgroups from n_spread on build the list of the step's deferred
+// tiles, which needs nothing of the impulses.
 __global__ __launch_bounds__(256) void k_spread(const BoxDev* __restrict__ boxes, const int32_t* __restrict__ list,
                                                 ChainArgs ca, const double* __restrict__ rec,
-                                                Ctrl* __restrict__ ctrl, uint32_t s_off)
+                                                const int4* __restrict__ near_c, Ctrl* __restrict__ ctrl,
+                                                uint32_t s_off, uint32_t n_spread)
 {
     const BoxDev& bx = boxes[list[blockIdx.y]];
-    if (bx.dense) return;   // binned and gathered instead (k_bin_runs, k_gather_imp)
+    if (bx.dense) return;   // k_dense_impulse
+    if (blockIdx.x >= n_spread) {
+        list_deferred(bx, ca, near_c, ctrl, s_off, (int)((blockIdx.x - n_spread) * blockDim.x + threadIdx.x));
+        return;
+    }
     const int N = bx.N, L = bx.L;
     const int tid = (int)(blockIdx.x * blockDim.x + threadIdx.x);
     if (tid >= N * 8) return;
@@ -1493,10 +1603,8 @@ __global__ __launch_bounds__(256) void k_spread(const BoxDev* __restrict__ boxes
     uint32_t cur = 0xffffffffu;
     for (int s = 0; s < bx.substeps; ++s) {
         const double* r = rec + ((uint64_t)s * ca.total_beads + g) * REC;
-        const uint32_t base = (uint32_t)r[6];
-        const uint32_t bz = base / ((uint32_t)L * (uint32_t)L), rem = base - bz * (uint32_t)L * (uint32_t)L;
-        const uint32_t by = rem / (uint32_t)L, bxn = rem - by * (uint32_t)L;
-        const uint32_t node = node_of((int)bxn + (k & 1), (int)by + ((k >> 1) & 1), (int)bz + ((k >> 2) & 1), L);
+        const Cell cl = cell_of_packed((unsigned long long)__double_as_longlong(r[6]));
+        const uint32_t node = node_of(cl.x + (k & 1), cl.y + ((k >> 1) & 1), cl.z + ((k >> 2) & 1), L);
         if (node != cur) {
             if (cur != 0xffffffffu) {
 #pragma unroll
@@ -1528,162 +1636,101 @@ __global__ __launch_bounds__(256) void k_spread(const BoxDev* __restrict__ boxes
     if (hb) atomicOr(&ctrl->health, hb);
 }
 
-// Dense boxes hand their impulses over without atomics.  A stencil run is a
-// maximal range of substeps in which a bead keeps one base node; k_spread
-// accumulates each (run, corner) in FP64 and rounds it to fixed point once.
-// Here k_bin_runs gives every run a slot, the slots sorted by base node
-// (counting sort in LDS, one workgroup per box); k_run_impulse, one thread
-// per (bead, corner) like k_spread, stores each (run, corner) value in its
-// run's slot; k_gather_imp gives each node the sum over the runs whose
-// stencil holds it.  The fixed-point sums do not depend on order, so the
-// field equals the one the atomics would build.
-constexpr uint32_t DENSE_MAXV = 32768;   // a dense box has at most 32 N <= 32768 nodes
-__global__ __launch_bounds__(WG_MAXB) void k_bin_runs(const BoxDev* __restrict__ boxes,
-                                                      const int32_t* __restrict__ list, ChainArgs ca,
-                                                      const double* __restrict__ rec,
-                                                      uint32_t* __restrict__ bin_start,
-                                                      uint32_t* __restrict__ slot_of)
+// Dense boxes hand their impulses over in LDS: grid (node ranges of the
+// largest box, list), one workgroup holds the fixed-point sums of DENSE_NODES
+// consecutive nodes of a box (64 KB: two workgroups per CU), adds every
+// (bead, corner) impulse that falls into them, accumulated over the substeps
+// that share a stencil and rounded once as in k_spread, and writes the range
+// out.  Integer sums do not depend on order.  Bounds: the latency of the
+// records' reads (each range reads every bead's base node) and of the LDS
+// atomics.  A counting sort of the stencils by node, their values and a
+// gather per node, three kernels, took 31 us on 64 boxes of 20^3 with 1024
+// beads; this takes 15.
+constexpr uint32_t DENSE_NODES = 2720;
+__global__ __launch_bounds__(1024) void k_dense_impulse(const BoxDev* __restrict__ boxes,
+                                                        const int32_t* __restrict__ list, ChainArgs ca,
+                                                        const double* __restrict__ rec, Ctrl* __restrict__ ctrl)
 {
-    __shared__ uint32_t cnt[DENSE_MAXV];        // runs per base node, then the placement cursor
-    __shared__ uint32_t wsum[WG_MAXB / 64];
-    const BoxDev& bx = boxes[list[blockIdx.x]];
+    __shared__ unsigned long long sum[3 * DENSE_NODES];
+    const BoxDev& bx = boxes[list[blockIdx.y]];
     if (!bx.dense) return;
     const int N = bx.N, S = bx.substeps, L = bx.L;
-    const uint32_t V = (uint32_t)L * L * L;
-    const int b = (int)threadIdx.x;
-    const bool act = b < N;
-    const uint64_t g = bx.bead_off + (uint64_t)(act ? b : 0);
-    auto base_at = [&](int s) {
-        return (uint32_t)rec[((uint64_t)s * ca.total_beads + g) * REC + 6];
-    };
-    for (uint32_t i = (uint32_t)b; i < V; i += WG_MAXB) cnt[i] = 0u;
+    const uint32_t V = (uint32_t)L * L * L, r0 = blockIdx.x * DENSE_NODES;
+    if (r0 >= V) return;
+    const uint32_t nr = min(DENSE_NODES, V - r0);
+    for (uint32_t i = threadIdx.x; i < 3 * nr; i += 1024) sum[i] = 0ull;
     __syncthreads();
-    if (act) {
-        uint32_t cur = 0xffffffffu;
-        for (int s = 0; s < S; ++s) {
-            const uint32_t base = base_at(s);
-            if (base != cur) { atomicAdd(&cnt[base], 1u); cur = base; }
-        }
-    }
-    __syncthreads();
-    // exclusive prefix sum over the V counts: a chunk of C per thread, a
-    // scan per wave of the chunk totals, then the totals of the waves before
-    const uint32_t C = (V + WG_MAXB - 1) / WG_MAXB;
-    const uint32_t i0 = (uint32_t)b * C < V ? (uint32_t)b * C : V, i1 = i0 + C < V ? i0 + C : V;
-    uint32_t tot = 0;
-    for (uint32_t i = i0; i < i1; ++i) tot += cnt[i];
-    uint32_t inc = tot;
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t t = __shfl_up(inc, o, 64);
-        if ((b & 63) >= o) inc += t;
-    }
-    if ((b & 63) == 63) wsum[b >> 6] = inc;
-    __syncthreads();
-    uint32_t run = inc - tot;
-    for (int w = 0; w < (b >> 6); ++w) run += wsum[w];
-    uint32_t* bs = bin_start + bx.bin_off;
-    for (uint32_t i = i0; i < i1; ++i) {
-        const uint32_t c = cnt[i];
-        bs[i] = run;
-        cnt[i] = run;
-        run += c;
-    }
-    if (b == WG_MAXB - 1) bs[V] = run;
-    __syncthreads();
-    if (act) {
-        // slot of the j-th run of bead b
-        uint32_t cur = 0xffffffffu;
-        int j = 0;
-        for (int s = 0; s < S; ++s) {
-            const uint32_t base = base_at(s);
-            if (base != cur) {
-                slot_of[bx.item_off + (uint64_t)b * S + j] = atomicAdd(&cnt[base], 1u);
-                ++j;
-                cur = base;
-            }
-        }
-    }
-}
-
-// one thread per (bead, corner): k_spread's accumulation, stored in the
-// run's slot instead of added to the field
-__global__ __launch_bounds__(256) void k_run_impulse(const BoxDev* __restrict__ boxes,
-                                                     const int32_t* __restrict__ list, ChainArgs ca,
-                                                     const double* __restrict__ rec,
-                                                     const uint32_t* __restrict__ slot_of,
-                                                     unsigned long long* __restrict__ runimp,
-                                                     Ctrl* __restrict__ ctrl)
-{
-    const BoxDev& bx = boxes[list[blockIdx.y]];
-    if (!bx.dense) return;
-    const int N = bx.N, S = bx.substeps;
-    const int tid = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (tid >= N * 8) return;
-    const int b = tid >> 3, k = tid & 7;
-    const uint64_t g = bx.bead_off + (uint64_t)b;
     const double dt = bx.dt, tau = bx.tau_lb;
     uint32_t hb = 0;
-    double acc[3] = {0, 0, 0};
-    uint32_t cur = 0xffffffffu;
-    int j = 0;
-    auto store = [&]() {
-        unsigned long long* o = runimp + (bx.item_off + slot_of[bx.item_off + (uint64_t)b * S + j]) * 24 + 3 * k;
+    // four (bead, corner) items at a time, their records' loads in flight
+    // together; k is the same for all of a thread's items
+    const int k = (int)threadIdx.x & 7;
+    for (int e0 = (int)threadIdx.x; e0 < 8 * N; e0 += 4 * 1024) {
+        double acc[4][3];
+        unsigned long long cur[4];   // base cell of the stencil
+        uint32_t at[4];              // its corner's node in the range (nr: outside)
+        uint64_t g[4];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            double q = acc[c] * tau;
-            if (!(fabs(q) < IMP_MAX)) { hb |= H_FIXED; q = 0.0; }
-            o[c] = (unsigned long long)(long long)llrint(q * IMP_SCALE);
+        for (int u = 0; u < 4; ++u) {
+            const int e = e0 + 1024 * u;
+            g[u] = bx.bead_off + (uint64_t)((e < 8 * N ? e : e0) >> 3);
+            cur[u] = ~0ull;
+            at[u] = nr;
+            acc[u][0] = acc[u][1] = acc[u][2] = 0.0;
         }
-    };
-    for (int s = 0; s < S; ++s) {
-        const double* r = rec + ((uint64_t)s * ca.total_beads + g) * REC;
-        const uint32_t base = (uint32_t)r[6];
-        if (base != cur) {
-            if (cur != 0xffffffffu) { store(); ++j; }
-            cur = base;
-            acc[0] = acc[1] = acc[2] = 0.0;
+        auto hand_over = [&](uint32_t i, const double q3[3]) __attribute__((always_inline)) {
+            if (i >= nr) return;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                double q = q3[c] * tau;
+                if (!(fabs(q) < IMP_MAX)) { hb |= H_FIXED; q = 0.0; }
+                atomicAdd(&sum[3 * i + c], (unsigned long long)(long long)llrint(q * IMP_SCALE));
+            }
+        };
+        for (int s = 0; s < S; ++s) {
+            // the base nodes first: the beads of a wavefront are neighbours
+            // on a chain, so it often has nothing in the range
+            const double* p[4];
+            double r[4][6], bd[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                p[u] = rec + ((uint64_t)s * ca.total_beads + g[u]) * REC;
+                bd[u] = p[u][6];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const unsigned long long cell = (unsigned long long)__double_as_longlong(bd[u]);
+                if (cell != cur[u]) {
+                    hand_over(at[u], acc[u]);
+                    cur[u] = cell;
+                    acc[u][0] = acc[u][1] = acc[u][2] = 0.0;
+                    const Cell cl = cell_of_packed(cell);
+                    const uint32_t node = node_of(cl.x + (k & 1), cl.y + ((k >> 1) & 1), cl.z + (k >> 2), L);
+                    at[u] = node - r0 < nr && e0 + 1024 * u < 8 * N ? node - r0 : nr;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (at[u] < nr) {
+#pragma unroll
+                    for (int c = 0; c < 6; ++c) r[u][c] = p[u][c];
+                }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (at[u] < nr) {
+                    const double wk = ((k & 1) ? r[u][0] : 1.0 - r[u][0]) * (((k >> 1) & 1) ? r[u][1] : 1.0 - r[u][1]) *
+                                      (((k >> 2) & 1) ? r[u][2] : 1.0 - r[u][2]);
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) acc[u][c] -= wk * r[u][3 + c] * dt;
+                }
         }
-        const double wk = ((k & 1) ? r[0] : 1.0 - r[0]) * (((k >> 1) & 1) ? r[1] : 1.0 - r[1]) *
-                          (((k >> 2) & 1) ? r[2] : 1.0 - r[2]);
-        acc[0] -= wk * r[3] * dt;
-        acc[1] -= wk * r[4] * dt;
-        acc[2] -= wk * r[5] * dt;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) hand_over(at[u], acc[u]);
     }
-    if (cur != 0xffffffffu) store();
+    __syncthreads();
+    unsigned long long* imp = ca.imp + 3 * (bx.node_off + r0);
+    for (uint32_t i = threadIdx.x; i < 3 * nr; i += 1024) imp[i] = sum[i];
     if (hb) atomicOr(&ctrl->health, hb);
-}
-
-__global__ __launch_bounds__(256) void k_gather_imp(const BoxDev* __restrict__ boxes,
-                                                    const int32_t* __restrict__ list, ChainArgs ca,
-                                                    const uint32_t* __restrict__ bin_start,
-                                                    const unsigned long long* __restrict__ runimp)
-{
-    const BoxDev& bx = boxes[list[blockIdx.y]];
-    if (!bx.dense) return;
-    const int L = bx.L;
-    const uint32_t V = (uint32_t)L * L * L;
-    const uint32_t r = blockIdx.x * 256u + threadIdx.x;
-    if (r >= V) return;
-    const int x = (int)(r % (uint32_t)L), y = (int)((r / (uint32_t)L) % (uint32_t)L), z = (int)(r / ((uint32_t)L * L));
-    const uint32_t* bs = bin_start + bx.bin_off;
-    // the bins of the 8 base nodes whose corner k is this node: all bounds
-    // are loaded before any is used
-    uint32_t e0[8], e1[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const uint32_t base = node_of(x - (k & 1), y - ((k >> 1) & 1), z - ((k >> 2) & 1), L);
-        e0[k] = bs[base];
-        e1[k] = bs[base + 1];
-    }
-    unsigned long long sum[3] = {0ull, 0ull, 0ull};
-#pragma unroll
-    for (int k = 0; k < 8; ++k)
-        for (uint32_t e = e0[k]; e < e1[k]; ++e) {
-            const unsigned long long* q = runimp + (bx.item_off + e) * 24 + 3 * k;
-            sum[0] += q[0]; sum[1] += q[1]; sum[2] += q[2];
-        }
-    unsigned long long* dst = ca.imp + 3 * (bx.node_off + r);
-    dst[0] = sum[0]; dst[1] = sum[1]; dst[2] = sum[2];
 }
 
 // ---------------------------------------------------------------- fixup
@@ -2069,41 +2116,6 @@ __global__ __launch_bounds__(256) void k_collide_forced(const BoxDev* __restrict
 {
     collide_forced_tile<R>(boxes, ccs, tile_box, fixed_box, tile0 + blockIdx.x, imp, A, B, ctrl,
                            ctrl->step + s_off, threadIdx.x);
-}
-
-// The deferred tiles of a step as a list, built after the coupling on the
-// chain's stream: thread (bead, table node) of a sparse box claims the node's
-// tile for this step; each wave appends its new tiles with one atomic.
-__global__ __launch_bounds__(256) void k_defer_list(const BoxDev* __restrict__ boxes,
-                                                    const int32_t* __restrict__ list, ChainArgs ca,
-                                                    const int4* __restrict__ near_c, Ctrl* __restrict__ ctrl,
-                                                    uint32_t s_off)
-{
-    const BoxDev& bx = boxes[list[blockIdx.y]];
-    if (bx.dense) return;
-    const int tid = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    const uint32_t stamp = defer_stamp(ctrl->step + s_off);
-    bool win = false;
-    uint32_t seg = 0;
-    if (tid < bx.N * NEAR) {
-        const int b = tid / NEAR, q = tid - b * NEAR;
-        const int4 nc = near_c[bx.bead_off + (uint64_t)b];
-        const uint32_t node = node_of(nc.x - 1 + q % 3, nc.y - 1 + (q / 3) % 3, nc.z - 1 + q / 9, bx.L);
-        seg = dseg_of(bx, node);
-        win = ca.dclaim[seg] != stamp && atomicExch(&ca.dclaim[seg], stamp) != stamp;
-    }
-    const unsigned long long m = __ballot(win);
-    if (m == 0ull) return;
-    const int lane = (int)(threadIdx.x & 63u);
-    const int lead = __ffsll((long long)m) - 1;
-    uint32_t base = 0;
-    if (lane == lead) base = atomicAdd(&ctrl->defer_cnt, (uint32_t)__popcll(m));
-    base = __shfl(base, lead);
-    if (win) {
-        const uint32_t k = base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-        if (k < ca.defer_cap) ca.defer_list[k] = seg;
-        else atomicOr(&ctrl->health, H_TABLE);
-    }
 }
 
 // the deferred tiles of a step, after its coupling stage, beside the plain
@@ -2620,9 +2632,9 @@ hipError_t launch_couple_big(const LaunchCtx& c, const void* A, const int32_t* l
     if (c.dense_max_tiles)
         hipLaunchKernelGGL(k_node_field<R>, dim3(c.dense_max_tiles, n_list), dim3(256), 0, c.stream, c.boxes, list,
                            (const R*)A, (R*)c.field);
-    if (!wait_head)
+    if (!wait_head && c.big_sparse)   // a dense box's beads read the node field
         hipLaunchKernelGGL(k_near_nodes<R>, dim3((max_n * NEAR + 255) / 256, n_list), dim3(256), 0, c.stream,
-                           c.boxes, list, (R*)A, ca, (R*)c.near_u, c.near_c, (const R*)c.field, c.ctrl, s_off,
+                           c.boxes, list, (R*)A, ca, (R*)c.near_u, c.near_c, c.ctrl, s_off,
                            (const CollideConst<R>*)c.ccs, c.bead_box, c.claim, (const R*)Aprev,
                            n_list == 1 && single_box >= 0 ? single_box : -1,
                            n_list == 1 && single_box >= 0 ? c.boxes_host[single_box] : BoxDev{}, zero_head);
@@ -2630,22 +2642,25 @@ hipError_t launch_couple_big(const LaunchCtx& c, const void* A, const int32_t* l
         const hipError_t e = hipEventRecord(after_table, c.stream);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_chain_wg<R>, dim3(n_list), dim3(WG_MAXB), 0, c.stream, c.boxes, list, (const R*)A, ca,
-                       (const R*)c.near_u, (const int4*)c.near_c, c.sub_rec, c.ctrl, s_off, c.bead_box,
+    if (max_n <= 512)
+        hipLaunchKernelGGL((k_chain_wg<R, 512>), dim3(n_list), dim3(512), 0, c.stream, c.boxes, list, (const R*)A, ca,
+                       (const R*)c.near_u, (const int4*)c.near_c, (const R*)c.field, c.sub_rec, c.ctrl, s_off,
+                       c.bead_box,
                        (Aprev || wait_head) ? 1 : 0, wait_head, stamp_next);
-    if (c.big_sparse)
-        hipLaunchKernelGGL(k_spread, dim3((max_n * 8 + 255) / 256, n_list), dim3(256), 0, c.stream, c.boxes, list,
-                           ca, (const double*)c.sub_rec, c.ctrl, s_off);
-    if (c.defer_on && c.big_sparse)
-        hipLaunchKernelGGL(k_defer_list, dim3((max_n * NEAR + 255) / 256, n_list), dim3(256), 0, c.stream, c.boxes,
-                           list, ca, (const int4*)c.near_c, c.ctrl, s_off);
+    else
+        hipLaunchKernelGGL((k_chain_wg<R, WG_MAXB>), dim3(n_list), dim3(WG_MAXB), 0, c.stream, c.boxes, list, (const R*)A, ca,
+                       (const R*)c.near_u, (const int4*)c.near_c, (const R*)c.field, c.sub_rec, c.ctrl, s_off,
+                       c.bead_box,
+                       (Aprev || wait_head) ? 1 : 0, wait_head, stamp_next);
+    if (c.big_sparse) {
+        const uint32_t n_spread = (uint32_t)(max_n * 8 + 255) / 256;
+        const uint32_t n_defer = c.defer_on ? (uint32_t)(max_n * NEAR + 255) / 256 : 0u;
+        hipLaunchKernelGGL(k_spread, dim3(n_spread + n_defer, n_list), dim3(256), 0, c.stream, c.boxes, list, ca,
+                           (const double*)c.sub_rec, (const int4*)c.near_c, c.ctrl, s_off, n_spread);
+    }
     if (c.dense_max_tiles) {
-        hipLaunchKernelGGL(k_bin_runs, dim3(n_list), dim3(WG_MAXB), 0, c.stream, c.boxes, list, ca,
-                           (const double*)c.sub_rec, c.bin_start, c.slot_of);
-        hipLaunchKernelGGL(k_run_impulse, dim3((max_n * 8 + 255) / 256, n_list), dim3(256), 0, c.stream, c.boxes,
-                           list, ca, (const double*)c.sub_rec, (const uint32_t*)c.slot_of, c.runimp, c.ctrl);
-        hipLaunchKernelGGL(k_gather_imp, dim3(c.dense_max_tiles, n_list), dim3(256), 0, c.stream, c.boxes, list, ca,
-                           (const uint32_t*)c.bin_start, (const unsigned long long*)c.runimp);
+        hipLaunchKernelGGL(k_dense_impulse, dim3((c.dense_max_tiles * 256 + DENSE_NODES - 1) / DENSE_NODES, n_list),
+                           dim3(1024), 0, c.stream, c.boxes, list, ca, (const double*)c.sub_rec, c.ctrl);
     }
     return hipGetLastError();
 }

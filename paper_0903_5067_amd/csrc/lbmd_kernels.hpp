@@ -57,9 +57,6 @@ struct LaunchCtx {
     void* field;                   // dense boxes: node velocities (MD units, storage precision) [nodes][3]
     uint32_t dense_max_tiles;      // collide tiles of the largest dense box (0: none)
     int big_sparse;                // boxes on the 1024-thread path that are not dense (k_spread's boxes)
-    uint32_t* bin_start;           // dense boxes: per base node, first binned stencil run [L^3 + 1]
-    unsigned long long* runimp;    // dense boxes: per stencil run, the fixed-point impulse to its 8 corners x 3
-    uint32_t* slot_of;             // dense boxes: per bead and run, the run's slot [N x substeps]
     // deferred segments: in a batched step the 64-node segments (wavefronts
     // of the collide tiles) that hold a node of any table of a sparse box's
     // large chain are left out of the plain collide and collided with their

@@ -71,8 +71,6 @@ struct Layout {
     std::vector<uint8_t> dense;                       // per box: collide after the coupling, no fix-up
     std::vector<uint64_t> field_off;                  // per box: first node in the velocity field (dense boxes)
     uint64_t field_nodes = 0;                         // nodes of all dense boxes
-    std::vector<uint64_t> bin_off, item_off;          // per box: its run bins and binned runs (dense boxes)
-    uint64_t bin_entries = 0, item_entries = 0;
     uint32_t dense_max_tiles = 0;                     // collide tiles of the largest dense box
     uint64_t tiles_sparse = 0, beads_sparse = 0;      // collide tiles (first in tile order) and beads of the other boxes
     uint64_t pop_elems = 0, total_tiles = 0, total_beads = 0, total_nodes = 0;
@@ -82,7 +80,7 @@ struct Layout {
     size_t sc_ctrl = 0, sc_boxes = 0, sc_ccs = 0, sc_tilebox = 0, sc_couple = 0, sc_imp = 0, sc_claim = 0,
            sc_touched = 0, sc_tcnt = 0, sc_beadbox = 0, sc_nlcnt = 0, sc_nlidx = 0, sc_nlx0 = 0,
            sc_part = 0, sc_mid = 0, sc_obs = 0, sc_vhist = 0, sc_nlreb = 0, sc_biglist = 0, sc_alllist = 0,
-           sc_nearu = 0, sc_nearc = 0, sc_subrec = 0, sc_field = 0, sc_binstart = 0, sc_items = 0, sc_slotof = 0,
+           sc_nearu = 0, sc_nearc = 0, sc_subrec = 0, sc_field = 0,
            sc_defer = 0, sc_dclaim = 0, sc_dlist = 0, sc_ovf = 0, sc_ovm = 0, sc_nmask[2] = {0, 0}, sc_nlist[2] = {0, 0},
            sc_steprec = 0, scratch_bytes = 0;
     uint64_t beads_big_sparse = 0;                    // beads of the chains above BIG_CHAIN in the other boxes
@@ -147,12 +145,8 @@ Layout make_layout(const lb_box_desc* b, int32_t n, int32_t prec, int32_t hist)
         // fix-up would cost more than colliding the box after the coupling
         Lo.dense.push_back(b[i].n_beads > BIG_CHAIN && 32 * (uint64_t)b[i].n_beads >= V ? 1 : 0);
         Lo.field_off.push_back(Lo.field_nodes);
-        Lo.bin_off.push_back(Lo.bin_entries);
-        Lo.item_off.push_back(Lo.item_entries);
         if (Lo.dense.back()) {
             Lo.field_nodes += V;
-            Lo.bin_entries += V + 1;
-            Lo.item_entries += (uint64_t)b[i].n_beads * (uint64_t)b[i].md_substeps;
             Lo.dense_max_tiles = std::max(Lo.dense_max_tiles, (uint32_t)((V + 255) / 256));
         } else {
             Lo.beads_sparse += (uint64_t)b[i].n_beads;
@@ -244,9 +238,6 @@ Layout make_layout(const lb_box_desc* b, int32_t n, int32_t prec, int32_t hist)
         Lo.sc_nearc = o; o = align256(o + nbig * 4 * sizeof(int32_t));
         Lo.sc_subrec = o; o = align256(o + (uint64_t)std::max(Lo.big_max_sub, 1) * nbig * 8 * sizeof(double));
         Lo.sc_field = o; o = align256(o + std::max<uint64_t>(Lo.field_nodes, 1) * 3 * Lo.esz);
-        Lo.sc_binstart = o; o = align256(o + std::max<uint64_t>(Lo.bin_entries, 1) * sizeof(uint32_t));
-        Lo.sc_items = o; o = align256(o + std::max<uint64_t>(Lo.item_entries, 1) * 24 * sizeof(unsigned long long));
-        Lo.sc_slotof = o; o = align256(o + std::max<uint64_t>(Lo.item_entries, 1) * sizeof(uint32_t));
         // deferred segments (64 nodes, four per collide tile): three step
         // stamps per segment (deferred in the steps of either parity, listed
         // in); a segment is listed once, and a bead's table spans at most
@@ -588,13 +579,6 @@ lb_status enqueue_one_run(lb_handle* h, int from, uint32_t n)
     return enqueue_one_end(h, h->ctx, h->pop(pl), h->pop(1 - pl), n);
 }
 
-// Layouts that put a step's kernels on both streams are launched directly,
-// never from a graph: only steps that keep to one stream are recorded.
-bool linear_steps(const lb_handle* h)
-{
-    return !h->batched || one_kernel_steps(h) || h->lo.total_beads == 0 || h->lo.tiles_sparse == 0;
-}
-
 // FP32 runs whose chains are all large (every box with beads holds a chain
 // above BIG_CHAIN beads, none of them dense) take the collide that carries
 // its own node tables from the second step on.  (In FP64 the node-table code
@@ -682,6 +666,19 @@ lb_status enqueue_fused_run(lb_handle* h, int from, uint32_t n, uint32_t advance
     return LB_OK;
 }
 
+// Which steps a graph records: those that keep to one stream, and the runs of
+// enqueue_headed_run (a replay places their two streams' kernels on queues of
+// its own; two streams of a program that holds many may share one: the 256^3
+// box in FP64 took 962 us/step launched directly against 912 replayed).  The
+// other steps that put kernels on both streams are launched directly:
+// replaying such a graph again while it ran has ended in a segmentation fault
+// of the host process.
+bool graph_steps_apply(const lb_handle* h)
+{
+    if (fused_steps(h)) return false;
+    return !h->batched || one_kernel_steps(h) || headed_steps(h) || h->lo.total_beads == 0 || h->lo.tiles_sparse == 0;
+}
+
 // n coupled steps from buffer `from`, step offsets 0..n-1, then the device
 // step counter advanced by n
 lb_status enqueue_steps(lb_handle* h, int from, uint32_t n)
@@ -732,7 +729,7 @@ lb_status build_graph(lb_handle* h, int parity)
 lb_status prepare_graphs(lb_handle* h)
 {
     drop_graphs(h);
-    if (h->graph_steps <= 0 || !linear_steps(h)) return LB_OK;
+    if (h->graph_steps <= 0 || !graph_steps_apply(h)) return LB_OK;
     for (int p = 0; p < 2; ++p) {
         lb_status s = build_graph(h, p);
         if (s != LB_OK) return s;
@@ -814,8 +811,6 @@ lb_status lb_init(const lb_box_desc* boxes, int32_t n_boxes, int32_t precision, 
         b.dense = lo.dense[i];
         b.stat_off = lo.stat_off[i];
         b.field_off = lo.field_off[i];
-        b.bin_off = lo.bin_off[i];
-        b.item_off = lo.item_off[i];
         b.rho0 = d.rho0; b.gam_b = 1 - d.omega_bulk; b.gam_s = 1 - d.omega_shear; b.gam_g = 1 - d.omega_ghost;
         b.mu = 3.0 * d.kT * d.tau_lb * d.tau_lb;
         b.tau_lb = d.tau_lb; b.dt = d.md_dt; b.mass = d.bead_mass; b.zeta = d.zeta; b.k_fene = d.k_fene;
@@ -903,9 +898,6 @@ lb_status lb_init(const lb_box_desc* boxes, int32_t n_boxes, int32_t precision, 
     c.dense_max_tiles = lo.dense_max_tiles;
     c.big_sparse = 0;
     for (int i : lo.big_list) c.big_sparse += lo.dense[i] ? 0 : 1;
-    c.bin_start = (uint32_t*)sc(lo.sc_binstart);
-    c.runimp = (unsigned long long*)sc(lo.sc_items);
-    c.slot_of = (uint32_t*)sc(lo.sc_slotof);
     c.sub_rec = (double*)sc(lo.sc_subrec);
     c.defer_on = 0;
     c.defer = (uint32_t*)sc(lo.sc_defer);
@@ -1003,7 +995,7 @@ lb_status lb_step(lb_handle* h, int64_t n_steps)
         h->pending = false;
         left -= 1;
     }
-    if (h->graph_steps > 0 && linear_steps(h)) {
+    if (h->graph_steps > 0 && graph_steps_apply(h)) {
         while (left >= h->graph_steps) {
             if (!h->gexec[h->cur]) {
                 lb_status s = build_graph(h, h->cur);

@@ -138,3 +138,24 @@ def test_checkpoint_of_uneven_boxes(prec):
     with pytest.raises(lbm.LBError):
         s.import_state({"step": a["step"], "boxes": a["boxes"][:2]})
     s.close()
+
+
+# 512 / 513 beads: both widths of the large-chain kernel; dense boxes (32 N >=
+# L^3) of one node range, of several with a ragged end, and the largest; cell
+# rows of the list build that pass a multiple of 16 cells (L = 40: 24 cells)
+# and ones that do not; several chains in a box
+@pytest.mark.parametrize("prec", [FP64, FP32])
+@pytest.mark.parametrize("L,N,chain_len", [(13, 257, 0), (14, 512, 32), (20, 513, 0), (32, 1024, 64), (24, 512, 0),
+                                           (40, 400, 0), (40, 700, 100)])
+def test_large_chain_kernels_match_oracle(orc, L, N, chain_len, prec):
+    say("large chain edges", L, N, chain_len, prec)
+    p = params(L=L, N=N, chain_len=chain_len, kT=0.05, md_dt=0.005, tau_lb=0.05, seed=31, box_id=2)
+    x = chain(p)
+    got = _run([p], [x], prec, True, 0, (3, 2))
+    o = oracle_state(orc, p, initial_pops(orc, p), x)
+    o.run(5)
+    if prec == FP64:
+        assert np.max(np.abs(got[0]["n"] - o.n)) < 1e-12
+        assert np.max(np.abs(got[0]["x"] - o.x)) < 1e-10
+    else:
+        assert max_rel_pop_err(got[0]["n"], o.n, orc) < 1e-5
