@@ -25,7 +25,6 @@ struct BoxDev {
     int32_t therm;       // 0 none, 1 stress modes, 2 all non-conserved modes
     int32_t substeps;
     int32_t couple_T;    // lanes per bead on the one-workgroup coupling path (a function of N only)
-    int32_t adj_T;       // the same for its reverse
     int32_t chain_len;   // beads per chain (> 0; N for a single chain)
     int32_t dense;       // 1: beads cover much of the box; its collide follows the coupling and
                          // takes the node impulses itself (no fix-up pass)

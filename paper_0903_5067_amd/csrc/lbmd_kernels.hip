@@ -2875,7 +2875,7 @@ __global__ __launch_bounds__(256) void k_adj_collide(const BoxDev* __restrict__ 
                                                      double* __restrict__ lam_dp, double* __restrict__ gpart,
                                                      uint64_t nodes, uint32_t step)
 {
-    __shared__ double red[2][256];
+    __shared__ double red[4][2];
     const uint32_t tile = blockIdx.x;
     const int bi = (int)tile_box[tile];
     const BoxDev& bx = boxes[bi];
@@ -2914,49 +2914,10 @@ __global__ __launch_bounds__(256) void k_adj_collide(const BoxDev* __restrict__ 
 #pragma unroll
         for (int c = 0; c < 3; ++c) lam_dp[c * nodes + gn] = lf[c];
     }
-    red[0][threadIdx.x] = gws;
-    red[1][threadIdx.x] = gwb;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) {
-            red[0][threadIdx.x] += red[0][threadIdx.x + w];
-            red[1][threadIdx.x] += red[1][threadIdx.x + w];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        gpart[2 * (uint64_t)tile] += red[0][0];
-        gpart[2 * (uint64_t)tile + 1] += red[1][0];
-    }
-}
-
-// densities of the eight stencil nodes over the T lanes of one bead, as
-// stencil_shared splits the corners: lane l sums corners l, l + T8, ... (NK
-// of them, T8 = 8 / NK), then the lanes exchange the sums
-template <typename R, int NK>
-__device__ __forceinline__ void adj_densities(const R* __restrict__ a, const int i0[3], int L, double rho0,
-                                              int lane, int T, double rho_k[8])
-{
-    constexpr int T8 = 8 / NK;
-    const int k0 = lane & (T8 - 1);
-    R dn[NK][19];
-#pragma unroll
-    for (int k = 0; k < NK; ++k) {
-        const int kk = k0 + k * T8;
-        const int ix = i0[0] + (kk & 1), iy = i0[1] + ((kk >> 1) & 1), iz = i0[2] + ((kk >> 2) & 1);
-        const Upwind up((uint32_t)(ix >= L ? ix - L : ix), (uint32_t)(iy >= L ? iy - L : iy),
-                        (uint32_t)(iz >= L ? iz - L : iz), (uint32_t)L);
-        gather_pre<R, false>(a, up, dn[k]);
-    }
-    double own[NK];
-#pragma unroll
-    for (int k = 0; k < NK; ++k) {
-        double rho = 0.0;
-        for (int i = 0; i < 19; ++i) rho += (double)dn[k][i];
-        own[k] = rho + rho0;
-    }
-#pragma unroll
-    for (int k = 0; k < 8; ++k) rho_k[k] = __shfl(own[k / T8], k % T8, T);
+    // the tile's sums: nothing waits for the old value
+    double g2[2] = {gws, gwb};
+    const double gs = block_sum256<2>(g2, red);
+    if (threadIdx.x < 2) atomicAdd(&gpart[2 * (uint64_t)tile + threadIdx.x], gs);
 }
 
 // add dJ/dv(end of step) and reverse the chain's substeps of one LB step; one
@@ -2981,32 +2942,54 @@ __device__ __forceinline__ void pair_kernel(const double d[3], double g, double 
     out[2] += g * v[2] + dv * d[2];
 }
 
-// Reverse sweep of one LB step's substeps for chains of at most 256 beads.
-// Thread layout as in the forward kernel: T lanes per bead (T a function of
-// N only), bead b = tid / T.  All lanes of a bead carry identical copies of
-// the bead's adjoint; the repulsive-LJ pairs of the force Hessian are split
-// over the lanes (partners j = lane mod T) and combined by a butterfly, which
-// gives every lane the same bits, and every lane adds the two bonds' terms;
-// the lanes share the stencil's density gathers; lane 0 writes and performs
-// the atomics.
-template <typename R>
-__global__ __launch_bounds__(256) void k_adj_couple(const BoxDev* __restrict__ boxes,
-                                                    const int32_t* __restrict__ couple_list, const R* __restrict__ P,
-                                                    AdjChainArgs aa, uint32_t step)
+// sum of v over the T lanes of a bead (all active), the same bits in each
+template <int T>
+__device__ __forceinline__ double bead_sum(double v)
 {
-    __shared__ double xs[3 * 256], lF[3 * 256], red[256];
-    const int bi = couple_list[blockIdx.x];
-    const BoxDev bx = boxes[bi];   // a copy: its fields stay in registers across the substeps
+    v += dpp_from<0xB1>(v);                 // quad_perm [1,0,3,2]
+    v += dpp_from<0x4E>(v);                 // quad_perm [2,3,0,1]
+    if (T >= 8) v += dpp_from<0x141>(v);    // row_half_mirror
+    if (T >= 16) v += dpp_from<0x140>(v);   // row_mirror
+    return v;
+}
+
+// Reverse sweep of one LB step's substeps for chains of at most 256 beads, T
+// lanes per bead as in the forward kernel (a function of N only).  Bound, like
+// it, by the serial chain of a substep; the lanes of a bead share its work:
+// each holds 8 / T corners of the stencil (velocities, densities, impulse and
+// velocity adjoints) and hands their adjoints over itself, takes every T-th
+// partner of the force Hessian from a list (bits of one word, as in the
+// forward kernel) and, lanes 0 and 1, one bond each; the noise words of T
+// substeps are drawn at once.  Sums over the lanes are DPP butterflies, so
+// every lane carries the same bead adjoint.  Positions and force adjoints
+// alternate between two LDS buffers: one barrier per substep.  32 beads, ten
+// substeps: 26.5 us, where lanes that each held all eight corners, with
+// lane 0 handing over and every partner tested, took 43 us.
+template <int MB>
+struct AdjLds {
+    double xs[2][3 * MB], lF[2][3 * MB];
+    int moved[3];
+    double red[16];
+};
+template <typename R, int T, int MB>
+__device__ __forceinline__ double adj_substeps(const BoxDev& bx, const R* __restrict__ P, const AdjChainArgs& aa,
+                                               uint32_t step, AdjLds<MB>& sh)
+{
+    constexpr int T8 = T < 8 ? T : 8, NC = 8 / T8;
+    constexpr int NB = MB <= 128 ? NC : 1;   // corners whose loads are in flight together
     const int N = bx.N, S = bx.substeps, L = bx.L;
-    const int T = bx.adj_T;
     const int b = (int)threadIdx.x / T, lane = (int)threadIdx.x % T;
     const bool act = b < N;
-    const bool writer = act && lane == 0;
     const uint64_t g = bx.bead_off + (uint64_t)(act ? b : 0);
     const ChainSpan sp = chain_span(bx, act ? b : 0);
     const double dt = bx.dt, h = 0.5 * dt / bx.mass, tau = bx.tau_lb, Ld = (double)L, iL = bx.inv_L;
     const double eps24 = 24.0 * bx.eps, s6c = bx.sigsq * bx.sigsq * bx.sigsq, s12c = s6c * s6c;
-    double lx[3] = {0, 0, 0}, lv[3] = {0, 0, 0}, lf[3] = {0, 0, 0};
+    const int kc = lane & (T8 - 1);
+    const double half = T == 16 && lane >= 8 ? 0.0 : 1.0;   // T = 16: the upper lanes repeat the corners
+    const bool bonded = act && ((lane == 0 && b > sp.lo) || (lane == 1 && b < sp.hi));
+    const int jb = lane == 0 ? b - 1 : b + 1;
+    if (threadIdx.x < 3) sh.moved[threadIdx.x] = 0;
+    double lx[3] = {0, 0, 0}, lv[3] = {0, 0, 0}, lf[3] = {0, 0, 0}, x0[3] = {0, 0, 0};
     if (act)
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
@@ -3014,26 +2997,30 @@ __global__ __launch_bounds__(256) void k_adj_couple(const BoxDev* __restrict__ b
         }
     double gz = 0.0;
     int cb[3] = {-1, -1, -1};
-    double lcu[8][3];          // accumulated adjoint of the stencil's node velocities
-    double rho_k[8];
-    uint32_t cnode[8];
-    double cuk[8][3];
-    double la[8][3];           // tau * lam_dp at the stencil's nodes
-    bool have = false;
+    double lcu[NC][3];         // accumulated adjoint of the stencil's node velocities
+    double rho_k[NC], cuk[NC][3];
+    double la[NC][3];          // tau * lam_dp at the stencil's nodes
+    uint32_t cnode[NC];
+    unsigned long long nl = 0ull;   // partners lane + T m within the list radius
+    U4 pw{0, 0, 0, 0};
     const R* pb = P + bx.pop_off;
     auto flush = [&]() __attribute__((always_inline)) {   // node velocity adjoint -> population adjoint at the stencil nodes
+        if (lane >= T8) return;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const double ir = 1.0 / (rho_k[k] * tau);
-            const double ul[3] = {cuk[k][0] * tau, cuk[k][1] * tau, cuk[k][2] * tau};
+        for (int kk = 0; kk < NC; ++kk) {
+            const double ir = 1.0 / (rho_k[kk] * tau);
+            const double lsum = lcu[kk][0] * (cuk[kk][0] * tau) + lcu[kk][1] * (cuk[kk][1] * tau) + lcu[kk][2] * (cuk[kk][2] * tau);
+            double* dst = aa.lam_n + bx.node_off + cnode[kk];
+#pragma unroll
             for (int i = 0; i < 19; ++i) {
-                const double cc = (double)cxv(i) * lcu[k][0] + (double)cyv(i) * lcu[k][1] + (double)czv(i) * lcu[k][2];
-                const double lsum = lcu[k][0] * ul[0] + lcu[k][1] * ul[1] + lcu[k][2] * ul[2];
-                atomicAdd(&aa.lam_n[i * aa.nodes + bx.node_off + cnode[k]], (cc - lsum) * ir);
+                const double cc = (double)cxv(i) * lcu[kk][0] + (double)cyv(i) * lcu[kk][1] + (double)czv(i) * lcu[kk][2];
+                atomicAdd(dst + i * aa.nodes, (cc - lsum) * ir);
             }
         }
     };
-    // tape record of substep s, loaded one substep ahead
+    // tape record of substep s, loaded one substep ahead where the registers
+    // allow it
+    constexpr bool AHEAD = MB <= 128;
     double nx1[3] = {0, 0, 0}, nv1[3] = {0, 0, 0}, nfc[3] = {0, 0, 0}, nfr[3] = {0, 0, 0}, ni0[3] = {0, 0, 0};
     auto load_rec = [&](int s) __attribute__((always_inline)) {
         const double* tq = aa.tape + ((uint64_t)s * aa.total_beads + g) * TAPE_REC;
@@ -3042,162 +3029,152 @@ __global__ __launch_bounds__(256) void k_adj_couple(const BoxDev* __restrict__ b
             nx1[c] = tq[c]; nv1[c] = tq[3 + c]; nfc[c] = tq[6 + c]; ni0[c] = tq[9 + c]; nfr[c] = tq[12 + c];
         }
     };
-    if (act) load_rec(S - 1);
-    for (int s = S - 1; s >= 0; --s) {
-        const double* tp = aa.tape + ((uint64_t)s * aa.total_beads + g) * TAPE_REC;
-        double x1[3], v1[3], fc[3], fr[3];
+    if (AHEAD && act) load_rec(S - 1);
+    for (int s = S - 1, it = 0; s >= 0; --s, ++it) {
+        if (!AHEAD && act) load_rec(s);
+        double* xs = sh.xs[s & 1];
+        double* lF = sh.lF[s & 1];
+        double x1[3], v1[3], fc[3], fr[3], rn[3] = {0, 0, 0};
         int i0[3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) { x1[c] = nx1[c]; v1[c] = nv1[c]; fc[c] = nfc[c]; i0[c] = (int)ni0[c]; fr[c] = nfr[c]; }
-        if (act && s > 0) load_rec(s - 1);
         // v' = v1 + f' h and f' = F_c + fc
         double lft[3], lv1[3], lfc[3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) { lft[c] = lf[c] + h * lv[c]; lv1[c] = lv[c]; lfc[c] = lft[c]; }
-        if (writer) {
-            xs[3 * b] = x1[0]; xs[3 * b + 1] = x1[1]; xs[3 * b + 2] = x1[2];
-            lF[3 * b] = lft[0]; lF[3 * b + 1] = lft[1]; lF[3 * b + 2] = lft[2];
+        if (act) {
+            if (lane == 0) {
+                bool far = false;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    xs[3 * b + c] = x1[c];
+                    lF[3 * b + c] = lft[c];
+                    far |= fabs(x1[c] - x0[c]) > 0.5 * NL_SKIN * 0.577;
+                }
+                if (it > 0 && far) sh.moved[it % 3] = 1;
+            }
+            if (AHEAD && s > 0) load_rec(s - 1);
+            if (it == 0 || s % T == T - 1)
+                pw = philox10(U4{(uint32_t)b, step, (1u << 16) | (uint32_t)(s - s % T + lane), 0u}, bx.seed, bx.box_id);
+            rn[0] = unit_noise<double>(__shfl(pw.x, s % T, T));
+            rn[1] = unit_noise<double>(__shfl(pw.y, s % T, T));
+            rn[2] = unit_noise<double>(__shfl(pw.z, s % T, T));
         }
         __syncthreads();
+        const bool rebuild = it == 0 || sh.moved[it % 3] != 0;
+        if (threadIdx.x == 0) sh.moved[(it + 2) % 3] = 0;
         double lx1[3] = {lx[0], lx[1], lx[2]};
         if (act) {
             // stencil of this substep
             if (i0[0] != cb[0] || i0[1] != cb[1] || i0[2] != cb[2]) {
-                if (have && lane == 0) flush();
+                if (it > 0) flush();
+                const double* tp = aa.tape + ((uint64_t)s * aa.total_beads + g) * TAPE_REC + 15;
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const int ix = i0[0] + (k & 1), iy = i0[1] + ((k >> 1) & 1), iz = i0[2] + ((k >> 2) & 1);
-                    const uint32_t nx = ix >= L ? ix - L : ix, ny = iy >= L ? iy - L : iy, nz = iz >= L ? iz - L : iz;
-                    cnode[k] = nx + (uint32_t)L * (ny + (uint32_t)L * nz);
-                }
-                // the densities of the 8 nodes, gathered by the bead's lanes
-                // together (T is uniform over the workgroup)
-                if (T >= 8) adj_densities<R, 1>(pb, i0, L, bx.rho0, lane, T, rho_k);
-                else if (T == 4) adj_densities<R, 2>(pb, i0, L, bx.rho0, lane, T, rho_k);
-                else if (T == 2) adj_densities<R, 4>(pb, i0, L, bx.rho0, lane, T, rho_k);
-                else {
-                    // one lane per bead: all eight, in batches whose loads are
-                    // issued before any is summed
-                    constexpr int NB = sizeof(R) == 4 ? 8 : 4;
+                for (int k0 = 0; k0 < NC; k0 += NB) {
+                    R d[NB][19];
 #pragma unroll
-                    for (int k0 = 0; k0 < 8; k0 += NB) {
-                        R dn[NB][19];
+                    for (int kk = k0; kk < k0 + NB; ++kk) {
+                        const int k = kc + kk * T8;
+                        const int ix = i0[0] + (k & 1), iy = i0[1] + ((k >> 1) & 1), iz = i0[2] + (k >> 2);
+                        const uint32_t nx = ix >= L ? ix - L : ix, ny = iy >= L ? iy - L : iy, nz = iz >= L ? iz - L : iz;
+                        cnode[kk] = nx + (uint32_t)L * (ny + (uint32_t)L * nz);
+                        gather_pre<R, false>(pb, Upwind(nx, ny, nz, (uint32_t)L), d[kk - k0]);
 #pragma unroll
-                        for (int kk = 0; kk < NB; ++kk) {
-                            const int k = k0 + kk;
-                            const int ix = i0[0] + (k & 1), iy = i0[1] + ((k >> 1) & 1), iz = i0[2] + ((k >> 2) & 1);
-                            const Upwind up((uint32_t)(ix >= L ? ix - L : ix), (uint32_t)(iy >= L ? iy - L : iy),
-                                            (uint32_t)(iz >= L ? iz - L : iz), (uint32_t)L);
-                            gather_pre<R, false>(pb, up, dn[kk]);
-                        }
-#pragma unroll
-                        for (int kk = 0; kk < NB; ++kk) {
-                            double rho = 0.0;
-                            for (int i = 0; i < 19; ++i) rho += (double)dn[kk][i];
-                            rho_k[k0 + kk] = rho + bx.rho0;
+                        for (int c = 0; c < 3; ++c) {
+                            cuk[kk][c] = tp[3 * k + c];
+                            lcu[kk][c] = 0.0;
+                            la[kk][c] = tau * aa.lam_dp[c * aa.nodes + bx.node_off + cnode[kk]];
                         }
                     }
-                }
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const uint64_t gn = bx.node_off + cnode[k];
+                    for (int kk = k0; kk < k0 + NB; ++kk) {
+                        double rho = 0.0;
 #pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        cuk[k][c] = tp[15 + 3 * k + c];
-                        lcu[k][c] = 0.0;
-                        la[k][c] = tau * aa.lam_dp[c * aa.nodes + gn];
+                        for (int i = 0; i < 19; ++i) rho += (double)d[kk - k0][i];
+                        rho_k[kk] = rho + bx.rho0;
                     }
                 }
                 cb[0] = i0[0]; cb[1] = i0[1]; cb[2] = i0[2];
-                have = true;
             }
-            double wt[8], ub[3] = {0, 0, 0};
+            double wt[NC], gx[NC], gy[NC], gw3[NC], ub[3] = {0, 0, 0}, sl[3] = {0, 0, 0};
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                wt[k] = ((k & 1) ? fr[0] : 1.0 - fr[0]) * (((k >> 1) & 1) ? fr[1] : 1.0 - fr[1]) *
-                        (((k >> 2) & 1) ? fr[2] : 1.0 - fr[2]);
-                ub[0] += wt[k] * cuk[k][0]; ub[1] += wt[k] * cuk[k][1]; ub[2] += wt[k] * cuk[k][2];
-            }
-            // impulse spread: acc_k -= w_k fc dt, handed over as tau * acc
-            double lw[8];
+            for (int kk = 0; kk < NC; ++kk) {
+                const int k = kc + kk * T8;
+                gx[kk] = (k & 1) ? fr[0] : 1.0 - fr[0];
+                gy[kk] = ((k >> 1) & 1) ? fr[1] : 1.0 - fr[1];
+                gw3[kk] = (k >> 2) ? fr[2] : 1.0 - fr[2];
+                wt[kk] = gx[kk] * gy[kk] * gw3[kk];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const double la0 = la[k][0], la1 = la[k][1], la2 = la[k][2];
-                lfc[0] -= dt * wt[k] * la0; lfc[1] -= dt * wt[k] * la1; lfc[2] -= dt * wt[k] * la2;
-                lw[k] = -dt * (fc[0] * la0 + fc[1] * la1 + fc[2] * la2);
+                for (int c = 0; c < 3; ++c) { ub[c] += wt[kk] * cuk[kk][c]; sl[c] += wt[kk] * la[kk][c]; }
             }
+#pragma unroll
+            for (int c = 0; c < 3; ++c) { ub[c] = bead_sum<T8>(ub[c]); sl[c] = bead_sum<T8>(sl[c]); }
+            // impulse spread: acc_k -= w_k fc dt, handed over as tau * acc;
             // fc = -zeta (v1 - u_b) + A(zeta) r
-            const U4 w = philox10(U4{(uint32_t)b, step, (1u << 16) | (uint32_t)s, 0u}, bx.seed, bx.box_id);
-            const double rn[3] = {unit_noise<double>(w.x), unit_noise<double>(w.y), unit_noise<double>(w.z)};
-            double lub[3];
+            double lub[3], part[3] = {0, 0, 0};
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
+                lfc[c] -= dt * sl[c];
                 if (bx.zeta > 0.0) gz += 0.5 * bx.bead_noise / bx.zeta * rn[c] * lfc[c];
                 gz -= (v1[c] - ub[c]) * lfc[c];
-                lv1[c] -= bx.zeta * lfc[c];
                 lub[c] = bx.zeta * lfc[c];
+                lv1[c] -= lub[c];
             }
-            // u_b = sum_k w_k cu_k
+            // u_b = sum_k w_k cu_k, and the trilinear weights w_k(fractions of x1)
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                lw[k] += cuk[k][0] * lub[0] + cuk[k][1] * lub[1] + cuk[k][2] * lub[2];
-                lcu[k][0] += wt[k] * lub[0]; lcu[k][1] += wt[k] * lub[1]; lcu[k][2] += wt[k] * lub[2];
-            }
-            // trilinear weights w_k(fractions of x1)
+            for (int kk = 0; kk < NC; ++kk) {
+                const int k = kc + kk * T8;
+                double lw = -dt * (fc[0] * la[kk][0] + fc[1] * la[kk][1] + fc[2] * la[kk][2]);
+                lw += cuk[kk][0] * lub[0] + cuk[kk][1] * lub[1] + cuk[kk][2] * lub[2];
+                lw *= half;
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const double g0 = (k & 1) ? fr[0] : 1.0 - fr[0], g1 = ((k >> 1) & 1) ? fr[1] : 1.0 - fr[1],
-                             g2 = ((k >> 2) & 1) ? fr[2] : 1.0 - fr[2];
-                lx1[0] += lw[k] * ((k & 1) ? 1.0 : -1.0) * g1 * g2;
-                lx1[1] += lw[k] * (((k >> 1) & 1) ? 1.0 : -1.0) * g0 * g2;
-                lx1[2] += lw[k] * (((k >> 2) & 1) ? 1.0 : -1.0) * g0 * g1;
+                for (int c = 0; c < 3; ++c) lcu[kk][c] += wt[kk] * lub[c];
+                part[0] += lw * ((k & 1) ? 1.0 : -1.0) * gy[kk] * gw3[kk];
+                part[1] += lw * (((k >> 1) & 1) ? 1.0 : -1.0) * gx[kk] * gw3[kk];
+                part[2] += lw * ((k >> 2) ? 1.0 : -1.0) * gx[kk] * gy[kk];
             }
             // conservative forces at x1: lam_x1_b += sum_j K_bj (lam_F_b - lam_F_j).
-            // The repulsive LJ pairs: this lane's share of the partners, four
-            // at a time (their terms are computed side by side, then added in
-            // ascending j), summed over the lanes
-            double lp[3] = {0, 0, 0};
-            for (int j0 = lane; j0 < N; j0 += 4 * T) {
-                double d[4][3], dl[4][3], gw[4], gpw[4];
-                bool hit[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int jj = j0 + u * T;
-                    const int j = jj < N ? jj : b;   // past the end: the bead itself, masked
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        dl[u][c] = lft[c] - lF[3 * j + c];
-                        d[u][c] = x1[c] - xs[3 * j + c];
-                        d[u][c] -= Ld * rint(d[u][c] * iL);
-                    }
-                    const double q = d[u][0] * d[u][0] + d[u][1] * d[u][1] + d[u][2] * d[u][2];
-                    hit[u] = j != b && q < bx.rc2;
-                    const double iq = 1.0 / (hit[u] ? q : 1.0), iq4 = iq * iq * iq * iq, iq7 = iq4 * iq * iq * iq;
-                    gw[u] = eps24 * (2.0 * s12c * iq7 - s6c * iq4);
-                    gpw[u] = eps24 * (-14.0 * s12c * iq7 * iq + 4.0 * s6c * iq4 * iq);
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (hit[u]) pair_kernel(d[u], gw[u], gpw[u], dl[u], lp);
-            }
-            for (int o = 1; o < T; o <<= 1) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) lp[c] += __shfl_xor(lp[c], o, T);
-            }
-            // the bonds (FENE) to b - 1 and b + 1, the same in every lane
-#pragma unroll
-            for (int side = 0; side < 2; ++side) {
-                const int j = side ? b + 1 : b - 1;
-                if (j < sp.lo || j > sp.hi) continue;
+            // This lane's bond (FENE) ...
+            {
+                const int j = bonded ? jb : b;
                 const double dl[3] = {lft[0] - lF[3 * j], lft[1] - lF[3 * j + 1], lft[2] - lF[3 * j + 2]};
                 const double d[3] = {x1[0] - xs[3 * j], x1[1] - xs[3 * j + 1], x1[2] - xs[3 * j + 2]};
                 const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
-                const double den = 1.0 - r2 * bx.inv_r0sq;
-                const double gfe = -bx.k_fene / den;
-                const double gpe = -bx.k_fene * bx.inv_r0sq / (den * den);
-                pair_kernel(d, gfe, gpe, dl, lp);
+                const double iden = 1.0 / (1.0 - r2 * bx.inv_r0sq);
+                const double gfe = -bx.k_fene * iden;
+                pair_kernel(d, gfe, gfe * bx.inv_r0sq * iden, dl, part);   // a zero separation adds nothing
             }
-            lx1[0] += lp[0]; lx1[1] += lp[1]; lx1[2] += lp[2];
+            // ... and its share of the repulsive LJ partners
+            if (rebuild) {
+                const double rl = sqrt(bx.rc2) + NL_SKIN + 1e-6, rl2 = rl * rl;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) x0[c] = x1[c];
+                nl = 0ull;
+#pragma unroll 2
+                for (int j = lane, m = 0; j < N; j += T, ++m) {
+                    double d0 = x1[0] - xs[3 * j], d1 = x1[1] - xs[3 * j + 1], d2 = x1[2] - xs[3 * j + 2];
+                    d0 -= Ld * rint(d0 * iL); d1 -= Ld * rint(d1 * iL); d2 -= Ld * rint(d2 * iL);
+                    if (j != b && d0 * d0 + d1 * d1 + d2 * d2 < rl2) nl |= 1ull << m;
+                }
+            }
+            for (unsigned long long m = nl; m; m &= m - 1ull) {
+                const int j = lane + T * (__ffsll((long long)m) - 1);
+                double d[3], dl[3];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    dl[c] = lft[c] - lF[3 * j + c];
+                    d[c] = x1[c] - xs[3 * j + c];
+                    d[c] -= Ld * rint(d[c] * iL);
+                }
+                const double q = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+                if (q < bx.rc2) {
+                    const double iq = 1.0 / q, iq4 = iq * iq * iq * iq, iq7 = iq4 * iq * iq * iq;
+                    pair_kernel(d, eps24 * (2.0 * s12c * iq7 - s6c * iq4),
+                                eps24 * (-14.0 * s12c * iq7 * iq + 4.0 * s6c * iq4 * iq), dl, part);
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < 3; ++c) lx1[c] += bead_sum<T>(part[c]);
         }
         // x1 = x + v1 dt,  v1 = v + f h
 #pragma unroll
@@ -3207,24 +3184,38 @@ __global__ __launch_bounds__(256) void k_adj_couple(const BoxDev* __restrict__ b
             lv[c] = lv1[c];
             lf[c] = h * lv1[c];
         }
-        __syncthreads();
     }
-    if (writer) {
-        if (have) flush();
+    if (act) {
+        flush();
+        if (lane == 0) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) { aa.lx[3 * g + c] = lx[c]; aa.lv[3 * g + c] = lv[c]; aa.lf[3 * g + c] = lf[c]; }
+            for (int c = 0; c < 3; ++c) { aa.lx[3 * g + c] = lx[c]; aa.lv[3 * g + c] = lv[c]; aa.lf[3 * g + c] = lf[c]; }
+        }
     }
-    // dJ/dzeta of the box: one copy per bead, summed over a zero-padded array
-    // (the block may hold fewer than 256 threads)
-    for (int i = (int)threadIdx.x; i < 256; i += (int)blockDim.x) red[i] = 0.0;
+    return act && lane == 0 ? gz : 0.0;   // one copy per bead
+}
+
+template <typename R, int MAXT>
+__global__ __launch_bounds__(MAXT) void k_adj_couple(const BoxDev* __restrict__ boxes,
+                                                     const int32_t* __restrict__ couple_list, const R* __restrict__ P,
+                                                     AdjChainArgs aa, uint32_t step)
+{
+    __shared__ AdjLds<MAXT / 4> sh;
+    const int bi = couple_list[blockIdx.x];
+    const BoxDev bx = boxes[bi];   // a copy: its fields stay in registers across the substeps
+    double gz;
+    if (bx.couple_T == 4) gz = adj_substeps<R, 4>(bx, P, aa, step, sh);
+    else if (bx.couple_T == 8) gz = adj_substeps<R, 8>(bx, P, aa, step, sh);
+    else gz = adj_substeps<R, 16>(bx, P, aa, step, sh);
+    // dJ/dzeta of the box: over each wavefront, then the wavefronts in order
+    for (int o = 1; o < 64; o <<= 1) gz += __shfl_xor(gz, o, 64);
+    if ((threadIdx.x & 63u) == 0u) sh.red[threadIdx.x / 64u] = gz;
     __syncthreads();
-    if (writer) red[threadIdx.x] = gz;
-    __syncthreads();
-    for (int wdt = 128; wdt > 0; wdt >>= 1) {
-        for (int i = (int)threadIdx.x; i < wdt; i += (int)blockDim.x) red[i] += red[i + wdt];
-        __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+        for (uint32_t w = 0; w < blockDim.x / 64u; ++w) t += sh.red[w];
+        aa.gz[bi] += t;
     }
-    if (threadIdx.x == 0) aa.gz[bi] += red[0];
 }
 
 template <typename R>
@@ -3243,11 +3234,18 @@ hipError_t launch_adj_couple(const LaunchCtx& c, const int32_t* list, int n_list
                              const AdjArgsHost& a, uint32_t step)
 {
     if (n_list == 0) return hipSuccess;
-    if (block < 64 || block > 256) return hipErrorInvalidValue;
+    if (block < 64 || block > 1024) return hipErrorInvalidValue;
     AdjChainArgs aa{a.x0, a.v0, a.f0, a.tape, a.dj, a.lx, a.lv, a.lf, a.lam_n, a.lam_dp, a.gz, a.nodes,
                     c.total_beads};
-    hipLaunchKernelGGL(k_adj_couple<R>, dim3(n_list), dim3(block), 0, c.stream, c.boxes, list, (const R*)P, aa,
-                       step);
+    if (block > 512)
+        hipLaunchKernelGGL((k_adj_couple<R, 1024>), dim3(n_list), dim3(block), 0, c.stream, c.boxes, list, (const R*)P,
+                           aa, step);
+    else if (block > 256)
+        hipLaunchKernelGGL((k_adj_couple<R, 512>), dim3(n_list), dim3(block), 0, c.stream, c.boxes, list, (const R*)P,
+                           aa, step);
+    else
+        hipLaunchKernelGGL((k_adj_couple<R, 256>), dim3(n_list), dim3(block), 0, c.stream, c.boxes, list, (const R*)P,
+                           aa, step);
     return hipGetLastError();
 }
 

@@ -89,8 +89,8 @@ struct Layout {
     std::vector<int32_t> big_list;                    // boxes whose chain takes the 1024-thread kernel
     int big_max_n = 0, big_max_sub = 0;              // largest chain and most substeps among them
     std::vector<int32_t> small_list;                  // boxes on the one-workgroup path
-    std::vector<int> couple_T, adj_T;   // per box: lanes per bead on the one-workgroup path and its reverse
-    int couple_block = 64, adj_block = 64;
+    std::vector<int> couple_T;   // per box: lanes per bead on the one-workgroup path
+    int couple_block = 64;
     int touch_cap = 8;
 };
 
@@ -181,24 +181,18 @@ Layout make_layout(const lb_box_desc* b, int32_t n, int32_t prec, int32_t hist)
     Lo.total_tiles = tiles;
     Lo.total_beads = beads;
     Lo.total_nodes = nodes;
-    // lanes per bead of the one-workgroup coupling kernels (functions of the
+    // lanes per bead of the one-workgroup coupling kernels, a function of the
     // box's own N, so that a box computes the same bits alone and in any
-    // batch): forward 16 to 16 beads, 8 to 32, 4 above (256 threads to 64
-    // beads, 1024 at 256); reverse as many as 256 threads hold
-    int widest = 0, adj_widest = 0;
+    // batch: 16 to 16 beads, 8 to 32, 4 above (256 threads to 64 beads, 1024
+    // at 256)
+    int widest = 0;
     for (int i = 0; i < n; ++i) {
         const int N = b[i].n_beads;
-        const bool on = N > 0 && N <= BIG_CHAIN;
         const int T = N <= 16 ? 16 : (N <= 32 ? 8 : 4);
-        int Ta = 1;
-        if (on)
-            while (Ta < 16 && 2 * Ta * N <= 256) Ta *= 2;
         Lo.couple_T.push_back(T);
-        Lo.adj_T.push_back(Ta);
-        if (on) { widest = std::max(widest, T * N); adj_widest = std::max(adj_widest, Ta * N); }
+        if (N > 0 && N <= BIG_CHAIN) widest = std::max(widest, T * N);
     }
     if (widest > 0) Lo.couple_block = (int)round_up((uint64_t)widest, 64);
-    if (adj_widest > 0) Lo.adj_block = (int)round_up((uint64_t)adj_widest, 64);
     size_t o = 0;
     Lo.st_popA = o; o = align256(o + pop * Lo.esz);
     Lo.st_popB = o; o = align256(o + pop * Lo.esz);
@@ -806,7 +800,6 @@ lb_status lb_init(const lb_box_desc* boxes, int32_t n_boxes, int32_t precision, 
         b.tile_begin = lo.tile_begin[i]; b.n_tiles = lo.n_tiles[i];
         b.therm = d.thermalize; b.substeps = d.md_substeps;
         b.couple_T = lo.couple_T[i];
-        b.adj_T = lo.adj_T[i];
         b.chain_len = d.chain_len > 0 ? d.chain_len : std::max(d.n_beads, 1);
         b.dense = lo.dense[i];
         b.stat_off = lo.stat_off[i];
@@ -1684,8 +1677,8 @@ lb_status lb_window_backward(lb_handle* h, void* d_ws, size_t bytes, const doubl
             a.gz = (double*)(ws + w.gz);
             a.nodes = nodes;
             const int nc = (int)h->couple_host.size();
-            HIPCHK(h, f64 ? launch_adj_couple<double>(rc, h->couple_list, nc, lo.adj_block, P, a, stepv)
-                          : launch_adj_couple<float>(rc, h->couple_list, nc, lo.adj_block, P, a, stepv));
+            HIPCHK(h, f64 ? launch_adj_couple<double>(rc, h->couple_list, nc, lo.couple_block, P, a, stepv)
+                          : launch_adj_couple<float>(rc, h->couple_list, nc, lo.couple_block, P, a, stepv));
             std::swap(lam_next, lam_cur);
         }
         HIPCHK(h, hipEventRecord(reversed[tb], rs));

@@ -159,3 +159,21 @@ def test_large_chain_kernels_match_oracle(orc, L, N, chain_len, prec):
         assert np.max(np.abs(got[0]["x"] - o.x)) < 1e-10
     else:
         assert max_rel_pop_err(got[0]["n"], o.n, orc) < 1e-5
+
+
+@pytest.mark.parametrize("L,N,chain_len", [(8, 1, 0), (10, 17, 0), (14, 65, 13), (16, 129, 0)])
+def test_adjoint_lane_layouts_match_oracle_tangent(orc, L, N, chain_len):
+    """The reverse coupling kernel at the edges of its lanes per bead and
+    threads per workgroup, against the oracle's exact tangent."""
+    say("adjoint lane layouts", L, N, chain_len)
+    p = params(L=L, N=N, chain_len=chain_len, kT=1e-3, omega_s=1.2, omega_b=0.9, seed=17, box_id=1)
+    x0, n0 = chain(p), initial_pops(orc, p, amp=0.01, seed=11)
+    s = gpu_system([p], FP64, xs=[x0], pops=[n0])
+    vh = s.window_forward(6, 4)
+    cw = np.random.default_rng(5).normal(size=vh.shape)
+    grad = s.window_backward(cw)[0]
+    ho, dh = oracle_state(orc, p, n0, x0).window_tangent(6)
+    assert np.max(np.abs(vh - ho)) < 1e-10
+    ref = np.einsum("tna,tnak->k", cw, dh)
+    np.testing.assert_allclose(grad, ref, rtol=1e-7, atol=1e-7 * np.max(np.abs(ref)))
+    s.close()
