@@ -257,10 +257,11 @@ lb_status lb_bead_positions(lb_handle* h, double* host_out, size_t bytes);
  * boxes that their beads all cover densely) and batched steps with chains
  * above 256 beads and no dense box; the other batched forms, whose steps put
  * kernels on two streams, are always launched directly, and so are batched
- * FP32 steps whose chains all exceed 256 beads (and cover no box densely):
- * each collide there carries the step's node tables and a resident chain
- * kernel waits for them, an order that graph replay does not keep (a stream
- * under capture takes a graph-safe form).
+ * FP32 steps whose chains all exceed 256 beads (and cover no box densely).
+ * Where the collide sets the time of those (large boxes), each collide
+ * carries the step's node tables and a resident chain kernel waits for them,
+ * an order that graph replay does not keep (a stream under capture takes a
+ * graph-safe form).
  * Such a run also needs the GPU to run kernels of its two streams at once;
  * where a tool runs one kernel at a time (hardware counter collection), the
  * wait gives up and LB_HEALTH_SYNC is set.  batched = 3 is batched = 1

@@ -291,6 +291,7 @@ struct lb_handle {
     // collide kernel of the same step (both only read the current state)
     hipStream_t stream2 = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_table = nullptr, ev_head = nullptr, ev_def = nullptr;
+    hipEvent_t ev_coll = nullptr;     // runs bound by a large chain: the last collide is done
     LaunchCtx ctx{};
     LaunchCtx ctx2{};
     int32_t* couple_list = nullptr;   // device: boxes on the one-workgroup path (chains <= 256 beads)
@@ -573,6 +574,56 @@ lb_status enqueue_one_run(lb_handle* h, int from, uint32_t n)
     return enqueue_one_end(h, h->ctx, h->pop(pl), h->pop(1 - pl), n);
 }
 
+// Runs of steps with large chains only, so small that a step's collide (~30 us
+// per million nodes in FP32) ends well before its chain work (node table,
+// substeps at 6-8 us each, spread): the chain's queue sets the step time.
+bool large_chain_bound(const lb_handle* h)
+{
+    const double collide_us = 30e-6 * (double)h->lo.total_nodes * (double)h->lo.esz / 4.0;
+    return headed_steps(h) && h->couple_host.empty() && collide_us < 20.0 + 5.0 * h->lo.big_max_sub;
+}
+
+// A run of n such steps from buffer `from`, launched directly: the second
+// stream holds the chain work of one step after another, node table to
+// deferred tiles, so that no kernel of it waits for an event of the other
+// queue that is not long past; the handle's stream holds the collides, each
+// behind its step's node table (which first re-collides the previous step's
+// impulses outside its deferred tiles).  96^3, 512 beads: 96
+// against 106 us/step with the node tables in the collide, where the chain
+// kernel waited ~17 us for them.  Every node gets the same collide call with
+// the same impulse as in enqueue_step, so the bits are the same.
+lb_status enqueue_large_chain_run(lb_handle* h, int from, uint32_t n)
+{
+    const Layout& lo = h->lo;
+    const bool f64 = h->prec == LB_FP64;
+    LaunchCtx ca = h->ctx, cb = h->ctx2;
+    ca.defer_on = cb.defer_on = 1;
+    const int nbig = (int)lo.big_list.size();
+    const uint32_t ts = (uint32_t)lo.tiles_sparse;
+    const int one = nbig == 1 ? lo.big_list[0] : -1;
+    HIPCHK(h, hipEventRecord(h->ev_coll, h->stream));
+    for (uint32_t k = 0; k < n; ++k) {
+        const int p = from ^ (int)(k & 1);
+        const void* A = h->pop(p);
+        void* B = h->pop(1 - p);
+        const void* pend = k > 0 ? h->pop(1 - p) : nullptr;   // step k-1's input
+        HIPCHK(h, hipStreamWaitEvent(h->stream2, h->ev_coll, 0));
+        HIPCHK(h, f64 ? launch_couple_big<double>(cb, A, h->big_list, nbig, lo.big_max_n, k, h->ev_head, pend, one)
+                      : launch_couple_big<float>(cb, A, h->big_list, nbig, lo.big_max_n, k, h->ev_head, pend, one));
+        HIPCHK(h, f64 ? launch_collide_deferred<double>(cb, A, B, k) : launch_collide_deferred<float>(cb, A, B, k));
+        // behind the node table, and with it behind step k-1's deferred tiles
+        HIPCHK(h, hipStreamWaitEvent(h->stream, h->ev_head, 0));
+        HIPCHK(h, f64 ? launch_collide<double>(ca, A, B, -1, 0, ts, k) : launch_collide<float>(ca, A, B, -1, 0, ts, k));
+        HIPCHK(h, hipEventRecord(h->ev_coll, h->stream));
+    }
+    const int pl = from ^ (int)((n - 1) & 1);
+    HIPCHK(h, hipEventRecord(h->ev_def, h->stream2));
+    HIPCHK(h, hipStreamWaitEvent(h->stream, h->ev_def, 0));
+    HIPCHK(h, f64 ? launch_overflow<double>(ca, h->pop(pl), h->pop(1 - pl), n - 1)
+                  : launch_overflow<float>(ca, h->pop(pl), h->pop(1 - pl), n - 1));
+    return LB_OK;
+}
+
 // FP32 runs whose chains are all large (every box with beads holds a chain
 // above BIG_CHAIN beads, none of them dense) take the collide that carries
 // its own node tables from the second step on.  (In FP64 the node-table code
@@ -589,7 +640,7 @@ bool fused_steps(const lb_handle* h)
 {
     // the collide's node-table workgroups wait for each other, so they must
     // fit on the GPU at once: at most one per CU
-    return h->resident && headed_steps(h) && h->couple_host.empty() && h->prec == LB_FP32_DEV &&
+    return h->resident && headed_steps(h) && !large_chain_bound(h) && h->couple_host.empty() && h->prec == LB_FP32_DEV &&
            head_blocks((int)h->lo.big_list.size(), h->lo.big_max_n) <= (uint32_t)h->ctx.n_cu;
 }
 
@@ -669,7 +720,7 @@ lb_status enqueue_fused_run(lb_handle* h, int from, uint32_t n, uint32_t advance
 // of the host process.
 bool graph_steps_apply(const lb_handle* h)
 {
-    if (fused_steps(h)) return false;
+    if (fused_steps(h) || (large_chain_bound(h) && h->prec == LB_FP32_DEV)) return false;
     return !h->batched || one_kernel_steps(h) || headed_steps(h) || h->lo.total_beads == 0 || h->lo.tiles_sparse == 0;
 }
 
@@ -680,7 +731,10 @@ lb_status enqueue_steps(lb_handle* h, int from, uint32_t n)
     if (n == 0) return LB_OK;
     if (one_kernel_steps(h)) return enqueue_one_run(h, from, n);
     if (fused_steps(h) && !capturing(h->stream)) return enqueue_fused_run(h, from, n, n);
-    if (headed_steps(h)) {
+    if (large_chain_bound(h) && !capturing(h->stream)) {
+        const lb_status s = enqueue_large_chain_run(h, from, n);
+        if (s != LB_OK) return s;
+    } else if (headed_steps(h)) {
         const lb_status s = enqueue_headed_run(h, from, n);
         if (s != LB_OK) return s;
     } else {
@@ -919,6 +973,7 @@ lb_status lb_init(const lb_box_desc* boxes, int32_t n_boxes, int32_t precision, 
     if (e == hipSuccess) e = hipEventCreateWithFlags(&h->ev_table, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&h->ev_head, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&h->ev_def, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&h->ev_coll, hipEventDisableTiming);
     if (e != hipSuccess) {
         std::string msg = std::string("second stream: ") + hipGetErrorString(e);
         lb_free(h);
@@ -1804,6 +1859,7 @@ void lb_free(lb_handle* h)
     if (h->ev_table) (void)hipEventDestroy(h->ev_table);
     if (h->ev_head) (void)hipEventDestroy(h->ev_head);
     if (h->ev_def) (void)hipEventDestroy(h->ev_def);
+    if (h->ev_coll) (void)hipEventDestroy(h->ev_coll);
     if (h->stream2) (void)hipStreamDestroy(h->stream2);
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
     delete h;

@@ -177,3 +177,27 @@ def test_adjoint_lane_layouts_match_oracle_tangent(orc, L, N, chain_len):
     ref = np.einsum("tna,tnak->k", cw, dh)
     np.testing.assert_allclose(grad, ref, rtol=1e-7, atol=1e-7 * np.max(np.abs(ref)))
     s.close()
+
+
+def test_runs_whose_collides_carry_the_node_tables():
+    """A box large enough that its collide, not its large chain, sets the step
+    time (136^3): FP32 runs put the node tables into the collides.  A hot
+    chain's beads leave their tables within the steps; bits as with the
+    re-collision after the collide, in one run and in two."""
+    say("node tables in the collide")
+    p = params(L=136, N=300, seed=7, box_id=0, kT=1.0, therm=0, md_dt=0.02, md_substeps=10, tau_lb=0.2, zeta=1.0,
+               k_fene=7.0, r0_fene=2.0)
+    x = chain(p)
+    s = gpu_system([p], FP32, xs=[x])
+    s.set_launch(batched=True, overlap=False)
+    left = 0
+    for _ in range(8):
+        a = s.bead_positions()
+        s.step(1)
+        # a stencil outside the 3x3x3 nodes around the nearest node of the start
+        left += int((np.abs(np.floor(s.bead_positions()) + 0.5 - np.floor(a + 0.5)) > 1.0).any(1).sum())
+    want = s.export_state()["boxes"]
+    s.close()
+    assert left > 0
+    _equal(_run([p], [x], FP32, True, 0, (8,)), want)
+    _equal(_run([p], [x], FP32, True, 4, (5, 3)), want)
