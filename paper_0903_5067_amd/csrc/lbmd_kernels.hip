@@ -787,7 +787,8 @@ __global__ __launch_bounds__(MAXT) void k_couple(const BoxDev* __restrict__ boxe
 //   k_chain_wg    one workgroup of up to 1024 threads per box, one thread
 //                 per bead, every MD substep in one launch.  Positions,
 //                 neighbour lists, the positions they were built at and the
-//                 cell buckets of the list build live in LDS (150 KB); each
+//                 cell buckets of the list build live in LDS (156 KB for 1024
+//                 beads, 90 KB for 512); each
 //                 bead's stencil velocities in
 //                 registers, refilled from the 3x3x3 table when the bead
 //                 changes cell.  Per substep each bead writes one record
@@ -1530,11 +1531,10 @@ __global__ __launch_bounds__(NT) void k_chain_wg(const BoxDev* __restrict__ boxe
 
 // an impulse on a node whose tile is not deferred (the bead left its table):
 // listed for the end-of-step fix-up
-__device__ __forceinline__ uint32_t list_overflow(const ChainArgs& ca, const BoxDev& bx, uint64_t g, uint32_t node,
+__device__ __forceinline__ uint32_t list_overflow(const ChainArgs& ca, uint64_t g, uint64_t node_at, uint32_t node,
                                                   Ctrl* __restrict__ ctrl, uint32_t stamp)
 {
-    if (!ca.defer || ca.defer[2u * dseg_of(bx, node) + (stamp & 1u)] == stamp) return 0u;
-    ca.ovm[bx.node_off + node] = stamp;   // read by the next step's node-table work
+    ca.ovm[node_at] = stamp;              // read by the next step's node-table work
     ctrl->ovf_flag[stamp & 1u] = stamp;   // the next step's collide waits for that work
     const uint32_t k = atomicAdd(&ctrl->ovf_cnt, 1u);
     if (k >= ca.ovf_cap) return H_TABLE;
@@ -1579,6 +1579,11 @@ __device__ __forceinline__ void list_deferred(const BoxDev& bx, const ChainArgs&
 // stencil changes and after the last substep (lattice units, fixed point)
 // The workgroups from n_spread on build the list of the step's deferred
 // tiles, which needs nothing of the impulses.
+// Bounds: latency (16 to 32 workgroups for one chain).  The records of
+// REC_AHEAD substeps are read together, and the segment's stamp when a stencil
+// begins: a load per substep, each behind the one before, took 13.1 us for 512
+// beads and 10 substeps, this form 9.7 us.
+constexpr int REC_AHEAD = 5;
 __global__ __launch_bounds__(256) void k_spread(const BoxDev* __restrict__ boxes, const int32_t* __restrict__ list,
                                                 ChainArgs ca, const double* __restrict__ rec,
                                                 const int4* __restrict__ near_c, Ctrl* __restrict__ ctrl,
@@ -1600,39 +1605,46 @@ __global__ __launch_bounds__(256) void k_spread(const BoxDev* __restrict__ boxes
     unsigned long long* imp = ca.imp + 3 * bx.node_off;
     uint32_t hb = 0;
     double acc[3] = {0, 0, 0};
-    uint32_t cur = 0xffffffffu;
-    for (int s = 0; s < bx.substeps; ++s) {
-        const double* r = rec + ((uint64_t)s * ca.total_beads + g) * REC;
-        const Cell cl = cell_of_packed((unsigned long long)__double_as_longlong(r[6]));
-        const uint32_t node = node_of(cl.x + (k & 1), cl.y + ((k >> 1) & 1), cl.z + ((k >> 2) & 1), L);
-        if (node != cur) {
-            if (cur != 0xffffffffu) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    double q = acc[c] * tau;
-                    if (!(fabs(q) < IMP_MAX)) { hb |= H_FIXED; q = 0.0; }
-                    atomicAdd(imp + 3 * (uint64_t)cur + c, (unsigned long long)(long long)llrint(q * IMP_SCALE));
-                }
-                hb |= list_overflow(ca, bx, g, cur, ctrl, stamp);
-            }
-            cur = node;
-            acc[0] = acc[1] = acc[2] = 0.0;
-        }
-        const double wk = ((k & 1) ? r[0] : 1.0 - r[0]) * (((k >> 1) & 1) ? r[1] : 1.0 - r[1]) *
-                          (((k >> 2) & 1) ? r[2] : 1.0 - r[2]);
-        acc[0] -= wk * r[3] * dt;
-        acc[1] -= wk * r[4] * dt;
-        acc[2] -= wk * r[5] * dt;
-    }
-    if (cur != 0xffffffffu) {
+    uint32_t cur = 0xffffffffu, cur_stamp = 0;
+    auto hand_over = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             double q = acc[c] * tau;
             if (!(fabs(q) < IMP_MAX)) { hb |= H_FIXED; q = 0.0; }
             atomicAdd(imp + 3 * (uint64_t)cur + c, (unsigned long long)(long long)llrint(q * IMP_SCALE));
         }
-        hb |= list_overflow(ca, bx, g, cur, ctrl, stamp);
+        if (cur_stamp != stamp) hb |= list_overflow(ca, g, bx.node_off + cur, cur, ctrl, stamp);
+    };
+    const int S = bx.substeps;
+    for (int s0 = 0; s0 < S; s0 += REC_AHEAD) {
+        double2 r[REC_AHEAD][3];
+        unsigned long long cell[REC_AHEAD];
+#pragma unroll
+        for (int u = 0; u < REC_AHEAD; ++u) {
+            const double2* q = (const double2*)(rec + ((uint64_t)min(s0 + u, S - 1) * ca.total_beads + g) * REC);
+            r[u][0] = q[0]; r[u][1] = q[1]; r[u][2] = q[2];
+            cell[u] = ((const unsigned long long*)q)[6];
+        }
+#pragma unroll
+        for (int u = 0; u < REC_AHEAD; ++u) {
+            if (s0 + u >= S) break;
+            const Cell cl = cell_of_packed(cell[u]);
+            const uint32_t node = node_of(cl.x + (k & 1), cl.y + ((k >> 1) & 1), cl.z + ((k >> 2) & 1), L);
+            if (node != cur) {
+                if (cur != 0xffffffffu) hand_over();
+                cur = node;
+                // read here, used at the hand-over
+                cur_stamp = ca.defer ? ca.defer[2u * dseg_of(bx, node) + (stamp & 1u)] : stamp;
+                acc[0] = acc[1] = acc[2] = 0.0;
+            }
+            const double wk = ((k & 1) ? r[u][0].x : 1.0 - r[u][0].x) * (((k >> 1) & 1) ? r[u][0].y : 1.0 - r[u][0].y) *
+                              (((k >> 2) & 1) ? r[u][1].x : 1.0 - r[u][1].x);
+            acc[0] -= wk * r[u][1].y * dt;
+            acc[1] -= wk * r[u][2].x * dt;
+            acc[2] -= wk * r[u][2].y * dt;
+        }
     }
+    if (cur != 0xffffffffu) hand_over();
     if (hb) atomicOr(&ctrl->health, hb);
 }
 

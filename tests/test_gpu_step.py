@@ -201,3 +201,24 @@ def test_runs_whose_collides_carry_the_node_tables():
     assert left > 0
     _equal(_run([p], [x], FP32, True, 0, (8,)), want)
     _equal(_run([p], [x], FP32, True, 4, (5, 3)), want)
+
+
+@pytest.mark.parametrize("substeps", [1, 4, 5, 6, 11])
+def test_impulses_of_any_number_of_substeps(orc, substeps):
+    """The impulses of a large chain are made from its substep records, five
+    at a time: every remainder, against the oracle."""
+    say("records of", substeps, "substeps")
+    p = params(L=40, N=300, kT=1e-2, seed=9, md_dt=0.01, md_substeps=substeps, tau_lb=0.01 * substeps)
+    x = chain(p)
+    n0 = initial_pops(orc, p, amp=0.01, seed=3)
+    s = gpu_system([p], FP64, xs=[x], pops=[n0])
+    s.couple()
+    o = oracle_state(orc, p, n0, x)
+    dp = o.couple()
+    assert np.abs(s.pending_impulse()[0] - dp).max() < 1e-13
+    s.step(5)
+    o.collide_stream(dp)
+    o.run(4)
+    st = s.export_state()["boxes"][0]
+    s.close()
+    assert max_rel_pop_err(st["n"], o.n, orc) < 1e-11
