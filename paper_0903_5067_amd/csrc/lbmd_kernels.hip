@@ -2251,7 +2251,7 @@ __device__ __forceinline__ void wave_sums24(const double v[24], double* dst)
 // each population); on small ones by how many wavefronts share the nodes (a
 // 64^3 box's 64 blocks of 256 threads took 27 us).  The whole call, with one
 // copy to the host instead of four: 64^3 106 -> 39 us, 128 boxes of 15^3 178
-// -> 61, 256^3 304 -> 295 (1.275 GB).
+// -> 61, 256^3 304 -> 267 (1.275 GB).
 __device__ __forceinline__ float uniform_value(float v)
 {
     return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));

@@ -182,9 +182,17 @@ constexpr uint32_t STAT_DIRECT = 256;   // where it has more than these
 // Collide tiles per block of the observables pass, a function of the box
 // alone: few for a small box, so that its blocks fill the GPU, as far as its
 // records and their ranges fit 64 + n_tiles / 16 of them (what
-// lb_observables_static counts per box).
+// lb_observables_static counts per box).  Above 12000 tiles, where a CU holds
+// one block (1024 threads, four waves per SIMD) and a block's sums weigh more
+// than an uneven share: up to 64, in whole rounds of 256 blocks.  The whole
+// call with 16 against this, us: 150^3 85 and 76, 160^3 93 and 84, 192^3 148
+// and 131, 256^3 300 and 267; 128^3 and 144^3 are no faster with 32 to 64.
 __host__ __device__ inline uint32_t stat_tpb(uint32_t n_tiles)
 {
+    if (n_tiles > 12000) {
+        const uint32_t blocks = 256u * ((n_tiles + 256u * 64u - 1) / (256u * 64u));
+        return ((n_tiles + blocks - 1) / blocks + 3u) & ~3u;
+    }
     return n_tiles <= 320 ? 4u : (n_tiles <= 960 ? 8u : (n_tiles <= 2880 ? 12u : 16u));
 }
 __host__ __device__ inline uint32_t stat_recs_of(uint32_t n_tiles)

@@ -222,3 +222,21 @@ def test_impulses_of_any_number_of_substeps(orc, substeps):
     st = s.export_state()["boxes"][0]
     s.close()
     assert max_rel_pop_err(st["n"], o.n, orc) < 1e-11
+
+
+@pytest.mark.parametrize("L", [150, 163])
+def test_observables_of_large_boxes(orc, L):
+    """The sums of a box above 12000 tiles (one round of blocks, its records
+    summed at once; two rounds, the records in ranges; the last block short)
+    against the oracle's, on populations of which many are negative."""
+    say("observables", L)
+    p = params(L=L, N=0, kT=0.0, therm=0)
+    n = initial_pops(orc, p, amp=1.5, seed=5)
+    s = gpu_system([p], FP64, pops=[n])
+    got = s.observables(allow_unhealthy=True)[0]
+    s.close()
+    want = oracle_state(orc, p, n, np.zeros((0, 3))).observables()
+    assert got["neg"] == want[orc.OBS["neg"]]
+    assert got["mass"] == pytest.approx(want[0], rel=1e-12)
+    np.testing.assert_allclose(got["p_total"], want[10:13], atol=1e-7)   # 4e6 nodes of ~1, summed in FP64
+    np.testing.assert_allclose(got["mode_sq"], want[19:38], rtol=1e-9, atol=1e-20)
