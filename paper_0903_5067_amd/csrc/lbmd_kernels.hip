@@ -1052,11 +1052,22 @@ __device__ __forceinline__ void wait_count(Ctrl* __restrict__ ctrl, uint32_t* cn
     __syncthreads();
 }
 
-// every thread of the workgroup has written what it should: count the
-// workgroup in *cnt, visibly for the other agents' acquire
+// Every thread of the workgroup has written what another agent will read:
+// wait at the barrier with each wavefront's stores in L2.  The barrier alone
+// does not wait for them (the compiler drains LDS there, not global stores),
+// and a fence after it drains the fencing wavefront's only; with this, one
+// thread's release fence behind it covers the whole workgroup.
+__device__ __forceinline__ void all_stored()
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+}
+
+// count the workgroup, whose threads are done, in *cnt, visibly for the other
+// agents' acquire
 __device__ __forceinline__ void count_done(uint32_t* cnt)
 {
-    __syncthreads();
+    all_stored();
     if (threadIdx.x == 0) {
         __threadfence();
         atomicAdd(cnt, 1u);
@@ -1949,7 +1960,7 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(W))) void k_
         for (uint32_t e = threadIdx.x; e < n_ovf; e += BT)
             fixup_node<R>(fb, ccs[bi], ca.touched[bx.bead_off * ca.touch_cap + e], imp_prev, claim, Aprev, A, ctrl,
                           t - 1u, keep_imp);
-        __syncthreads();
+        all_stored();
         if (threadIdx.x == 0) {
             __threadfence();
             __hip_atomic_store(&rec.fixed[p], defer_stamp(t), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
