@@ -253,15 +253,14 @@ lb_status lb_bead_positions(lb_handle* h, double* host_out, size_t bytes);
  * graph and replays it; 0 launches kernels directly.  The graphs of both
  * buffer parities are recorded and instantiated here, before returning
  * (synchronous), so that lb_step only replays them.  Recorded are steps that
- * keep to one stream (the per-box form, one-kernel steps, boxes without beads,
- * boxes that their beads all cover densely) and batched steps with chains
- * above 256 beads and no dense box; the other batched forms, whose steps put
- * kernels on two streams, are always launched directly, and so are batched
- * FP32 steps whose chains all exceed 256 beads (and cover no box densely).
- * Where the collide sets the time of those (large boxes), each collide
- * carries the step's node tables and a resident chain kernel waits for them,
- * an order that graph replay does not keep (a stream under capture takes a
- * graph-safe form).
+ * keep to one stream: the per-box form, one-kernel steps, boxes without beads,
+ * and boxes that their beads all cover densely.  All other batched steps put
+ * kernels on two streams and are always launched directly, whatever
+ * graph_steps is.
+ * In FP32 steps whose chains all exceed 256 beads (and cover no box densely),
+ * in boxes so large that the collide sets the step time, each collide carries
+ * the step's node tables and a resident chain kernel waits for them (a stream
+ * under capture takes a form without that wait).
  * Such a run also needs the GPU to run kernels of its two streams at once;
  * where a tool runs one kernel at a time (hardware counter collection), the
  * wait gives up and LB_HEALTH_SYNC is set.  batched = 3 is batched = 1

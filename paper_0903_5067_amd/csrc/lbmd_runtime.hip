@@ -711,17 +711,14 @@ lb_status enqueue_fused_run(lb_handle* h, int from, uint32_t n, uint32_t advance
     return LB_OK;
 }
 
-// Which steps a graph records: those that keep to one stream, and the runs of
-// enqueue_headed_run (a replay places their two streams' kernels on queues of
-// its own; two streams of a program that holds many may share one: the 256^3
-// box in FP64 took 962 us/step launched directly against 912 replayed).  The
-// other steps that put kernels on both streams are launched directly:
-// replaying such a graph again while it ran has ended in a segmentation fault
-// of the host process.
+// Which steps a graph records: those that keep to one stream.  Steps that put
+// kernels on both streams are launched directly: twice, replaying a short
+// graph of such steps ended in a segmentation fault of the host process whose
+// cause is not known.  (A stream that its owner captures records what lb_step
+// enqueues on it.)
 bool graph_steps_apply(const lb_handle* h)
 {
-    if (fused_steps(h) || (large_chain_bound(h) && h->prec == LB_FP32_DEV)) return false;
-    return !h->batched || one_kernel_steps(h) || headed_steps(h) || h->lo.total_beads == 0 || h->lo.tiles_sparse == 0;
+    return !h->batched || one_kernel_steps(h) || h->lo.total_beads == 0 || h->lo.tiles_sparse == 0;
 }
 
 // n coupled steps from buffer `from`, step offsets 0..n-1, then the device
