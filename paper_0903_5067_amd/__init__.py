@@ -234,23 +234,19 @@ class LBSystem:
         return self._split(buf)
 
     def import_state(self, state: dict):
-        arrs, fits = [], len(state["boxes"]) == len(self.boxes)
+        head = np.array([state["step"]], dtype=np.uint64)   # refuses what is no step count
+        arrs, fits = [], len(state["boxes"]) == len(self.boxes) and head.ndim == 1
         for b, s in zip(self.boxes, state["boxes"]):
             for k in ("n", "x", "v", "f", "fc"):
                 a = np.ascontiguousarray(s[k], dtype=np.float64)
                 fits = fits and a.size == (19 * int(b["L"]) ** 3 if k == "n" else 3 * int(b["N"]))
                 arrs.append(a)
         if not fits:    # arrays of other sizes are taken, or refused, as one buffer
-            buf = self._join(state["step"], arrs)
+            buf = np.ascontiguousarray(np.concatenate([head.view(np.float64)] + [a.reshape(-1) for a in arrs]))
             _check(lib().lb_import_state(self.h, buf.ctypes.data_as(ctypes.c_void_p), buf.nbytes), self.h)
             return
         ptrs = (ctypes.c_void_p * len(arrs))(*[a.ctypes.data for a in arrs])
-        _check(lib().lb_import_arrays(self.h, int(state["step"]), ptrs, len(arrs)), self.h)
-
-    @staticmethod
-    def _join(step, arrs) -> np.ndarray:
-        head = np.array([step], dtype=np.uint64).view(np.float64)
-        return np.ascontiguousarray(np.concatenate([head] + [a.reshape(-1) for a in arrs]))
+        _check(lib().lb_import_arrays(self.h, int(head[0]), ptrs, len(arrs)), self.h)
 
     def _split(self, buf: np.ndarray) -> dict:
         step = int(buf[:1].view(np.uint64)[0])
