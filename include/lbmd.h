@@ -215,9 +215,11 @@ size_t lb_state_host_bytes(const lb_handle* h);
 lb_status lb_export_state(lb_handle* h, void* host_buf, size_t bytes);
 lb_status lb_import_state(lb_handle* h, const void* host_buf, size_t bytes);
 
-/* lb_import_state from arrays that lie apart: the step count, and per box n
- * [19][L^3], x, v, f and fc [N][3] (host, FP64; the last four may be null in a
- * box without beads), n_arrays = 5 per box.  Status as lb_import_state. */
+/* The same with arrays that lie apart: the step count, and per box n
+ * [19][L^3], x, v, f and fc [N][3] (host, FP64, caller-owned; the last four
+ * may be null in a box without beads), n_arrays = 5 per box.  Status as above;
+ * LB_EINVAL for another n_arrays or a null array. */
+lb_status lb_export_arrays(lb_handle* h, uint64_t* step, double* const* arrays, int32_t n_arrays);
 lb_status lb_import_arrays(lb_handle* h, uint64_t step, const double* const* arrays, int32_t n_arrays);
 
 /* Node impulses pending after lb_couple (the momentum the coupling of

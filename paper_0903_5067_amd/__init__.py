@@ -85,6 +85,7 @@ def lib() -> ctypes.CDLL:
         L.lb_state_host_bytes.restype = sz
         L.lb_export_state.argtypes = [vp, vp, sz]
         L.lb_import_state.argtypes = [vp, vp, sz]
+        L.lb_export_arrays.argtypes = [vp, ctypes.POINTER(ctypes.c_uint64), ctypes.POINTER(vp), i32]
         L.lb_import_arrays.argtypes = [vp, ctypes.c_uint64, ctypes.POINTER(vp), i32]
         L.lb_pending_impulse.argtypes = [vp, ctypes.POINTER(ctypes.c_double), sz]
         L.lb_velocity_history.argtypes = [vp, i64, ctypes.POINTER(ctypes.c_double), sz]
@@ -106,7 +107,7 @@ def lib() -> ctypes.CDLL:
         L.lb_last_error.argtypes = [vp]
         L.lb_last_error.restype = ctypes.c_char_p
         for name in ("lb_query_sizes", "lb_init", "lb_couple", "lb_step", "lb_observables", "lb_observables_static",
-                     "lb_export_state", "lb_import_state", "lb_import_arrays", "lb_pending_impulse",
+                     "lb_export_state", "lb_import_state", "lb_export_arrays", "lb_import_arrays", "lb_pending_impulse",
                      "lb_velocity_history", "lb_bead_positions", "lb_set_launch", "lb_collide_only", "lb_window_forward",
                      "lb_window_backward", "lb_window_rewind", "lb_set_rates", "lb_autotune",
                      "lb_set_collide_variant"):
@@ -228,10 +229,15 @@ class LBSystem:
         return res
 
     def export_state(self) -> dict:
-        nbytes = lib().lb_state_host_bytes(self.h)
-        buf = np.empty(nbytes // 8, dtype=np.float64)
-        _check(lib().lb_export_state(self.h, buf.ctypes.data_as(ctypes.c_void_p), nbytes), self.h)
-        return self._split(buf)
+        boxes = []
+        for b in self.boxes:
+            L, N = int(b["L"]), int(b["N"])
+            boxes.append({"n": np.empty((19, L, L, L)), **{k: np.empty((N, 3)) for k in ("x", "v", "f", "fc")}})
+        arrs = [a for s in boxes for a in s.values()]
+        ptrs = (ctypes.c_void_p * len(arrs))(*[a.ctypes.data for a in arrs])
+        step = ctypes.c_uint64()
+        _check(lib().lb_export_arrays(self.h, ctypes.byref(step), ptrs, len(arrs)), self.h)
+        return {"step": step.value, "boxes": boxes}
 
     def import_state(self, state: dict):
         head = np.array([state["step"]], dtype=np.uint64)   # refuses what is no step count
@@ -247,22 +253,6 @@ class LBSystem:
             return
         ptrs = (ctypes.c_void_p * len(arrs))(*[a.ctypes.data for a in arrs])
         _check(lib().lb_import_arrays(self.h, int(head[0]), ptrs, len(arrs)), self.h)
-
-    def _split(self, buf: np.ndarray) -> dict:
-        step = int(buf[:1].view(np.uint64)[0])
-        o = 1
-        boxes = []
-        for b in self.boxes:
-            L, N = int(b["L"]), int(b["N"])
-            V = L ** 3
-            n = buf[o:o + 19 * V].reshape(19, L, L, L)
-            o += 19 * V
-            arrs = []
-            for _ in range(4):
-                arrs.append(buf[o:o + 3 * N].reshape(N, 3))
-                o += 3 * N
-            boxes.append({"n": n, "x": arrs[0], "v": arrs[1], "f": arrs[2], "fc": arrs[3]})
-        return {"step": step, "boxes": boxes}
 
     def pending_impulse(self) -> list[np.ndarray]:
         total = sum(3 * int(b["L"]) ** 3 for b in self.boxes)

@@ -1233,6 +1233,66 @@ lb_status import_parts(lb_handle* h, uint64_t stepv, P part)
     return LB_OK;
 }
 
+// part(box, k): host array k of a box, as in import_parts
+template <typename P>
+lb_status export_parts(lb_handle* h, uint64_t* stepv, P part)
+{
+    const Layout& lo = h->lo;
+    const bool f64 = h->prec == LB_FP64;
+    HIPCHK(h, hipStreamSynchronize(h->stream));
+    Ctrl ctrl;
+    HIPCHK(h, hipMemcpy(&ctrl, h->scratch + lo.sc_ctrl, sizeof ctrl, hipMemcpyDeviceToHost));
+    *stepv = ctrl.step;
+    const void* A = h->pop(h->cur);
+    double* stage = (double*)h->pop(1 - h->cur);
+    for (int i = 0; i < h->n_boxes; ++i) {
+        const uint64_t V = lo.V[i];
+        double* n = part(i, 0);
+        const int per = (int)staged_planes(h, i);
+        for (int q = 0; q < 19; q += per) {
+            const int nq = std::min(per, 19 - q);
+            HIPCHK(h, f64 ? launch_export<double>(h->ctx, i, A, stage, q, nq)
+                          : launch_export<float>(h->ctx, i, A, stage, q, nq));
+            HIPCHK(h, hipMemcpyAsync(n + (uint64_t)q * V, stage, (size_t)nq * V * sizeof(double), hipMemcpyDeviceToHost,
+                                     h->stream));
+        }
+        const size_t nbb = (size_t)h->desc[i].n_beads * 3 * sizeof(double);
+        const size_t goff = lo.bead_off[i] * 3 * sizeof(double);
+        const size_t arrs[4] = {lo.st_x, lo.st_v, lo.st_f, lo.st_fc};
+        for (int k = 0; k < 4 && nbb; ++k)
+            HIPCHK(h, hipMemcpyAsync(part(i, 1 + k), h->state + arrs[k] + goff, nbb, hipMemcpyDeviceToHost, h->stream));
+    }
+    const lb_status st = clear_staging(h);
+    if (st != LB_OK) return st;
+    HIPCHK(h, hipStreamSynchronize(h->stream));
+    if (ctrl.health) return fail(h, LB_ENUMERIC, "device health flags set: " + std::to_string(ctrl.health));
+    return LB_OK;
+}
+
+// where box i's arrays start in a packed state's doubles
+std::vector<uint64_t> packed_offsets(const lb_handle* h)
+{
+    std::vector<uint64_t> at(h->n_boxes);
+    uint64_t o = 0;
+    for (int i = 0; i < h->n_boxes; ++i) {
+        at[i] = o;
+        o += 19 * h->lo.V[i] + 12 * (uint64_t)h->desc[i].n_beads;
+    }
+    return at;
+}
+uint64_t packed_part(const lb_handle* h, int i, int k)
+{
+    return k == 0 ? 0 : 19 * h->lo.V[i] + (uint64_t)(k - 1) * 3 * h->desc[i].n_beads;
+}
+
+lb_status check_arrays(lb_handle* h, const double* const* arrays, int32_t n_arrays)
+{
+    if (n_arrays != 5 * h->n_boxes) return fail(h, LB_EINVAL, "five arrays per box expected");
+    for (int k = 0; k < n_arrays; ++k)
+        if (!arrays[k] && (k % 5 == 0 || h->desc[k / 5].n_beads > 0)) return fail(h, LB_EINVAL, "null array");
+    return LB_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1241,39 +1301,20 @@ lb_status lb_export_state(lb_handle* h, void* host_buf, size_t bytes)
 {
     if (!h || !host_buf) return fail(h, LB_EINVAL, "null argument");
     if (bytes < lb_state_host_bytes(h)) return fail(h, LB_ENOMEM, "host buffer too small");
-    const Layout& lo = h->lo;
-    const bool f64 = h->prec == LB_FP64;
-    HIPCHK(h, hipStreamSynchronize(h->stream));
-    Ctrl ctrl;
-    HIPCHK(h, hipMemcpy(&ctrl, h->scratch + lo.sc_ctrl, sizeof ctrl, hipMemcpyDeviceToHost));
-    char* o = (char*)host_buf;
-    uint64_t stepv = ctrl.step;
-    std::memcpy(o, &stepv, sizeof stepv);
-    o += sizeof stepv;
-    const void* A = h->pop(h->cur);
-    double* stage = (double*)h->pop(1 - h->cur);
-    for (int i = 0; i < h->n_boxes; ++i) {
-        const uint64_t V = lo.V[i];
-        const int per = (int)staged_planes(h, i);
-        for (int q = 0; q < 19; q += per) {
-            const int nq = std::min(per, 19 - q);
-            HIPCHK(h, f64 ? launch_export<double>(h->ctx, i, A, stage, q, nq)
-                          : launch_export<float>(h->ctx, i, A, stage, q, nq));
-            HIPCHK(h, hipMemcpyAsync(o, stage, (size_t)nq * V * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-            o += (size_t)nq * V * sizeof(double);
-        }
-        const size_t nbb = (size_t)h->desc[i].n_beads * 3 * sizeof(double);
-        const size_t goff = lo.bead_off[i] * 3 * sizeof(double);
-        for (size_t arr : {lo.st_x, lo.st_v, lo.st_f, lo.st_fc}) {
-            if (nbb) HIPCHK(h, hipMemcpyAsync(o, h->state + arr + goff, nbb, hipMemcpyDeviceToHost, h->stream));
-            o += nbb;
-        }
-    }
-    const lb_status st = clear_staging(h);
+    const std::vector<uint64_t> at = packed_offsets(h);
+    uint64_t stepv = 0;
+    double* o = (double*)((char*)host_buf + sizeof stepv);
+    const lb_status st = export_parts(h, &stepv, [&](int i, int k) { return o + at[i] + packed_part(h, i, k); });
+    std::memcpy(host_buf, &stepv, sizeof stepv);
+    return st;
+}
+
+lb_status lb_export_arrays(lb_handle* h, uint64_t* step, double* const* arrays, int32_t n_arrays)
+{
+    if (!h || !step || !arrays) return fail(h, LB_EINVAL, "null argument");
+    const lb_status st = check_arrays(h, arrays, n_arrays);
     if (st != LB_OK) return st;
-    HIPCHK(h, hipStreamSynchronize(h->stream));
-    if (ctrl.health) return fail(h, LB_ENUMERIC, "device health flags set: " + std::to_string(ctrl.health));
-    return LB_OK;
+    return export_parts(h, step, [&](int i, int k) { return arrays[5 * i + k]; });
 }
 
 lb_status lb_import_state(lb_handle* h, const void* host_buf, size_t bytes)
@@ -1284,23 +1325,16 @@ lb_status lb_import_state(lb_handle* h, const void* host_buf, size_t bytes)
     HIPCHK(h, hipStreamSynchronize(h->stream));
     uint64_t stepv;
     std::memcpy(&stepv, host_buf, sizeof stepv);
-    std::vector<const double*> at(h->n_boxes);
+    const std::vector<uint64_t> at = packed_offsets(h);
     const double* o = (const double*)((const char*)host_buf + sizeof stepv);
-    for (int i = 0; i < h->n_boxes; ++i) {
-        at[i] = o;
-        o += 19 * h->lo.V[i] + 12 * (uint64_t)h->desc[i].n_beads;
-    }
-    return import_parts(h, stepv, [&](int i, int k) {
-        return k == 0 ? at[i] : at[i] + 19 * h->lo.V[i] + (uint64_t)(k - 1) * 3 * h->desc[i].n_beads;
-    });
+    return import_parts(h, stepv, [&](int i, int k) { return o + at[i] + packed_part(h, i, k); });
 }
 
 lb_status lb_import_arrays(lb_handle* h, uint64_t step, const double* const* arrays, int32_t n_arrays)
 {
     if (!h || !arrays) return fail(h, LB_EINVAL, "null argument");
-    if (n_arrays != 5 * h->n_boxes) return fail(h, LB_EINVAL, "five arrays per box expected");
-    for (int k = 0; k < n_arrays; ++k)
-        if (!arrays[k] && (k % 5 == 0 || h->desc[k / 5].n_beads > 0)) return fail(h, LB_EINVAL, "null array");
+    const lb_status st = check_arrays(h, arrays, n_arrays);
+    if (st != LB_OK) return st;
     if (h->pending) return fail(h, LB_ESTATE, "impulses pending from lb_couple");
     HIPCHK(h, hipStreamSynchronize(h->stream));
     return import_parts(h, step, [&](int i, int k) { return arrays[5 * i + k]; });

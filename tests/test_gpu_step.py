@@ -240,3 +240,39 @@ def test_observables_of_large_boxes(orc, L):
     assert got["mass"] == pytest.approx(want[0], rel=1e-12)
     np.testing.assert_allclose(got["p_total"], want[10:13], atol=1e-7)   # 4e6 nodes of ~1, summed in FP64
     np.testing.assert_allclose(got["mode_sq"], want[19:38], rtol=1e-9, atol=1e-20)
+
+
+@pytest.mark.parametrize("prec", [FP64, FP32])
+def test_packed_state_and_arrays_are_the_same(prec):
+    """lb_export_state / lb_import_state (one buffer) against lb_export_arrays /
+    lb_import_arrays, and what the array calls refuse."""
+    import ctypes
+
+    import paper_0903_5067_amd as lbm
+    say("packed state", prec)
+    boxes = [params(L=9, N=12, kT=1e-2, seed=6, box_id=0), params(L=4, N=0, kT=1e-2, seed=6, box_id=1)]
+    s = gpu_system(boxes, prec, xs=[chain(b) for b in boxes])
+    s.step(4)
+    L, st = lbm.lib(), s.export_state()
+    buf = np.empty(L.lb_state_host_bytes(s.h) // 8)
+    assert L.lb_export_state(s.h, buf.ctypes.data_as(ctypes.c_void_p), buf.nbytes) == lbm.LB_OK
+    arrs = [b[k] for b in st["boxes"] for k in ("n", "x", "v", "f", "fc")]
+    assert int(buf[:1].view(np.uint64)[0]) == st["step"] == 4
+    assert np.array_equal(buf[1:], np.concatenate([a.reshape(-1) for a in arrs]))
+    s.import_state(st)   # FP64 deviations come back to the last bit of n_i: both runs go on from an import
+    s.step(3)
+    want = s.export_state()["boxes"]
+    assert L.lb_import_state(s.h, buf.ctypes.data_as(ctypes.c_void_p), buf.nbytes) == lbm.LB_OK
+    s.step(3)
+    _equal(s.export_state()["boxes"], want)
+    step, null = ctypes.c_uint64(), ctypes.c_void_p()
+    ptrs = [a.ctypes.data for a in arrs]
+    for bad in (ptrs[:5], [None] + ptrs[1:], ptrs[:2] + [None] + ptrs[3:]):
+        p = (ctypes.c_void_p * len(bad))(*bad)
+        assert L.lb_export_arrays(s.h, ctypes.byref(step), p, len(bad)) == lbm.LB_EINVAL
+        assert L.lb_import_arrays(s.h, 4, p, len(bad)) == lbm.LB_EINVAL
+    p = (ctypes.c_void_p * 10)(*(ptrs[:6] + [null] * 4))   # no beads in the second box
+    assert L.lb_export_arrays(s.h, ctypes.byref(step), p, 10) == lbm.LB_OK and step.value == 7
+    _equal(st["boxes"], want)
+    assert L.lb_import_arrays(s.h, 7, p, 10) == lbm.LB_OK
+    s.close()

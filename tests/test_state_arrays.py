@@ -23,16 +23,33 @@ class Library:
     def lb_state_host_bytes(self, h):
         return 8 * (1 + sum(19 * int(b["L"]) ** 3 + 12 * int(b["N"]) for b in BOXES))
 
+    def lb_export_state(self, h, buf, nbytes):
+        a = np.ctypeslib.as_array(ctypes.cast(buf, ctypes.POINTER(ctypes.c_double)), (nbytes // 8,))
+        a[:1].view(np.uint64)[0], a[1:] = self.step, self.packed
+        return lbm.LB_OK
+
+    def lb_export_arrays(self, h, step, ptrs, n):
+        ctypes.cast(step, ctypes.POINTER(ctypes.c_uint64))[0] = self.step
+        o = 0
+        for p, s in zip(ptrs, self._sizes(n)):
+            if s:
+                np.ctypeslib.as_array(ctypes.cast(p, ctypes.POINTER(ctypes.c_double)), (s,))[:] = self.packed[o:o + s]
+            o += s
+        return lbm.LB_OK
+
+    def _sizes(self, n):
+        sizes = [s for b in BOXES for s in [19 * int(b["L"]) ** 3] + 4 * [3 * int(b["N"])]]
+        assert n == len(sizes)
+        return sizes
+
     def lb_import_state(self, h, buf, nbytes):
         a = np.ctypeslib.as_array(ctypes.cast(buf, ctypes.POINTER(ctypes.c_double)), (nbytes // 8,))
         self.step, self.packed = int(a[:1].view(np.uint64)[0]), a[1:].copy()
         return lbm.LB_OK
 
     def lb_import_arrays(self, h, step, ptrs, n):
-        sizes = [s for b in BOXES for s in [19 * int(b["L"]) ** 3] + 4 * [3 * int(b["N"])]]
-        assert n == len(sizes)
-        parts = [np.ctypeslib.as_array(ctypes.cast(p, ctypes.POINTER(ctypes.c_double)), (s,)) for p, s in zip(ptrs, sizes)
-                 if s]
+        parts = [np.ctypeslib.as_array(ctypes.cast(p, ctypes.POINTER(ctypes.c_double)), (s,))
+                 for p, s in zip(ptrs, self._sizes(n)) if s]
         self.step, self.packed = ctypes.c_uint64(step).value, np.concatenate(parts)
         return lbm.LB_OK
 
@@ -85,3 +102,16 @@ def test_import_of_other_layouts(system):
     st["boxes"][2]["fc"] = np.zeros((9, 3))
     system.import_state(st)
     assert system.L.packed.size == want.size + 21
+
+
+def test_exported_arrays_are_independent(system):
+    """Each array owns its memory: one that is kept does not keep the others."""
+    st = _state(41)
+    system.import_state(st)
+    got = system.export_state()
+    assert got["step"] == 41
+    for b, w in zip(got["boxes"], st["boxes"]):
+        assert list(b) == ["n", "x", "v", "f", "fc"]
+        for k, a in b.items():
+            assert np.array_equal(a, w[k]) and a.shape == w[k].shape and a.dtype == np.float64
+            assert a.base is None and a.flags.c_contiguous and a.flags.writeable, k
