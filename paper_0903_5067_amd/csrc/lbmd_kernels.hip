@@ -475,7 +475,7 @@ struct ChainLds {
         struct {
             double xs[2][3 * MB];   // positions of this and the previous substep
         };
-        uint32_t hash[MB >= 256 ? 4096 : 1024];   // after the substeps: nodes set aside for the next step
+        uint32_t hash[MB > 64 ? 4096 : 1024];   // after the substeps: nodes set aside for the next step
     };
     int moved[3];                  // per substep mod 3: a bead moved past half the skin
     uint32_t n_ovf, n_next;        // one-kernel steps: impulses outside the set-aside nodes, next step's such nodes
@@ -1927,11 +1927,11 @@ __device__ __forceinline__ void step_tile(const BoxDev* __restrict__ boxes, cons
     collide_tile<R>(boxes, ccs, tile_box, bi, tile, A, B, ctrl, t, nullptr, lane);
 }
 
-// BT threads per workgroup, at least W waves per SIMD.  A chain's workgroup
-// needs couple_T lanes per bead; further threads clear the old mask and take
+// BT threads per workgroup, at least W waves per SIMD, chains of at most MB
+// beads.  A chain's workgroup needs couple_T lanes per bead; further threads clear the old mask and take
 // the first of its nodes while the bead's lanes set the next step's nodes
 // aside.
-template <typename R, int BT, int W>
+template <typename R, int BT, int W, int MB>
 __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(W))) void k_step(
     const BoxDev* __restrict__ boxes, const CollideConst<R>* __restrict__ ccs, const uint32_t* __restrict__ tile_box,
     const int32_t* __restrict__ list, uint32_t n_chain, uint32_t n_tiles, R* A, R* B, const R* Aprev, ChainArgs ca,
@@ -1946,7 +1946,7 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(W))) void k_
         if (BT == 256 || tile < n_tiles) step_tile<R>(boxes, ccs, tile_box, sa, tile, lane, A, B, ctrl, t);
         return;
     }
-    __shared__ ChainLds<BT == 1024 ? 256 : 64> sh;
+    __shared__ ChainLds<MB> sh;
     __builtin_amdgcn_s_setprio(3);   // latency-bound chain beside the bandwidth-bound tiles
     const int bi = list[blockIdx.x];
     const BoxDev bx = boxes[bi];   // a copy: its fields stay in registers across the substeps
@@ -1976,7 +1976,7 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(W))) void k_
     if (T == 4) hbits = chain_substeps<R, 4, true>(bx, A, ca, t, sh, sa.mask[p], xe, ve);
     else if (T == 8) hbits = chain_substeps<R, 8, true>(bx, A, ca, t, sh, sa.mask[p], xe, ve);
     else hbits = chain_substeps<R, 16, true>(bx, A, ca, t, sh, sa.mask[p], xe, ve);
-    constexpr int HASH = 16 * (BT == 1024 ? 256 : 64);
+    constexpr int HASH = sizeof(sh.hash) / sizeof(uint32_t);
     __syncthreads();   // every impulse of the box is in the field, the positions in LDS are done with
     for (int i = (int)threadIdx.x; i < HASH; i += BT) sh.hash[i] = 0u;
     __syncthreads();
@@ -2596,31 +2596,59 @@ hipError_t launch_couple(const LaunchCtx& c, const void* A, const int32_t* list,
 
 static StepArgs step_args(const LaunchCtx& c) { return StepArgs{{c.nmask[0], c.nmask[1]}, {c.nlist[0], c.nlist[1]}, c.step_rec}; }
 
+// Launch shapes of k_step (threads, waves per SIMD it is held to), us per step:
+//   - Chains to 64 beads, few tiles: 512 threads, whose spare ones take set-aside
+//     nodes and shorten the chain's end; many: 256, where the tiles set the
+//     time.  The line at 16 tiles per CU lies between the chains' lengths (256
+//     against 512 threads, FP32): 4 per CU, 16 beads 23.0 and 22.4, 64 beads
+//     48.4 and 44.7; 16 per CU, 16 beads 43.0 and 47.5, 64 beads 81.0 and 79.6;
+//     62 per CU, 64 beads 113 and 120.
+//   - Held to four waves per SIMD (128 VGPRs), as the tiles want it, the coupling
+//     code spills 55 VGPRs in FP32 and 85 in FP64 (free it takes 170 and 196).
+//     In FP64 that traffic shows with many chains of more than 32 beads at
+//     once: 128 boxes of 15^3, 64 beads 91.6, with three waves (170 VGPRs) 67.0;
+//     256 boxes of 12^3 101 and 78.  Above one chain per CU the fewer waves
+//     cost more (500 boxes of 10^3 126.5 and 128.3), as they do below 33 beads.
+//   - Chains of 65 to 128 beads: 512 threads, three waves; in FP32 four where
+//     the tiles set the time or chains fill the CUs.  1024 threads, three and
+//     four waves: FP64 32 boxes of 32^3, 100 beads 114, 91, 122; FP32 128^3,
+//     128 beads 88.9, 79.7, 91.5; 900 boxes of 16^3 426, 403, 348.
+//   - Longer chains need 1024 threads, and with them four waves.
 constexpr int STEP_FEW_TILES_PER_CU = 16;
 
-template <typename R, int BT, int W>
+template <typename R, int BT, int W, int MB>
 static void launch_step_v(const LaunchCtx& c, const int32_t* list, int n_list, void* A, void* B, const void* Aprev,
                           unsigned long long* imp_prev, uint32_t n_tiles, uint32_t s_off)
 {
     constexpr uint32_t M = BT / 256;
-    hipLaunchKernelGGL((k_step<R, BT, W>), dim3((uint32_t)n_list + (n_tiles + M - 1) / M), dim3(BT), 0, c.stream,
+    hipLaunchKernelGGL((k_step<R, BT, W, MB>), dim3((uint32_t)n_list + (n_tiles + M - 1) / M), dim3(BT), 0, c.stream,
                        c.boxes, (const CollideConst<R>*)c.ccs, c.tile_box, list, (uint32_t)n_list, n_tiles, (R*)A,
                        (R*)B, (const R*)Aprev, chain_args(c), imp_prev, step_args(c), c.claim, c.ctrl, s_off,
                        c.keep_imp);
 }
 
 template <typename R>
-hipError_t launch_step(const LaunchCtx& c, const int32_t* list, int n_list, int block, void* A, void* B,
+hipError_t launch_step(const LaunchCtx& c, const int32_t* list, int n_list, int block, int max_n, void* A, void* B,
                        const void* Aprev, unsigned long long* imp_prev, uint32_t n_tiles, uint32_t s_off)
 {
-    if (n_list <= 0 || n_tiles == 0 || block > 1024 || !c.step_rec) return hipErrorInvalidValue;
-    // few tiles: the chain sets the time, and threads beyond the beads' lanes
-    // shorten its end; many: the tiles do, in 256-thread workgroups where the
-    // chains fit them
+    if (n_list <= 0 || n_tiles == 0 || block > 1024 || block < 4 * max_n || !c.step_rec) return hipErrorInvalidValue;
     const bool few = n_tiles <= (uint32_t)(STEP_FEW_TILES_PER_CU * c.n_cu);
-    if (block > 256) launch_step_v<R, 1024, 4>(c, list, n_list, A, B, Aprev, imp_prev, n_tiles, s_off);
-    else if (few) launch_step_v<R, 512, 4>(c, list, n_list, A, B, Aprev, imp_prev, n_tiles, s_off);
-    else launch_step_v<R, 256, 4>(c, list, n_list, A, B, Aprev, imp_prev, n_tiles, s_off);
+    if (block > 512) {
+        launch_step_v<R, 1024, 4, 256>(c, list, n_list, A, B, Aprev, imp_prev, n_tiles, s_off);
+    } else if (block > 256) {
+        const bool tiles_bound = n_tiles > (uint32_t)(2 * STEP_FEW_TILES_PER_CU * c.n_cu) || n_list > c.n_cu / 2;
+        if (sizeof(R) == 4 && tiles_bound)
+            launch_step_v<R, 512, 4, 128>(c, list, n_list, A, B, Aprev, imp_prev, n_tiles, s_off);
+        else
+            launch_step_v<R, 512, 3, 128>(c, list, n_list, A, B, Aprev, imp_prev, n_tiles, s_off);
+    } else if (few) {
+        if (sizeof(R) == 8 && max_n > 32 && n_list <= c.n_cu)
+            launch_step_v<R, 512, 3, 64>(c, list, n_list, A, B, Aprev, imp_prev, n_tiles, s_off);
+        else
+            launch_step_v<R, 512, 4, 64>(c, list, n_list, A, B, Aprev, imp_prev, n_tiles, s_off);
+    } else {
+        launch_step_v<R, 256, 4, 64>(c, list, n_list, A, B, Aprev, imp_prev, n_tiles, s_off);
+    }
     return hipGetLastError();
 }
 
@@ -3295,9 +3323,9 @@ template hipError_t launch_collide_forced<double>(const LaunchCtx&, const void*,
                                                   uint32_t);
 template hipError_t launch_couple<float>(const LaunchCtx&, const void*, const int32_t*, int, int, uint32_t);
 template hipError_t launch_couple<double>(const LaunchCtx&, const void*, const int32_t*, int, int, uint32_t);
-template hipError_t launch_step<float>(const LaunchCtx&, const int32_t*, int, int, void*, void*, const void*,
+template hipError_t launch_step<float>(const LaunchCtx&, const int32_t*, int, int, int, void*, void*, const void*,
                                        unsigned long long*, uint32_t, uint32_t);
-template hipError_t launch_step<double>(const LaunchCtx&, const int32_t*, int, int, void*, void*, const void*,
+template hipError_t launch_step<double>(const LaunchCtx&, const int32_t*, int, int, int, void*, void*, const void*,
                                         unsigned long long*, uint32_t, uint32_t);
 template hipError_t launch_step_end<float>(const LaunchCtx&, const int32_t*, int, const void*, void*, uint32_t);
 template hipError_t launch_step_end<double>(const LaunchCtx&, const int32_t*, int, const void*, void*, uint32_t);

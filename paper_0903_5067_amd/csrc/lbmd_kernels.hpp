@@ -98,10 +98,11 @@ hipError_t launch_couple(const LaunchCtx& c, const void* A, const int32_t* list,
 // one whole step of boxes whose chains (those in `list`) have at most
 // BIG_CHAIN beads, from A into B; Aprev, imp_prev: the previous step's input
 // and impulse field (unused by the first step after launch_step_begin).
-// block: threads of the widest chain workgroup.  A run of steps starts with
+// block: threads of the widest chain workgroup, max_n: beads of the longest
+// chain.  A run of steps starts with
 // launch_step_begin and ends with launch_step_end on the last step's buffers.
 template <typename R>
-hipError_t launch_step(const LaunchCtx& c, const int32_t* list, int n_list, int block, void* A, void* B,
+hipError_t launch_step(const LaunchCtx& c, const int32_t* list, int n_list, int block, int max_n, void* A, void* B,
                        const void* Aprev, unsigned long long* imp_prev, uint32_t n_tiles, uint32_t s_off);
 hipError_t launch_step_begin(const LaunchCtx& c, const int32_t* list, int n_list, uint32_t s_off);
 template <typename R>

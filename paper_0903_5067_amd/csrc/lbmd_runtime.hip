@@ -528,15 +528,18 @@ lb_status enqueue_headed_run(lb_handle* h, int from, uint32_t n)
 
 // Batched coupled steps whose chains all have at most BIG_CHAIN beads run as
 // one kernel each (k_step).  Chains above 64 beads make its workgroups 512 or
-// 1024 threads wide, which costs the collide of a large box (16-19 % of it at
-// 256^3) more than the fix-up and the boundaries it saves (~20 us): such
-// batches take it up to ONE_KERNEL_NODES nodes.
-constexpr uint64_t ONE_KERNEL_NODES = 4ull << 20;
+// 1024 threads wide, which in FP32 costs the collide of a large box more than
+// the fix-up and the boundaries it saves: one box, 80 beads, one kernel against
+// fix-up form 231 and 242 us at 200^3, 343 and 342 at 228^3, 400 and 384 at
+// 240^3.  Such batches take it up to ONE_KERNEL_NODES nodes.  In FP64, where the
+// collide holds fewer waves anyway, one kernel is the faster to the largest
+// measured (256^3, 96 beads: 862 and 890; 128^3: 117 and 184).
+constexpr uint64_t ONE_KERNEL_NODES = 10ull << 20;
 bool one_kernel_steps(const lb_handle* h)
 {
     const Layout& lo = h->lo;
     return h->batched && h->overlap && !h->couple_host.empty() && lo.big_list.empty() &&
-           (lo.couple_block <= 256 || lo.total_nodes <= ONE_KERNEL_NODES);
+           (lo.couple_block <= 256 || h->prec == LB_FP64 || lo.total_nodes <= ONE_KERNEL_NODES);
 }
 
 // one such step with launch context c (k = 0 follows launch_step_begin and
@@ -547,8 +550,10 @@ lb_status enqueue_one(lb_handle* h, const LaunchCtx& c, void* A, void* B, const 
     const int nc = (int)h->couple_host.size();
     const uint32_t nt = (uint32_t)h->lo.total_tiles;
     HIPCHK(h, h->prec == LB_FP64
-                  ? launch_step<double>(c, h->couple_list, nc, h->lo.couple_block, A, B, Aprev, imp_prev, nt, s_off)
-                  : launch_step<float>(c, h->couple_list, nc, h->lo.couple_block, A, B, Aprev, imp_prev, nt, s_off));
+                  ? launch_step<double>(c, h->couple_list, nc, h->lo.couple_block, h->lo.max_N, A, B, Aprev, imp_prev,
+                                        nt, s_off)
+                  : launch_step<float>(c, h->couple_list, nc, h->lo.couple_block, h->lo.max_N, A, B, Aprev, imp_prev,
+                                       nt, s_off));
     return LB_OK;
 }
 

@@ -276,3 +276,26 @@ def test_packed_state_and_arrays_are_the_same(prec):
     _equal(st["boxes"], want)
     assert L.lb_import_arrays(s.h, 7, p, 10) == lbm.LB_OK
     s.close()
+
+
+@pytest.mark.parametrize("prec", [FP64, FP32])
+@pytest.mark.parametrize("n", [3, 129])
+def test_wide_chains_that_leave_their_set_aside_nodes(prec, n):
+    """The 512-thread shapes for 65 to 128 beads, few chains and more than half
+    as many as the GPU has CUs, one of them flying apart."""
+    say("wide chains", prec, n)
+    boxes = [params(L=16, N=100, kT=0.0, therm=0, seed=5, box_id=0)]
+    boxes += [params(L=11, N=65 + i % 64, kT=1e-2, seed=5, box_id=i) for i in range(1, n)]
+    xs = [chain(b) for b in boxes]
+    xs[0] = xs[0][0] + 0.93 * (xs[0] - xs[0][0])
+    ref = gpu_system(boxes, prec, xs=xs)
+    ref.set_launch(batched=True, overlap=False)
+    left = 0
+    for _ in range(4):
+        a = ref.export_state()["boxes"][0]
+        ref.step(1)
+        left += int(_left_set_aside(boxes[0], a["x"], a["v"], ref.export_state()["boxes"][0]["x"]).sum())
+    ref.close()
+    assert left > 0
+    want = _run(boxes, xs, prec, False, 0, (7,))
+    _equal(_run(boxes, xs, prec, True, 0, (1, 2, 4)), want)

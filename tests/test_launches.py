@@ -57,3 +57,29 @@ def test_graphs_hold_one_stream(record, batch, mode, prec):
         replays += c[0] == "replay"
     one_stream = mode == 0 or batch in ("dense", "fluid") or (mode != 2 and batch in ("small chains", "long small chains"))
     assert replays == (3 if one_stream else 0)
+
+
+def _steps(log):
+    names = [c[1] for c in log[log.index(["launch", "mode"]):] if c[0] == "launch" and len(c) > 2]
+    return names[0] if len(set(names)) == 1 else sorted(set(names))
+
+
+# both sides of every line of the rule: beads, tiles per CU (256 CUs in the
+# stand-in), chains per CU, nodes
+@pytest.mark.parametrize("n,L,N,fp64,fp32", [
+    (1, 16, 32, (512, 4, 64), (512, 4, 64)), (1, 16, 33, (512, 3, 64), (512, 4, 64)),
+    (256, 8, 64, (512, 3, 64), (512, 4, 64)), (257, 8, 64, (512, 4, 64), (512, 4, 64)),
+    (1, 101, 64, (512, 3, 64), (512, 4, 64)), (1, 102, 64, (256, 4, 64), (256, 4, 64)),
+    (1, 16, 65, (512, 3, 128), (512, 3, 128)), (1, 16, 128, (512, 3, 128), (512, 3, 128)),
+    (128, 8, 65, (512, 3, 128), (512, 3, 128)), (129, 8, 65, (512, 3, 128), (512, 4, 128)),
+    (1, 128, 65, (512, 3, 128), (512, 3, 128)), (1, 129, 65, (512, 3, 128), (512, 4, 128)),
+    (1, 16, 129, (1024, 4, 256), (1024, 4, 256)),
+    (1, 218, 65, (512, 3, 128), (512, 4, 128)), (1, 219, 65, (512, 3, 128), None),
+    (1, 219, 64, (256, 4, 64), (256, 4, 64))])
+def test_shapes_of_one_kernel_steps(record, n, L, N, fp64, fp32):
+    for prec, shape, real in ((FP64, fp64, "double"), (FP32, fp32, "float")):
+        got = _steps(record(prec, 1, 0, (1,), [(L, N, 0)] * n))
+        if shape is None:
+            assert not any(k.startswith("k_step") for k in got)
+        else:
+            assert got == sorted(["k_step_begin", f"k_step_end<{real}>", "k_step<%s,%d,%d,%d>" % (real, *shape)])
