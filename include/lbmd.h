@@ -184,13 +184,13 @@ lb_status lb_observables(lb_handle* h, lb_obs* out);
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the
  * observables of lb_observables, with the partial sums of the reduction in a
- * device array the library holds statically (LB_STATIC_SCRATCH_BYTES per
- * device, from the first lb_init on that device until the process ends)
+ * device array the library holds statically (LB_STATIC_SCRATCH_BYTES and 4 KB
+ * per device, from the first lb_init on that device until the process ends)
  * instead of the handle's scratch buffer.  Allocates nothing.  Same kernels
- * and summation order as lb_observables, so the same bits.  The partials
- * take 192 bytes per 4096 nodes of each box (rounded up per box) plus 12.5
- * KB per box; LB_ENOMEM if they exceed the array (the message gives both
- * sizes), LB_EDEVICE if the array's device address could not be found at
+ * and summation order as lb_observables, so the same bits.  A box counts 192
+ * bytes per 4096 nodes (rounded up) plus 12.5 KB, which holds its partials;
+ * LB_ENOMEM if the boxes count more than LB_STATIC_SCRATCH_BYTES (the message
+ * gives both sizes), LB_EDEVICE if the array's device address could not be found at
  * init.  Every call on one device shares that device's array: calls that
  * overlap on one GPU (other threads, other handles) race.  Every partial is
  * written before it is read, so nothing carries over between calls.

@@ -2348,9 +2348,8 @@ __device__ __forceinline__ double sum_records(const double* __restrict__ rec, ui
 }
 
 // boxes of more than STAT_DIRECT records: grid (STAT_CHUNKS, boxes), block
-// (c, box) sums range c of the box's records
-__global__ __launch_bounds__(256) void k_stats_mid(const BoxDev* __restrict__ boxes,
-                                                   const double* __restrict__ part, double* __restrict__ mid)
+// (c, box) sums range c of the box's records, into slot c behind them
+__global__ __launch_bounds__(256) void k_stats_mid(const BoxDev* __restrict__ boxes, double* part)
 {
     __shared__ double red[10][NSTAT];
     const BoxDev& bx = boxes[blockIdx.y];
@@ -2359,7 +2358,7 @@ __global__ __launch_bounds__(256) void k_stats_mid(const BoxDev* __restrict__ bo
     const uint32_t per = (nrec + STAT_CHUNKS - 1) / STAT_CHUNKS;
     const uint32_t t0 = min(nrec, blockIdx.x * per), t1 = min(nrec, t0 + per);
     const double s = sum_records(part + (uint64_t)(bx.stat_off + t0) * NSTAT, t1 - t0, red);
-    if (threadIdx.x < NSTAT) mid[((uint64_t)blockIdx.y * STAT_CHUNKS + blockIdx.x) * NSTAT + threadIdx.x] = s;
+    if (threadIdx.x < NSTAT) part[(uint64_t)(bx.stat_off + nrec + blockIdx.x) * NSTAT + threadIdx.x] = s;
 }
 
 // one block per box: the box's record of OBS_REC doubles, [0..23] the fluid
@@ -2371,8 +2370,8 @@ __global__ __launch_bounds__(256) void k_stats_mid(const BoxDev* __restrict__ bo
 constexpr int NCHAIN = NCHAIN_REC;
 
 __global__ __launch_bounds__(256) void k_obs(const BoxDev* __restrict__ boxes, ChainArgs ca,
-                                             const double* __restrict__ part, const double* __restrict__ mid,
-                                             const Ctrl* __restrict__ ctrl, double* __restrict__ out)
+                                             const double* __restrict__ part, const Ctrl* __restrict__ ctrl,
+                                             double* __restrict__ out)
 {
     __shared__ double red10[10][NSTAT];
     {
@@ -2380,7 +2379,7 @@ __global__ __launch_bounds__(256) void k_obs(const BoxDev* __restrict__ boxes, C
         const uint32_t nrec = stat_recs_of(bx.n_tiles);
         const double s = nrec <= STAT_DIRECT
                              ? sum_records(part + (uint64_t)bx.stat_off * NSTAT, nrec, red10)
-                             : sum_records(mid + (uint64_t)blockIdx.x * STAT_CHUNKS * NSTAT, STAT_CHUNKS, red10);
+                             : sum_records(part + (uint64_t)(bx.stat_off + nrec) * NSTAT, STAT_CHUNKS, red10);
         if (threadIdx.x < NSTAT) out[(uint64_t)blockIdx.x * OBS_REC + threadIdx.x] = s;
         if (threadIdx.x == 0) {
             out[(uint64_t)blockIdx.x * OBS_REC + NSTAT + NCHAIN] = (double)ca.nl_rebuilds[blockIdx.x];
@@ -2786,8 +2785,7 @@ hipError_t launch_advance(const LaunchCtx& c, uint32_t n)
 }
 
 template <typename R>
-hipError_t launch_observables(const LaunchCtx& c, const void* A, uint32_t max_recs, double* part, double* mid,
-                              double* out)
+hipError_t launch_observables(const LaunchCtx& c, const void* A, uint32_t max_recs, double* part, double* out)
 {
     // every box's population array under 4 GiB: 32-bit offsets
     bool o32 = true;
@@ -2801,9 +2799,9 @@ hipError_t launch_observables(const LaunchCtx& c, const void* A, uint32_t max_re
         hipLaunchKernelGGL((k_stats<R, false>), dim3(max_recs, c.n_boxes), dim3(STAT_BLOCK), 0, c.stream, c.boxes,
                            (const R*)A, part);
     if (max_recs > STAT_DIRECT)
-        hipLaunchKernelGGL(k_stats_mid, dim3(STAT_CHUNKS, c.n_boxes), dim3(256), 0, c.stream, c.boxes, part, mid);
+        hipLaunchKernelGGL(k_stats_mid, dim3(STAT_CHUNKS, c.n_boxes), dim3(256), 0, c.stream, c.boxes, part);
     hipLaunchKernelGGL(k_obs, dim3(c.n_boxes), dim3(256), 0, c.stream, c.boxes, chain_args(c), (const double*)part,
-                       (const double*)mid, (const Ctrl*)c.ctrl, out);
+                       (const Ctrl*)c.ctrl, out);
     return hipGetLastError();
 }
 
@@ -3337,7 +3335,7 @@ template hipError_t launch_collide_headed<float>(const LaunchCtx&, const void*, 
                                                  const int32_t*, int, int, const void*, int);
 template hipError_t launch_collide_headed<double>(const LaunchCtx&, const void*, void*, uint32_t, uint32_t,
                                                   const int32_t*, int, int, const void*, int);
-template hipError_t launch_observables<float>(const LaunchCtx&, const void*, uint32_t, double*, double*, double*);
-template hipError_t launch_observables<double>(const LaunchCtx&, const void*, uint32_t, double*, double*, double*);
+template hipError_t launch_observables<float>(const LaunchCtx&, const void*, uint32_t, double*, double*);
+template hipError_t launch_observables<double>(const LaunchCtx&, const void*, uint32_t, double*, double*);
 
 }  // namespace lbd

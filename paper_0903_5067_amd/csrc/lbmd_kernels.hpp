@@ -151,13 +151,12 @@ template <typename R>
 hipError_t launch_import(const LaunchCtx& c, int box, const double* n, void* A, int q0, int nq);
 template <typename R>
 hipError_t launch_clear_tails(const LaunchCtx& c, void* A);
-// observables of the state A: per-block records in part [sum of stat_recs_of(n_tiles)][NSTAT_REC]
-// (box b's from BoxDev::stat_off), sums of ranges of them in mid [n_boxes][STAT_CHUNKS][NSTAT_REC]
-// (boxes of more than STAT_DIRECT records), per-box records in out [n_boxes][OBS_REC], then the health
-// bits and the step; max_recs: the most records of any box
+// observables of the state A: per-block records in part [sum of stat_slots_of(n_tiles)][NSTAT_REC]
+// (box b's from BoxDev::stat_off, sums of ranges of them behind, in boxes of more than STAT_DIRECT
+// records), per-box records in out [n_boxes][OBS_REC], then the health bits and the step; max_recs: the
+// most records of any box
 template <typename R>
-hipError_t launch_observables(const LaunchCtx& c, const void* A, uint32_t max_recs, double* part, double* mid,
-                              double* out);
+hipError_t launch_observables(const LaunchCtx& c, const void* A, uint32_t max_recs, double* part, double* out);
 
 // device pointers of one reverse step of the adjoint window
 struct AdjArgsHost {
@@ -199,6 +198,12 @@ __host__ __device__ inline uint32_t stat_tpb(uint32_t n_tiles)
 __host__ __device__ inline uint32_t stat_recs_of(uint32_t n_tiles)
 {
     return (n_tiles + stat_tpb(n_tiles) - 1) / stat_tpb(n_tiles);
+}
+// records of a box with the ranges behind them: at most 64 + n_tiles / 16 (rounded up)
+__host__ __device__ inline uint32_t stat_slots_of(uint32_t n_tiles)
+{
+    const uint32_t n = stat_recs_of(n_tiles);
+    return n > STAT_DIRECT ? n + STAT_CHUNKS : n;
 }
 constexpr int NCHAIN_REC = 11;
 constexpr int OBS_REC = NSTAT_REC + NCHAIN_REC + 1;

@@ -29,10 +29,9 @@ using namespace lbd;
 // name stands for a host-side symbol, not a device address: kernels receive
 // the address hipGetSymbolAddress gives for the current device (static_scratch).
 constexpr size_t STATIC_SCRATCH_BYTES = LB_STATIC_SCRATCH_BYTES;
-// (boxes accepted by LB_STATIC_SCRATCH_BYTES need at most this much: their
-// block records fit into what that counts for records and ranges, and the
-// ranges of the large ones come on top)
-constexpr size_t STATIC_SCRATCH_ALLOC = 2 * STATIC_SCRATCH_BYTES + ((size_t)256 << 10);
+// (a box's partials fit into what LB_STATIC_SCRATCH_BYTES counts for it but
+// for 8 bytes, in boxes of 4097 to 12000 tiles, which count 61 KB or more each)
+constexpr size_t STATIC_SCRATCH_ALLOC = STATIC_SCRATCH_BYTES + 4096;
 static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_ALLOC];
 
 namespace {
@@ -75,11 +74,11 @@ struct Layout {
     uint64_t tiles_sparse = 0, beads_sparse = 0;      // collide tiles (first in tile order) and beads of the other boxes
     uint64_t pop_elems = 0, total_tiles = 0, total_beads = 0, total_nodes = 0;
     std::vector<uint32_t> stat_off;                   // per box: first observable partial record
-    uint32_t stat_recs = 0, stat_max_recs = 0;        // records of all boxes, of the largest box
+    uint32_t stat_recs = 0, stat_max_recs = 0;        // record slots of all boxes, records of the largest box
     size_t st_popA = 0, st_popB = 0, st_x = 0, st_v = 0, st_f = 0, st_fc = 0, state_bytes = 0;
     size_t sc_ctrl = 0, sc_boxes = 0, sc_ccs = 0, sc_tilebox = 0, sc_couple = 0, sc_imp = 0, sc_claim = 0,
            sc_touched = 0, sc_tcnt = 0, sc_beadbox = 0, sc_nlcnt = 0, sc_nlidx = 0, sc_nlx0 = 0,
-           sc_part = 0, sc_mid = 0, sc_obs = 0, sc_vhist = 0, sc_nlreb = 0, sc_biglist = 0, sc_alllist = 0,
+           sc_part = 0, sc_obs = 0, sc_vhist = 0, sc_nlreb = 0, sc_biglist = 0, sc_alllist = 0,
            sc_nearu = 0, sc_nearc = 0, sc_subrec = 0, sc_field = 0,
            sc_defer = 0, sc_dclaim = 0, sc_dlist = 0, sc_ovf = 0, sc_ovm = 0, sc_nmask[2] = {0, 0}, sc_nlist[2] = {0, 0},
            sc_steprec = 0, scratch_bytes = 0;
@@ -138,7 +137,7 @@ Layout make_layout(const lb_box_desc* b, int32_t n, int32_t prec, int32_t hist)
         Lo.n_tiles.push_back((uint32_t)((V + 255) / 256));
         tiles += (V + 255) / 256;
         Lo.stat_off.push_back(Lo.stat_recs);
-        Lo.stat_recs += stat_recs_of(Lo.n_tiles.back());
+        Lo.stat_recs += stat_slots_of(Lo.n_tiles.back());
         Lo.stat_max_recs = std::max(Lo.stat_max_recs, stat_recs_of(Lo.n_tiles.back()));
         // a chain on the workgroup path whose stencils (8 nodes per bead)
         // cover a quarter of the box or more: re-colliding its nodes in a
@@ -220,7 +219,6 @@ Layout make_layout(const lb_box_desc* b, int32_t n, int32_t prec, int32_t hist)
     Lo.sc_nlidx = o; o = align256(o + nbx * NL_CAP * sizeof(uint16_t));
     Lo.sc_nlx0 = o; o = align256(o + std::max<uint64_t>(beads, 1) * 3 * sizeof(double));
     Lo.sc_part = o; o = align256(o + (size_t)Lo.stat_recs * NSTAT_REC * sizeof(double));
-    Lo.sc_mid = o; o = align256(o + (size_t)n * STAT_CHUNKS * NSTAT_REC * sizeof(double));
     Lo.sc_obs = o; o = align256(o + ((size_t)n * OBS_REC + 2) * sizeof(double));
     Lo.sc_vhist = o; o = align256(o + (size_t)hist * std::max<uint64_t>(beads, 1) * 3 * sizeof(double));
     Lo.sc_nlreb = o; o = align256(o + n * sizeof(uint32_t));
@@ -1104,11 +1102,10 @@ lb_status lb_observables(lb_handle* h, lb_obs* out)
     if (!h || !out) return fail(h, LB_EINVAL, "null argument");
     const Layout& lo = h->lo;
     double* part = (double*)(h->scratch + lo.sc_part);
-    double* mid = (double*)(h->scratch + lo.sc_mid);
     double* obs = (double*)(h->scratch + lo.sc_obs);
     const void* A = h->pop(h->cur);
-    HIPCHK(h, h->prec == LB_FP64 ? launch_observables<double>(h->ctx, A, lo.stat_max_recs, part, mid, obs)
-                                 : launch_observables<float>(h->ctx, A, lo.stat_max_recs, part, mid, obs));
+    HIPCHK(h, h->prec == LB_FP64 ? launch_observables<double>(h->ctx, A, lo.stat_max_recs, part, obs)
+                                 : launch_observables<float>(h->ctx, A, lo.stat_max_recs, part, obs));
     std::vector<double> rec((size_t)h->n_boxes * OBS_REC + 2);
     HIPCHK(h, hipMemcpyAsync(rec.data(), obs, rec.size() * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     HIPCHK(h, hipStreamSynchronize(h->stream));
@@ -1136,22 +1133,19 @@ lb_status lb_observables_static(lb_handle* h, lb_obs* out)
     if (need > STATIC_SCRATCH_BYTES)
         return fail(h, LB_ENOMEM, "boxes need " + std::to_string(need) + " bytes of partial sums; the static array holds " +
                                       std::to_string(STATIC_SCRATCH_BYTES));
-    // in the static array: block records, range sums (boxes that have them), box records
+    // in the static array: block records and range sums, box records
     const size_t part_b = align256((size_t)lo.stat_recs * NSTAT_REC * sizeof(double));
-    const size_t mid_b = lo.stat_max_recs > STAT_DIRECT
-                             ? align256((size_t)h->n_boxes * STAT_CHUNKS * NSTAT_REC * sizeof(double)) : 0;
     const size_t obs_b = align256(((size_t)h->n_boxes * OBS_REC + 2) * sizeof(double));
-    if (part_b + mid_b + obs_b > STATIC_SCRATCH_ALLOC)
+    if (part_b + obs_b > STATIC_SCRATCH_ALLOC)
         return fail(h, LB_ENOMEM, "partial sums beyond the static array");
     char* base = (char*)h->static_scr;
     double* part = (double*)base;
-    double* mid = (double*)(base + part_b);
-    double* obs = (double*)(base + part_b + mid_b);
+    double* obs = (double*)(base + part_b);
     const void* A = h->pop(h->cur);
     // every partial the kernels read is written earlier in the same call, so
     // no value carries over from a previous call
-    HIPCHK(h, h->prec == LB_FP64 ? launch_observables<double>(h->ctx, A, lo.stat_max_recs, part, mid, obs)
-                                 : launch_observables<float>(h->ctx, A, lo.stat_max_recs, part, mid, obs));
+    HIPCHK(h, h->prec == LB_FP64 ? launch_observables<double>(h->ctx, A, lo.stat_max_recs, part, obs)
+                                 : launch_observables<float>(h->ctx, A, lo.stat_max_recs, part, obs));
     double tail[2];
     HIPCHK(h, hipMemcpyAsync(tail, obs + (size_t)h->n_boxes * OBS_REC, sizeof tail, hipMemcpyDeviceToHost, h->stream));
     // results to the host in chunks of boxes, through a fixed buffer

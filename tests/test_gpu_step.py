@@ -299,3 +299,26 @@ def test_wide_chains_that_leave_their_set_aside_nodes(prec, n):
     assert left > 0
     want = _run(boxes, xs, prec, False, 0, (7,))
     _equal(_run(boxes, xs, prec, True, 0, (1, 2, 4)), want)
+
+
+@pytest.mark.parametrize("prec", [FP64, FP32])
+def test_observables_with_and_without_ranges_of_records(orc, prec):
+    """Boxes whose block records are summed at once beside ones that sum ranges
+    of them first (above 256 records: 104^3), in either order; in the static
+    array the same bits, and against the boxes alone."""
+    say("record ranges", prec)
+    boxes = [params(L=104, N=0, kT=1e-2, box_id=0), params(L=10, N=7, kT=1e-2, box_id=1), params(L=103, N=0, kT=1e-2, box_id=2),
+             params(L=105, N=30, kT=1e-2, box_id=3)]
+    xs = [chain(b) for b in boxes]
+    s = gpu_system(boxes, prec, xs=xs)
+    s.step(2)
+    got, static = s.observables(), s.observables(static=True)
+    s.close()
+    for i, b in enumerate(boxes):
+        one = gpu_system([b], prec, xs=[xs[i]])
+        one.step(2)
+        for o in (static[i], one.observables()[0]):
+            for k, v in got[i].items():
+                assert np.array_equal(v, o[k]), (i, k)
+        one.close()
+        assert got[i]["mass"] == pytest.approx(int(b["L"]) ** 3, rel=1e-6) and got[i]["mode_sq"][4] > 0

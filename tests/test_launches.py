@@ -83,3 +83,9 @@ def test_shapes_of_one_kernel_steps(record, n, L, N, fp64, fp32):
             assert not any(k.startswith("k_step") for k in got)
         else:
             assert got == sorted(["k_step_begin", f"k_step_end<{real}>", "k_step<%s,%d,%d,%d>" % (real, *shape)])
+
+
+def test_static_array_is_the_size_the_header_states(record):
+    """LB_STATIC_SCRATCH_BYTES (8 MiB) and 4 KB, as registered with the runtime."""
+    sizes = [int(c[2]) for c in record(FP32, 1, 0, (1,), [FLUID]) if c[0] == "var"]
+    assert sizes == [(8 << 20) + 4096]
