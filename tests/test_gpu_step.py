@@ -322,3 +322,95 @@ def test_observables_with_and_without_ranges_of_records(orc, prec):
                 assert np.array_equal(v, o[k]), (i, k)
         one.close()
         assert got[i]["mass"] == pytest.approx(int(b["L"]) ** 3, rel=1e-6) and got[i]["mode_sq"][4] > 0
+
+
+@pytest.mark.parametrize("prec,resident", [(FP32, True), (FP32, False), (FP64, True)])
+def test_large_chains_in_two_boxes_whose_collide_sets_the_time(prec, resident):
+    """Two sparse boxes with a large chain each, so many nodes that the collide
+    sets the step time: in FP32 the collides carry the node tables of both
+    (workgroups of two list entries, the overflow fix-up sorted by box), in
+    launch mode 3 and in FP64 the two queues alternate.  The second chain is
+    hot: its beads leave their tables.  Bits as with the re-collision after
+    the collide."""
+    say("two large chains, collide-bound", prec, resident)
+    hot = dict(kT=1.0, therm=0, zeta=1.0, k_fene=7.0, r0_fene=2.0)
+    base = dict(seed=7, md_dt=0.02, md_substeps=10, tau_lb=0.2)
+    boxes = [params(L=107, N=280, box_id=0, **base, kT=1e-2, k_fene=7.0, r0_fene=2.0, zeta=1.0),
+             params(L=107, N=300, box_id=1, **base, **hot)]
+    xs = [chain(b) for b in boxes]
+    s = gpu_system(boxes, prec, xs=xs)
+    s.set_launch(batched=True, overlap=False)
+    left = 0
+    for _ in range(8):
+        a = s.bead_positions()[280:]
+        s.step(1)
+        left += int((np.abs(np.floor(s.bead_positions()[280:]) + 0.5 - np.floor(a + 0.5)) > 1.0).any(1).sum())
+    assert all(o["health"] == 0 for o in s.observables())
+    want = s.export_state()["boxes"]
+    s.close()
+    assert left > 0
+    s = gpu_system(boxes, prec, xs=xs)
+    s.set_launch(batched=True, overlap=True, resident=resident)
+    for n in (5, 3):
+        s.step(n)
+    assert all(o["health"] == 0 for o in s.observables())
+    _equal(s.export_state()["boxes"], want)
+    s.close()
+
+
+@pytest.mark.parametrize("prec", [FP64, FP32])
+@pytest.mark.parametrize("batch", ["small chains", "fluid", "large chain"])
+def test_every_launch_shape_of_the_batched_collide(prec, batch):
+    """k_collide over several boxes in every launch shape: with chains of at
+    most 256 beads re-collided after it, with no chain, and with the stamps of
+    the deferred segments around a large chain.  The autotuner's choice too."""
+    import paper_0903_5067_amd as lbm
+    say("batched collide shapes", prec, batch)
+    boxes = {"small chains": [params(L=16, N=20, kT=1e-2, box_id=0), params(L=9, N=40, kT=1e-2, box_id=1)],
+             "fluid": [params(L=16, N=0, kT=1e-2, box_id=0), params(L=11, N=0, kT=1e-2, box_id=1)],
+             "large chain": [params(L=40, N=300, kT=1e-2, box_id=0), params(L=11, N=0, kT=1e-2, box_id=1)]}[batch]
+    s = gpu_system(boxes, prec, xs=[chain(b) for b in boxes])
+    s.set_launch(batched=True, overlap=batch != "small chains")
+    a = s.export_state()
+    want = None
+    for v in list(range(lbm.N_COLLIDE_VARIANTS)) + ["autotuned"]:
+        if v == "autotuned":
+            s.autotune(reps=2)
+        else:
+            s.set_collide_variant(v)
+        s.import_state(a)
+        s.step(5)
+        got = s.export_state()["boxes"]
+        want = want or got
+        _equal(got, want)
+    assert s.observables()[0]["health"] == 0
+    s.close()
+
+
+@pytest.mark.parametrize("N,k", [(16, 4), (16, 1), (100, 3)])
+def test_window_whose_beads_leave_their_set_aside_nodes(orc, N, k):
+    """A chain that flies apart inside a window: the impulses outside the
+    set-aside nodes are re-collided in the forward run and, from the tape
+    slots of the step before, in the replay; trajectory and gradient against
+    the oracle's exact tangent."""
+    say("window, left set-aside nodes", N, k)
+    p = params(L=16, N=N, kT=0.0, therm=0, omega_s=1.2, omega_b=0.9, seed=5)
+    x0 = chain(p)
+    x0 = x0[0] + 0.93 * (x0 - x0[0])
+    n0 = initial_pops(orc, p, amp=0.01, seed=11)
+    o, left = oracle_state(orc, p, n0, x0), 0
+    for _ in range(6):
+        a, v = o.x.copy(), o.v.copy()
+        o.run(1)
+        left += int(_left_set_aside(p, a, v, o.x).sum())
+    assert left > 0
+    s = gpu_system([p], FP64, xs=[x0], pops=[n0])
+    vh = s.window_forward(6, k)
+    cw = np.random.default_rng(5).normal(size=vh.shape)
+    grad = s.window_backward(cw)[0]
+    assert s.observables()[0]["health"] == 0
+    ho, dh = oracle_state(orc, p, n0, x0).window_tangent(6)
+    assert np.max(np.abs(vh - ho)) < 1e-10
+    ref = np.einsum("tna,tnak->k", cw, dh)
+    np.testing.assert_allclose(grad, ref, rtol=1e-7, atol=1e-7 * np.max(np.abs(ref)))
+    s.close()

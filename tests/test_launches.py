@@ -89,3 +89,22 @@ def test_static_array_is_the_size_the_header_states(record):
     """LB_STATIC_SCRATCH_BYTES (8 MiB) and 4 KB, as registered with the runtime."""
     sizes = [int(c[2]) for c in record(FP32, 1, 0, (1,), [FLUID]) if c[0] == "var"]
     assert sizes == [(8 << 20) + 4096]
+
+
+# (launch mode, batch, precision, kernels of one step among others, kernels that it has not)
+LAYOUTS = [
+    (1, [(107, 280, 0), (107, 300, 0)], FP32, {"k_collide_headed<float,5>", "k_chain_wg<float,512>"}, {"k_fixup<float>"}),
+    (3, [(107, 280, 0), (107, 300, 0)], FP32, {"k_near_nodes<float>", "k_overflow<float>"}, {"k_collide_headed<float,5>"}),
+    (1, [(107, 280, 0), (107, 300, 0)], FP64, {"k_near_nodes<double>", "k_overflow<double>"}, {"k_collide_headed<double,5>"}),
+    (1, [(40, 300, 0)], FP32, {"k_near_nodes<float>", "k_collide_deferred<float>"}, {"k_collide_headed<float,5>"}),
+    (2, [(40, 300, 0)], FP32, {"k_near_nodes<float>", "k_fixup<float>"}, {"k_collide_deferred<float>"}),
+    (1, [SMALL, LARGE], FP32, {"k_couple<float,256>", "k_collide_deferred<float>", "k_fixup<float>"}, {"k_step_begin"}),
+    (1, [DENSE], FP32, {"k_node_field<float>", "k_dense_impulse", "k_collide_forced<float>"}, {"k_near_nodes<float>"}),
+    (2, [SMALL], FP64, {"k_couple<double,256>", "k_fixup<double>"}, {"k_step_begin"})]
+
+
+@pytest.mark.parametrize("mode,boxes,prec,some,none", LAYOUTS)
+def test_kernels_of_a_run(record, mode, boxes, prec, some, none):
+    """Each layout of a run of steps is the one its GPU test means to reach."""
+    names = set(_steps(record(prec, mode, 0, (3,), boxes)))
+    assert some <= names and not none & names, names
