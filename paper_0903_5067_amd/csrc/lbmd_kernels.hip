@@ -2172,6 +2172,26 @@ __global__ void k_advance(Ctrl* ctrl, uint32_t n)
     if (threadIdx.x == 0 && blockIdx.x == 0) ctrl->step += n;
 }
 
+// ---------------------------------------------------------- queue probe
+// Do two streams run on hardware queues of their own?  k_probe_wait on one of
+// them waits for the flag that k_probe_set, launched after it on the other,
+// sets; on one queue the second starts when the first has ended, at its limit.
+constexpr uint64_t PROBE_TICKS = 20000;   // of the 100 MHz clock: 200 us
+__global__ void k_probe_wait(uint32_t* probe)
+{
+    const uint64_t t0 = wall_clock64();
+    bool set = false;
+    while (!set && wall_clock64() - t0 < PROBE_TICKS) {
+        set = __hip_atomic_load(probe, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
+        __builtin_amdgcn_s_sleep(8);
+    }
+    probe[1] = set ? 1u : 0u;
+}
+__global__ void k_probe_set(uint32_t* probe, uint32_t value)
+{
+    __hip_atomic_store(probe, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // ----------------------------------------------------------------- stats
 // Per tile of 256 nodes: FP64 sums of mass deviation, momentum, squared modes,
 // negative population count.  Layout of a record: [0] sum drho, [1..3] j,
@@ -2781,6 +2801,18 @@ hipError_t launch_init_forces(const LaunchCtx& c, const int32_t* list, int n_lis
 hipError_t launch_advance(const LaunchCtx& c, uint32_t n)
 {
     hipLaunchKernelGGL(k_advance, dim3(1), dim3(64), 0, c.stream, c.ctrl, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_probe_wait(hipStream_t stream, uint32_t* probe)
+{
+    hipLaunchKernelGGL(k_probe_wait, dim3(1), dim3(1), 0, stream, probe);
+    return hipGetLastError();
+}
+
+hipError_t launch_probe_set(hipStream_t stream, uint32_t* probe, uint32_t value)
+{
+    hipLaunchKernelGGL(k_probe_set, dim3(1), dim3(1), 0, stream, probe, value);
     return hipGetLastError();
 }
 

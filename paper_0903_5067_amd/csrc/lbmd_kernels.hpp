@@ -141,6 +141,9 @@ inline uint32_t head_blocks(int n_list, int max_n)
     return (uint32_t)n_list * (uint32_t)((max_n * NEAR_ITEMS + 255) / 256);
 }
 hipError_t launch_advance(const LaunchCtx& c, uint32_t n);
+// probe[0] set to value; probe[1] = whether probe[0] was set within 200 us
+hipError_t launch_probe_set(hipStream_t stream, uint32_t* probe, uint32_t value);
+hipError_t launch_probe_wait(hipStream_t stream, uint32_t* probe);
 hipError_t launch_init_forces(const LaunchCtx& c, const int32_t* list, int n_list, int block);
 // planes q0 .. q0 + nq - 1 of one box as canonical FP64 populations in n
 // [nq][L^3], from or into the stored populations A; zeros behind every box's

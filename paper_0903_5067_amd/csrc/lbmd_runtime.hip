@@ -81,7 +81,7 @@ struct Layout {
            sc_part = 0, sc_obs = 0, sc_vhist = 0, sc_nlreb = 0, sc_biglist = 0, sc_alllist = 0,
            sc_nearu = 0, sc_nearc = 0, sc_subrec = 0, sc_field = 0,
            sc_defer = 0, sc_dclaim = 0, sc_dlist = 0, sc_ovf = 0, sc_ovm = 0, sc_nmask[2] = {0, 0}, sc_nlist[2] = {0, 0},
-           sc_steprec = 0, scratch_bytes = 0;
+           sc_steprec = 0, sc_probe = 0, scratch_bytes = 0;
     uint64_t beads_big_sparse = 0;                    // beads of the chains above BIG_CHAIN in the other boxes
     uint32_t defer_cap = 0, ovf_cap = 0;              // deferred-tile list and overflow list entries
     int max_N = 0;         // largest chain taking the one-workgroup path
@@ -249,6 +249,7 @@ Layout make_layout(const lb_box_desc* b, int32_t n, int32_t prec, int32_t hist)
         }
         Lo.sc_steprec = o; o = align256(o + n * sizeof(StepRec));
     }
+    Lo.sc_probe = o; o = align256(o + 2 * sizeof(uint32_t));
     Lo.scratch_bytes = o;
     return Lo;
 }
@@ -786,6 +787,36 @@ lb_status prepare_graphs(lb_handle* h)
     return LB_OK;
 }
 
+// A stream whose kernels run beside those of `main`.  Streams share a few
+// hardware queues (four here), and which of them a new stream gets depends on
+// all others of the program: where it is main's, each step's chain work and
+// collide run one after the other (256^3, 1024 beads, FP64: 1041 against 905
+// us per step; the second of three systems of a program got it).  So a few
+// streams are tried; the last is taken if none runs apart (a tool that runs
+// one kernel at a time).
+hipError_t stream_apart(hipStream_t main, uint32_t* probe, hipStream_t* out)
+{
+    std::vector<hipStream_t> tried;
+    uint32_t apart = 0;
+    hipError_t e = launch_probe_set(main, probe, 0u);
+    while (e == hipSuccess && !apart && tried.size() < 4) {
+        hipStream_t s = nullptr;
+        e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+        if (e != hipSuccess) break;
+        tried.push_back(s);
+        e = launch_probe_set(main, probe, 0u);
+        if (e == hipSuccess) e = hipStreamSynchronize(main);
+        if (e == hipSuccess) e = launch_probe_wait(s, probe);
+        if (e == hipSuccess) e = launch_probe_set(main, probe, 1u);
+        if (e == hipSuccess) e = hipStreamSynchronize(main);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (e == hipSuccess) e = hipMemcpy(&apart, probe + 1, sizeof apart, hipMemcpyDeviceToHost);
+    }
+    *out = tried.empty() ? nullptr : tried.back();
+    for (size_t i = 0; i + 1 < tried.size(); ++i) (void)hipStreamDestroy(tried[i]);
+    return e;
+}
+
 }  // namespace
 
 extern "C" {
@@ -967,7 +998,8 @@ lb_status lb_init(const lb_box_desc* boxes, int32_t n_boxes, int32_t precision, 
     c.total_beads = nb;
     h->couple_list = (int32_t*)sc(lo.sc_couple);
     h->big_list = (int32_t*)sc(lo.sc_biglist);
-    e = hipStreamCreateWithFlags(&h->stream2, hipStreamNonBlocking);
+    e = lo.beads_big_sparse ? stream_apart(h->stream, (uint32_t*)sc(lo.sc_probe), &h->stream2)
+                            : hipStreamCreateWithFlags(&h->stream2, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&h->ev_fork, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&h->ev_join, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&h->ev_table, hipEventDisableTiming);

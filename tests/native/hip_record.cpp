@@ -2,7 +2,9 @@
 // points the library imports.  Memory is host memory, kernels do nothing, and
 // every launch, event and graph call is printed in order.  Test code only.
 //
-//   hip_record <precision> <mode> <graph_steps> <steps,steps,...> <L:N:chain_len,...>
+//   hip_record <precision> <mode> <graph_steps> <steps,steps,...> <L:N:chain_len,...> [shared]
+//
+// shared: that many streams after the first share its hardware queue.
 #include <hip/hip_runtime_api.h>
 
 #include <cstdio>
@@ -23,6 +25,7 @@ int id(const void* p) { return ids.emplace(p, (int)ids.size()).first->second; }
 uintptr_t next_handle = 0x1000;
 template <typename T> hipError_t make(T* out) { *out = (T)(next_handle += 16); id(*out); return hipSuccess; }
 bool capture = false;
+int shared = 0;
 struct Config { dim3 grid, block; size_t lds; hipStream_t stream; };
 std::vector<Config> configs;
 }  // namespace
@@ -54,8 +57,9 @@ hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* lds, hipStream_t*
     *g = c.grid; *b = c.block; *lds = c.lds; *s = c.stream;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void**, size_t, hipStream_t s)
+hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t, hipStream_t s)
 {
+    if (kernels()[f] == "k_probe_wait") (*(uint32_t**)args[0])[1] = id(s) > shared ? 1u : 0u;
     std::printf("launch %s stream %d grid %u,%u block %u\n", kernels()[f].c_str(), id(s), g.x, g.y, b.x);
     return hipSuccess;
 }
@@ -70,7 +74,7 @@ hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { std::mem
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(d, s, n); return hipSuccess; }
 hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) { std::memset(d, v, n); return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { return make(s); }
-hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t s) { std::printf("destroy %d\n", id(s)); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t* e) { return make(e); }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return make(e); }
@@ -107,6 +111,7 @@ hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
 int main(int argc, char** argv)
 {
     if (argc < 6) return 2;
+    shared = argc > 6 ? std::atoi(argv[6]) : 0;
     lb_handle* h = nullptr;
     std::vector<lb_box_desc> boxes;
     std::vector<double> x0;
@@ -129,6 +134,7 @@ int main(int argc, char** argv)
         std::printf("step %s\n", t);
         CHECK(lb_step(h, std::atoi(t)));
     }
+    std::printf("free\n");
     lb_free(h);
     return 0;
 }

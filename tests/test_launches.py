@@ -25,9 +25,9 @@ def record(tmp_path_factory):
                     os.path.join(HERE, "native", "hip_record.cpp"), lbm.LIB_PATH, "-Wl,--allow-shlib-undefined",
                     f"-Wl,-rpath,{os.path.dirname(lbm.LIB_PATH)}"], check=True, capture_output=True, text=True)
 
-    def run(prec, mode, graph, calls, boxes):
+    def run(prec, mode, graph, calls, boxes, shared=0):
         r = subprocess.run([exe, str(prec), str(mode), str(graph), ",".join(map(str, calls)),
-                            ",".join("%d:%d:%d" % b for b in boxes)], capture_output=True, text=True)
+                            ",".join("%d:%d:%d" % b for b in boxes), str(shared)], capture_output=True, text=True)
         assert r.returncode == 0, r.stdout[-500:] + r.stderr[-500:]
         return [line.split() for line in r.stdout.splitlines()]
     return run
@@ -108,3 +108,18 @@ def test_kernels_of_a_run(record, mode, boxes, prec, some, none):
     """Each layout of a run of steps is the one its GPU test means to reach."""
     names = set(_steps(record(prec, mode, 0, (3,), boxes)))
     assert some <= names and not none & names, names
+
+
+@pytest.mark.parametrize("shared", [0, 1, 3, 9])
+@pytest.mark.parametrize("batch", ["large chain", "small and large chains"])
+def test_two_stream_steps_get_a_queue_of_their_own(record, batch, shared):
+    """The second stream of steps with large chains is the first of four tried
+    that does not share the first stream's queue, or the last; the others are
+    gone before the steps."""
+    log = record(FP64, 1, 0, (3,), BATCHES[batch], shared)
+    before, steps = log[:log.index(["launch", "mode"])], log[log.index(["launch", "mode"]):log.index(["free"])]
+    tried = [c[3] for c in before if c[:2] == ["launch", "k_probe_wait"]]
+    assert len(tried) == min(shared, 3) + 1 == len(set(tried))
+    assert [c[1] for c in before if c[0] == "destroy"] == tried[:-1]
+    assert {c[3] for c in steps if c[0] == "launch" and len(c) > 2} == {"0", tried[-1]}
+    assert not any(c[:2] == ["launch", "k_probe_wait"] for c in record(FP64, 1, 0, (1,), BATCHES["small chains"], shared))
