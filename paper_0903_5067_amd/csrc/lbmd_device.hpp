@@ -92,6 +92,33 @@ constexpr double IMP_SCALE = 4503599627370496.0;          // 2^52
 constexpr double IMP_INV_SCALE = 1.0 / 4503599627370496.0;
 constexpr double IMP_MAX = 1024.0;                        // |impulse| bound per contribution
 
+// ------------------------------------------------------------------- cells
+// Node coordinate i in [-1, L] of a wrapped position, folded into the box edge
+// [0, L): rounding in the wrap can leave it one outside.  Any other i becomes
+// 0: beyond ~1e16 edges the wrapped coordinate is rounding noise of any size,
+// and a bead gets there within a few substeps of a broken bond (the health
+// word tells); no address may follow it.
+__host__ __device__ __forceinline__ int on_edge(int i, int L)
+{
+    return (uint32_t)i < (uint32_t)L ? i : (i == -1 ? L - 1 : 0);
+}
+
+// base-cell index and fraction of one coordinate (periodic, nodes at integers)
+__host__ __device__ __forceinline__ int cell_of(double xc, int L, double Ld, double iL, double& fr)
+{
+    const double xt = xc - Ld * floor(xc * iL);
+    const double fl = floor(xt);
+    fr = xt - fl;
+    return on_edge((int)fl, L);
+}
+
+// nearest node of a bead position, per axis
+__host__ __device__ __forceinline__ int nearest_of(double xc, int L, double Ld, double iL)
+{
+    const double xt = xc - Ld * floor(xc * iL);
+    return on_edge((int)floor(xt + 0.5), L);
+}
+
 // ----------------------------------------------------------------- Philox
 struct U4 { uint32_t x, y, z, w; };
 

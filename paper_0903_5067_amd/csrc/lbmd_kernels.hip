@@ -587,9 +587,7 @@ __device__ __forceinline__ uint32_t chain_substeps(const BoxDev& bx, const R* __
             const double xt = x - Ld * floor(x * iL);
             const double fl = floor(xt);
             fr = xt - fl;
-            ii = (int)fl;
-            if (ii >= L) ii -= L;
-            if (ii < 0) ii += L;
+            ii = on_edge((int)fl, L);
         }
         __syncthreads();
         // the same for every thread; flag s + 2 (mod 3) was last read a
@@ -824,26 +822,6 @@ __device__ __forceinline__ int list_cells(int L, double rl)
 }
 __device__ __forceinline__ int wrap_cell(int q, int nc) { return q < 0 ? q + nc : (q >= nc ? q - nc : q); }
 __device__ __forceinline__ int bucket_of(int cx, int cy, int cz) { return (cx & 15) | ((cy & 15) << 4) | ((cz & 15) << 8); }
-
-// base-cell index and fraction of one coordinate (periodic, nodes at integers)
-__device__ __forceinline__ int cell_of(double xc, int L, double Ld, double iL, double& fr)
-{
-    const double xt = xc - Ld * floor(xc * iL);
-    const double fl = floor(xt);
-    fr = xt - fl;
-    int ii = (int)fl;
-    if (ii >= L) ii -= L;
-    if (ii < 0) ii += L;
-    return ii;
-}
-
-// nearest node of a bead position, per axis
-__device__ __forceinline__ int nearest_of(double xc, int L, double Ld, double iL)
-{
-    const double xt = xc - Ld * floor(xc * iL);
-    int n = (int)floor(xt + 0.5);
-    return n >= L ? n - L : n;
-}
 
 // dense boxes: the velocity of every node, once per LB step, so that their
 // beads' tables read 3 values per node instead of gathering 19 populations

@@ -43,3 +43,12 @@ extern "C" void host_collide_f32(const double* n, const double* dp, double rho0,
     lbd::collide<float>(d, o, (float)dp[0], (float)dp[1], (float)dp[2], cc, node, step, k0, k1);
     for (int i = 0; i < 19; i++) out[i] = (double)o[i] + lbd::wv(i) * rho0;
 }
+
+// base cell, fraction and nearest node of n coordinates
+extern "C" void host_cells(const double* x, int n, int L, int* cell, double* fr, int* nearest)
+{
+    for (int i = 0; i < n; i++) {
+        cell[i] = lbd::cell_of(x[i], L, (double)L, 1.0 / L, fr[i]);
+        nearest[i] = lbd::nearest_of(x[i], L, (double)L, 1.0 / L);
+    }
+}

@@ -414,3 +414,41 @@ def test_window_whose_beads_leave_their_set_aside_nodes(orc, N, k):
     ref = np.einsum("tna,tnak->k", cw, dh)
     np.testing.assert_allclose(grad, ref, rtol=1e-7, atol=1e-7 * np.max(np.abs(ref)))
     s.close()
+
+
+@pytest.mark.parametrize("prec", [FP64, FP32])
+@pytest.mark.parametrize("L,N,chain_len,modes", [(16, 16, 0, (0, 1, 2)), (16, 33, 0, (1,)), (20, 100, 0, (0, 1, 2)), (16, 200, 0, (1,)),
+                                                 (40, 300, 0, (0, 1, 2)), (16, 512, 32, (0, 1)), (48, 600, 0, (1,))])
+def test_beads_beyond_any_box_address_nothing_outside(L, N, chain_len, modes, prec):
+    """Positions and velocities as a broken bond leaves them (far past the box,
+    not finite): the steps end with health bits set, and the same system goes
+    on from an imported state as if nothing had been."""
+    import ctypes
+
+    import paper_0903_5067_amd as lbm
+    say("broken bonds", L, N, prec)
+    p = params(L=L, N=N, chain_len=chain_len, kT=1e-2, seed=6)
+    for mode in modes:
+        say("launch mode", mode)
+        s = gpu_system([p], prec, xs=[chain(p)])
+        s.set_launch(batched=mode > 0, overlap=mode != 2)
+        good = s.export_state()
+        s.import_state(good)
+        s.step(3)
+        want = s.export_state()["boxes"]
+        bad = {"step": 0, "boxes": [{k: a.copy() for k, a in good["boxes"][0].items()}]}
+        b = bad["boxes"][0]
+        b["x"][0], b["x"][3], b["x"][N // 2] = 1e18, -3e25, (1e300, 5.0, -1e17)
+        b["v"][5], b["v"][N - 1] = 1e200, np.nan
+        s.import_state(bad)
+        s.step(3)
+        assert s.observables(allow_unhealthy=True)[0]["health"] != 0
+        s.import_state(good)
+        s.step(3)
+        with pytest.raises(lbm.LBError):   # the health word stays
+            s.export_state()
+        got = {k: np.empty_like(a) for k, a in good["boxes"][0].items()}
+        ptrs = (ctypes.c_void_p * 5)(*[a.ctypes.data for a in got.values()])
+        assert lbm.lib().lb_export_arrays(s.h, ctypes.byref(ctypes.c_uint64()), ptrs, 5) == lbm.LB_ENUMERIC
+        _equal([got], want)
+        s.close()
