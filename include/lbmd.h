@@ -249,7 +249,8 @@ lb_status lb_bead_positions(lb_handle* h, double* host_out, size_t bytes);
  * not cover densely are collided beside the other nodes once the chain's
  * impulses are in; batched = 2 re-collides the chain's nodes after the
  * collide instead.  Batched steps of boxes whose chains all have at most 256
- * beads run as one kernel each (batched = 2: separate kernels, the chain's
+ * beads run as one kernel each (batched = 2, and in FP32 batches of more than
+ * 10 * 2^20 nodes with a chain above 64 beads: separate kernels, the chain's
  * nodes re-collided).  All forms compute the same bits.
  * graph_steps > 0 records that many LB steps (rounded up to even) in a HIP
  * graph and replays it; 0 launches kernels directly.  The graphs of both
@@ -330,7 +331,10 @@ lb_status lb_collide_only(lb_handle* h, int32_t n);
  * graphs (recording them again for the chosen shape), and writes each
  * variant's faster sweep average in microseconds per launch to
  * times_us[LB_N_COLLIDE_VARIANTS] (may be NULL) and the choice to *chosen (may
- * be NULL).  lb_set_collide_variant forces one (LB_EINVAL out of range).
+ * be NULL).  lb_set_collide_variant forces one (LB_EINVAL out of range).  The
+ * shape is that of the collide as a kernel of its own: one-kernel steps (see
+ * lb_set_launch) have shapes of their own, which neither call changes, and the
+ * collide that carries node tables follows variant 0 (4 waves per SIMD) only.
  * The arithmetic is the LB equation of Sec. II.B in every shape. */
 #define LB_N_COLLIDE_VARIANTS 13
 lb_status lb_autotune(lb_handle* h, int32_t reps, float* times_us, int32_t* chosen);

@@ -185,7 +185,8 @@ class LBSystem:
     def set_launch(self, batched: bool = True, graph_steps: int = 0, overlap: bool = True,
                    resident: bool = True):
         """Launch structure of step (lb_set_launch): batched or per box,
-        graph_steps per HIP graph (0: direct launches), overlap False to
+        graph_steps per HIP graph (0: direct launches; so are steps that use
+        two streams, whatever graph_steps is), overlap False to
         re-collide the chain's nodes after the collide, resident False to keep
         every chain kernel from waiting for a later collide (for tools that
         run one kernel at a time)."""
@@ -198,7 +199,8 @@ class LBSystem:
 
     def autotune(self, reps: int = 20):
         """Time every launch shape of the collide+stream kernel on this state
-        and keep the fastest; returns (chosen variant, microseconds per launch
+        and keep the fastest (one-kernel steps have shapes of their own, by
+        rule); returns (chosen variant, microseconds per launch
         of each variant)."""
         t = (ctypes.c_float * N_COLLIDE_VARIANTS)()
         ch = ctypes.c_int32()

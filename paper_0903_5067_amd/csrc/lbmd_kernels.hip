@@ -452,9 +452,11 @@ __device__ __forceinline__ void wca_add(const double x[3], const double* xs, con
 // words for cls = 1), set at the first substep and again whenever a coordinate
 // of some bead has moved more than half the skin / sqrt(3); the exact cut-off
 // decides, so the list's age does not show in the bits.
-// Measured per substep beside the step's tiles: 16 beads 0.84 us, 32 1.15,
-// 64 1.5, 128 2.7, where lanes that each repeated the whole bead but its pair
-// forces took 2.1, 1.9, 2.0 and 3.1 us (alone).
+// Measured per substep in a one-kernel step (24^3, kT = 0.01, dt = 0.005, list
+// builds and new stencils included): 16 beads 0.83 us, 32 1.34, 64 1.9, 128 2.8,
+// 256 6.5.  Near rest, where those are rare: 16 beads 0.84 us, 32 1.15, 64 1.5;
+// lanes that each repeated the whole bead but its pair forces took 2.1, 1.9 and
+// 2.0 us there (alone).
 
 // the same value, unknown to the compiler: keeps the addresses of rare paths
 // from being computed ahead of the substep loop and held through it
