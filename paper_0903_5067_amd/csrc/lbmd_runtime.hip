@@ -1287,15 +1287,19 @@ lb_status export_parts(lb_handle* h, uint64_t* stepv, P part)
             HIPCHK(h, hipMemcpyAsync(n + (uint64_t)q * V, stage, (size_t)nq * V * sizeof(double), hipMemcpyDeviceToHost,
                                      h->stream));
         }
-        const size_t nbb = (size_t)h->desc[i].n_beads * 3 * sizeof(double);
-        const size_t goff = lo.bead_off[i] * 3 * sizeof(double);
-        const size_t arrs[4] = {lo.st_x, lo.st_v, lo.st_f, lo.st_fc};
-        for (int k = 0; k < 4 && nbb; ++k)
-            HIPCHK(h, hipMemcpyAsync(part(i, 1 + k), h->state + arrs[k] + goff, nbb, hipMemcpyDeviceToHost, h->stream));
     }
     const lb_status st = clear_staging(h);
     if (st != LB_OK) return st;
     HIPCHK(h, hipStreamSynchronize(h->stream));
+    // the beads of all boxes in one copy (one per box and array took longer
+    // than the populations of small boxes)
+    std::vector<char> beads(lo.total_beads ? lo.state_bytes - lo.st_x : 0);
+    if (!beads.empty()) HIPCHK(h, hipMemcpy(beads.data(), h->state + lo.st_x, beads.size(), hipMemcpyDeviceToHost));
+    const size_t arrs[4] = {lo.st_x, lo.st_v, lo.st_f, lo.st_fc};
+    for (int i = 0; i < h->n_boxes; ++i)
+        for (int k = 0; k < 4 && h->desc[i].n_beads; ++k)
+            std::memcpy(part(i, 1 + k), beads.data() + (arrs[k] - lo.st_x) + lo.bead_off[i] * 3 * sizeof(double),
+                        (size_t)h->desc[i].n_beads * 3 * sizeof(double));
     if (ctrl.health) return fail(h, LB_ENUMERIC, "device health flags set: " + std::to_string(ctrl.health));
     return LB_OK;
 }

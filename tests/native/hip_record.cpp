@@ -70,8 +70,13 @@ hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t hipGetSymbolAddress(void** p, const void* s) { *p = (void*)s; return hipSuccess; }
 hipError_t hipMalloc(void** p, size_t n) { *p = std::calloc(n, 1); return hipSuccess; }
 hipError_t hipFree(void* p) { std::free(p); return hipSuccess; }
-hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
-hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind k)
+{
+    std::printf("copy %s %zu\n", k == hipMemcpyDeviceToHost ? "out" : "in", n);
+    std::memcpy(d, s, n);
+    return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind k, hipStream_t) { return hipMemcpy(d, s, n, k); }
 hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) { std::memset(d, v, n); return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { return make(s); }
 hipError_t hipStreamDestroy(hipStream_t s) { std::printf("destroy %d\n", id(s)); return hipSuccess; }
@@ -134,6 +139,9 @@ int main(int argc, char** argv)
         std::printf("step %s\n", t);
         CHECK(lb_step(h, std::atoi(t)));
     }
+    std::printf("export\n");
+    std::vector<char> state(lb_state_host_bytes(h));
+    CHECK(lb_export_state(h, state.data(), state.size()));
     std::printf("free\n");
     lb_free(h);
     return 0;

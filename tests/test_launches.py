@@ -60,7 +60,7 @@ def test_graphs_hold_one_stream(record, batch, mode, prec):
 
 
 def _steps(log):
-    names = [c[1] for c in log[log.index(["launch", "mode"]):] if c[0] == "launch" and len(c) > 2]
+    names = [c[1] for c in log[log.index(["launch", "mode"]):log.index(["export"])] if c[0] == "launch" and len(c) > 2]
     return names[0] if len(set(names)) == 1 else sorted(set(names))
 
 
@@ -117,9 +117,18 @@ def test_two_stream_steps_get_a_queue_of_their_own(record, batch, shared):
     that does not share the first stream's queue, or the last; the others are
     gone before the steps."""
     log = record(FP64, 1, 0, (3,), BATCHES[batch], shared)
-    before, steps = log[:log.index(["launch", "mode"])], log[log.index(["launch", "mode"]):log.index(["free"])]
+    before, steps = log[:log.index(["launch", "mode"])], log[log.index(["launch", "mode"]):log.index(["export"])]
     tried = [c[3] for c in before if c[:2] == ["launch", "k_probe_wait"]]
     assert len(tried) == min(shared, 3) + 1 == len(set(tried))
     assert [c[1] for c in before if c[0] == "destroy"] == tried[:-1]
     assert {c[3] for c in steps if c[0] == "launch" and len(c) > 2} == {"0", tried[-1]}
     assert not any(c[:2] == ["launch", "k_probe_wait"] for c in record(FP64, 1, 0, (1,), BATCHES["small chains"], shared))
+
+
+def test_export_copies_the_beads_of_all_boxes_at_once(record):
+    """Control words, the planes of each box (in two pieces where the staging
+    buffer does not hold them), then every box's beads."""
+    log = record(FP64, 1, 0, (1,), [(8, 4, 0), (6, 0, 0), (10, 7, 0)])
+    out = [int(c[2]) for c in log[log.index(["export"]):] if c[:2] == ["copy", "out"]]
+    assert sum(out[1:-1]) == sum(8 * 19 * L ** 3 for L in (8, 6, 10)) and out[-1] >= 4 * 3 * 8 * 11
+    assert len(out) <= 6
